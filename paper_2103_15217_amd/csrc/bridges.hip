@@ -3,23 +3,29 @@
 //  1. Spanning forest (the paper uses the connectivity code of Jaiganesh and
 //     Burtscher, which yields a spanning tree as a by-product): union-find
 //     hooking where a successful compare-and-swap of a root joins two
-//     different trees, so its edge is a forest edge; both of its slots are
-//     marked in a bitmask. Parallel copies of an edge are never forest edges
-//     and self-loops are skipped. Every vertex first hooks its first two
-//     distinct neighbours; then the most frequent root of a sample names the
-//     big component, and only rows of vertices outside it hook all their
-//     edges (an edge inside the big component joins nothing new).
-//  2. Euler tour of the forest as the paper's DCEL (Section 2.1) read from
-//     the CSR: the forest slots of a row, in row order, are the sorted run
-//     of B for that vertex, next() wraps inside the run, twin() is found by
-//     a search in the neighbour's run, succ = next(twin). The tours of all
-//     components are chained into one list (component roots in id order).
+//     different trees, so its edge is a forest edge. A root is hooked at most
+//     once, so the hooked root's id numbers the edge: half-edges 2e and 2e+1
+//     are its two directions, twins by numbering. Parallel copies of an edge
+//     are never forest edges and self-loops are skipped. Every vertex first
+//     hangs below its first neighbour, if that has a smaller id, and hooks
+//     its second; then the most frequent root of a sample names the big
+//     component, and only rows of vertices outside it hook all their edges
+//     (an edge inside the big component joins nothing new).
+//  2. Euler tour of the forest as the paper's DCEL (Section 2.1): succ(h) =
+//     next(twin(h)), next() cyclic over the half-edges that leave a vertex.
+//     Any cyclic order gives a tour and the bridges do not depend on it, so
+//     the half-edges of a vertex are kept as a linked list in the order they
+//     were found instead of being sorted. The tours of all components are
+//     chained into one list.
 //  3. One list ranking; a half-edge goes down iff it precedes its twin
 //     (Section 2), which gives every vertex its parent edge and subtree
 //     size. The preorder comes from an array scan over tour order of
 //     (down + starts-a-component) weights (Section 2.2).
 //  4. For every vertex the minimum and maximum preorder over itself and its
-//     non-forest neighbours (the paper's segreduce); stored by preorder.
+//     neighbours other than along its parent edge (the paper's segreduce
+//     leaves out all forest edges; a child's preorder lies inside the subtree
+//     interval of every vertex it could count for, so it changes no test);
+//     stored by preorder.
 //  5. low(v) / high(v) = range minimum / maximum of those over v's subtree
 //     interval, with a sparse table over 32-element blocks and per-position
 //     suffix-extreme bitmasks inside a block (the paper uses a segment tree).
@@ -38,11 +44,6 @@ constexpr int kMaxGrid = 1 << 20;  // workgroups of a grid-stride launch (a disp
 __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
-}
-
-__global__ void k_iota(int32_t* __restrict__ p, int32_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = (int32_t)i;
 }
 
 __device__ __forceinline__ int32_t ld(const int32_t* p) {
@@ -91,31 +92,32 @@ __device__ __forceinline__ int64_t cc_key(int32_t v, int32_t big) { return v == 
 // to its parent. A node of one tree is never hung under a node of the same
 // tree: the larger key of two such nodes is never that tree's root. Every
 // step moves the larger-key side strictly up, so the loop ends.
-// Returns true iff this call linked two trees (edge {u, w} joins the forest).
-__device__ bool cc_hook(int32_t* cc, int32_t u, int32_t w, int32_t big, bool* over) {
+// Returns the root this call hung under another tree (the id of the forest
+// edge {u, w}), or -1 if it linked nothing.
+__device__ int32_t cc_hook(int32_t* cc, int32_t u, int32_t w, int32_t big, bool* over) {
   int32_t p1 = ldc(cc + u), p2 = ldc(cc + w);
   for (int it = 0; it < (1 << 22); ++it) {
-    if (p1 == p2) return false;
+    if (p1 == p2) return -1;
     const bool up1 = cc_key(p1, big) > cc_key(p2, big);
     const int32_t hi = up1 ? p1 : p2, lo = up1 ? p2 : p1;
     int32_t ph = ldc(cc + hi);
-    if (ph == lo) return false;
+    if (ph == lo) return -1;
     if (ph == hi) {
       const int32_t old = atomicCAS(cc + hi, hi, lo);
-      if (old == hi) return true;
+      if (old == hi) return hi;
       ph = old;  // linked meanwhile: continue from its current parent
     }
     p1 = ldc(cc + ph);
     p2 = ldc(cc + lo);
   }
   *over = true;
-  return false;
+  return -1;
 }
 
-// mark slot k = (u, w) and its twin, the first (w, u) slot of row w
-__device__ void mark_forest(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int32_t nnz,
-                            uint32_t* __restrict__ tbits, int32_t k, int32_t u, int32_t w, bool* bad) {
-  atomicOr(tbits + (k >> 5), 1u << (k & 31));
+// slot of the twin of (u, w): the first (w, u) slot of row w (-1, flagged, if
+// there is none)
+__device__ int32_t twin_slot(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int32_t nnz,
+                             int32_t u, int32_t w, bool* bad) {
   const int32_t wbeg = min(max(row_ptr[w], 0), nnz);
   const int32_t wend = min(max(row_ptr[w + 1], wbeg), nnz);
   int32_t lo = wbeg, hi = wend;
@@ -124,21 +126,52 @@ __device__ void mark_forest(const int32_t* __restrict__ row_ptr, const int32_t* 
     if (col[mid] < u) lo = mid + 1;
     else hi = mid;
   }
-  if (lo < wend && col[lo] == u) atomicOr(tbits + (lo >> 5), 1u << (lo & 31));
-  else *bad = true;
+  if (lo < wend && col[lo] == u) return lo;
+  *bad = true;
+  return -1;
 }
 
 __device__ __forceinline__ int32_t clampi(int32_t x, int32_t lo, int32_t hi) { return min(max(x, lo), hi); }
 
-// row_ptr must be monotone from 0 to nnz; anything else is flagged
-__global__ void k_check_csr(const int32_t* __restrict__ row_ptr, int32_t n, int32_t nnz,
-                            uint32_t* __restrict__ status) {
+// Start of a forest, and its first round of links: a vertex whose first
+// neighbour has a smaller id hangs below it. Every vertex decides for itself
+// and ids strictly decrease upwards, so all these links are edges of one
+// forest and need no compare-and-swap (a device-scope one per vertex, at 24
+// G/s, and its dependent climb made this round 316 us at 2^22 vertices and
+// 2^25 edges; with plain stores it takes 81 us). Only local minima (smaller than every
+// neighbour) stay roots. row_ptr must be monotone from 0 to nnz, anything
+// else is flagged.
+// EDGES: keep the forest: a linked edge's record {u, w, slot (u, w), -} and
+// its half-edge out of u as u's list so far.
+template <bool EDGES>
+__global__ void k_forest_init(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int32_t n,
+                              int32_t nnz, int32_t* __restrict__ cc, int4* __restrict__ erec,
+                              int32_t* __restrict__ first, int32_t* __restrict__ next,
+                              uint32_t* __restrict__ status) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n) return;
-  const int32_t a = row_ptr[v], b = row_ptr[v + 1];
-  bool bad = a > b || a < 0 || b > nnz;
-  if (v == 0 && a != 0) bad = true;
-  if (v == n - 1 && b != nnz) bad = true;
+  const int32_t a0 = row_ptr[v], b0 = row_ptr[v + 1];
+  bool bad = a0 > b0 || a0 < 0 || b0 > nnz;
+  if (v == 0 && a0 != 0) bad = true;
+  if (v == n - 1 && b0 != nnz) bad = true;
+  const int32_t a = clampi(a0, 0, nnz), b = clampi(b0, a, nnz);
+  int32_t w = (int32_t)v;
+  if (a < b) {  // rows are sorted: no later slot has a smaller neighbour
+    w = col[a];
+    if ((uint32_t)w >= (uint32_t)n) {
+      bad = true;
+      w = (int32_t)v;
+    }
+  }
+  const bool link = w < (int32_t)v;
+  cc[v] = link ? w : (int32_t)v;
+  if (EDGES) {
+    first[v] = link ? (int32_t)(2 * v) : -1;
+    if (link) {
+      erec[v] = make_int4((int32_t)v, w, a, -1);
+      next[2 * v] = -1;
+    }
+  }
   if (bad) flag(status, ST_BAD_CSR);
 }
 
@@ -153,27 +186,37 @@ __device__ __forceinline__ int row_of(const int32_t* rp_lds, int cnt, int32_t k)
   return lo;
 }
 
-// Sampling phase: in round j every vertex hooks its j-th distinct neighbour
-// (rounds 0 .. kSample-1, each followed by a full path compression).
+// Second round: every vertex hooks its second distinct neighbour, and one
+// whose first is larger than itself (no link in the first round) that one
+// too. Both rounds end with a full path compression.
+// EDGES: only the lane of u touches u's list here, so the insertion of the
+// half-edge out of u needs no atomics; those out of the other ends follow in
+// k_link_in.
 constexpr int kSample = 2;
 
+template <bool EDGES>
 __global__ void k_hook_sample(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int32_t n,
-                              int32_t nnz, int32_t* cc, uint32_t* __restrict__ tbits, uint32_t* __restrict__ status,
-                              int jsel) {
+                              int32_t nnz, int32_t* cc, int4* __restrict__ erec, int32_t* __restrict__ first,
+                              int32_t* __restrict__ next, uint32_t* __restrict__ status) {
   const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (u >= n) return;
   const int32_t a = clampi(row_ptr[u], 0, nnz), b = clampi(row_ptr[u + 1], a, nnz);
   bool bad = false, over = false;
   int taken = 0;
-  for (int32_t k = a; k < b && taken <= jsel; ++k) {
+  for (int32_t k = a; k < b && taken < kSample; ++k) {
     const int32_t w = col[k];
     if ((uint32_t)w >= (uint32_t)n) {
       bad = true;
       continue;
     }
     if (w == u || (k > a && col[k - 1] == w)) continue;  // self-loop or a parallel copy
-    if (taken++ != jsel) continue;
-    if (cc_hook(cc, (int32_t)u, w, -1, &over)) mark_forest(row_ptr, col, nnz, tbits, k, (int32_t)u, w, &bad);
+    if (taken++ == 0 && w < u && k == a) continue;       // linked in the first round
+    const int32_t e = cc_hook(cc, (int32_t)u, w, -1, &over);
+    if (EDGES && e >= 0) {
+      erec[e] = make_int4((int32_t)u, w, k, -1);
+      next[2 * e] = first[u];
+      first[u] = 2 * e;
+    }
   }
   if (bad) flag(status, ST_BAD_CSR);
   if (over) flag(status, ST_OVERFLOW);
@@ -237,9 +280,13 @@ __global__ __launch_bounds__(kBigSample) void k_big_component(const int32_t* cc,
 // Remaining phase: rows of vertices outside the big component hook every
 // distinct neighbour. An edge between two vertices of the big component is
 // already inside one tree; any other edge is seen from an endpoint outside.
+// The lanes of one row run side by side here, so the list insertion is an
+// exchange.
+template <bool EDGES>
 __global__ __launch_bounds__(kB) void k_hook_rest(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                                                  int32_t n, int32_t nnz, int32_t* cc, const int32_t* __restrict__ bigp,
-                                                 uint32_t* __restrict__ tbits, uint32_t* __restrict__ status) {
+                                                 int4* __restrict__ erec, int32_t* first, int32_t* __restrict__ next,
+                                                 uint32_t* __restrict__ status) {
   __shared__ int32_t rp[kRowsPerBlock + 1];
   __shared__ uint8_t skip[kRowsPerBlock];
   const int32_t r0 = blockIdx.x * kRowsPerBlock;
@@ -262,255 +309,239 @@ __global__ __launch_bounds__(kB) void k_hook_rest(const int32_t* __restrict__ ro
       continue;
     }
     if (w == u || (k > rp[ri] && col[k - 1] == w)) continue;
-    if (cc_hook(cc, u, w, big, &over)) mark_forest(row_ptr, col, nnz, tbits, k, u, w, &bad);
+    const int32_t e = cc_hook(cc, u, w, big, &over);
+    if (EDGES && e >= 0) {
+      erec[e] = make_int4(u, w, k, -1);
+      next[2 * e] = atomicExch(first + u, 2 * e);
+    }
   }
   if (bad) flag(status, ST_BAD_CSR);
   if (over) flag(status, ST_OVERFLOW);
 }
 
-__device__ __forceinline__ uint32_t bits_in(const uint32_t* tbits, int32_t a, int32_t b, int32_t wd) {
-  // forest bits of slots [a, b) that fall into word wd
-  uint32_t x = tbits[wd];
-  const int64_t base = (int64_t)wd << 5;  // 64-bit: base + 32 reaches 2^31 in the last word
-  if (a > base) x &= ~0u << (int)(a - base);
-  if (b < base + 32) x &= (b - base <= 0) ? 0u : (~0u >> (int)(32 - (b - base)));
-  return x;
+// The other half-edge of every forest edge in front of its vertex's list
+// (cc[e] != e: root e was hooked, so edge e exists), and the slot of that
+// half-edge. The search is made here, one lane per edge, not in the hooking
+// kernels, whose lanes already climb. Bound by random accesses: an exchange
+// (25 G/s) and two or three lines of the twin's row per edge; 339 us at 2^22
+// vertices. It stands in place of sorted forest rows (both slots of every
+// edge marked by atomics, degrees, a scan, the fill and a twin search per
+// half-edge: 0.97 ms).
+__global__ void k_link_in(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
+                          const int32_t* __restrict__ cc, int4* __restrict__ erec, int32_t n, int32_t nnz,
+                          int32_t* first, int32_t* __restrict__ next, uint32_t* __restrict__ status) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= n || cc[e] == (int32_t)e) return;
+  const int4 r = erec[e];
+  const int32_t before = atomicExch(first + r.y, (int32_t)(2 * e + 1));
+  bool bad = false;
+  const int32_t t = twin_slot(row_ptr, col, nnz, r.x, r.y, &bad);
+  next[2 * e + 1] = before;
+  erec[e].w = t;
+  if (bad) flag(status, ST_BAD_CSR);
 }
 
-__global__ void k_tree_deg(const int32_t* __restrict__ row_ptr, const uint32_t* __restrict__ tbits, int32_t n,
-                           int32_t nnz, uint32_t* __restrict__ tdeg) {
-  const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= n) return;
-  const int32_t a = clampi(row_ptr[u], 0, nnz), b = clampi(row_ptr[u + 1], a, nnz);
-  uint32_t d = 0;
-  if (a < b)
-    for (int32_t wd = a >> 5; wd <= (b - 1) >> 5; ++wd) d += __popc(bits_in(tbits, a, b, wd));
-  tdeg[u] = d;
+// scalars of a forest
+enum {
+  FS_BIG = 0,    // the big component's root
+  FS_HEAD = 1,   // first half-edge of the chained tour, -1 if there is none
+  FS_LEN = 2,    // forest half-edges
+  FS_ROOTS = 3,  // components with an edge
+};
+
+__global__ void k_forest_scalars(int32_t* __restrict__ sc) {
+  sc[FS_HEAD] = -1;
+  sc[FS_LEN] = 0;
+  sc[FS_ROOTS] = 0;
 }
 
-// Forest entries of every vertex u at tptr[u]..: its forest slots in slot
-// order, the neighbour at each, and u. The vertices of a workgroup own one
-// contiguous output range; when it holds at most kFillStage entries it is
-// built in LDS and stored with consecutive lanes on consecutive addresses
-// (a lane per vertex storing its own entries leaves every line partly
-// written, four times the bytes); a longer range (a hub) is stored directly.
-constexpr int kFillStage = 2048;
+// The roots of the components that have an edge and the first half-edge of
+// each, in any order, and the number of forest half-edges. A workgroup takes
+// kRootPer vertices per lane, so the shared counters see one update of each
+// per 4096 vertices.
+constexpr int kRootPer = 16;
 
-__global__ __launch_bounds__(kB) void k_tree_fill(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-                            const uint32_t* __restrict__ tbits, const uint32_t* __restrict__ tptr, int32_t n,
-                            int32_t nnz, int32_t Lcap, int32_t* __restrict__ tslot, int32_t* __restrict__ tnbr,
-                            int32_t* __restrict__ tsrc) {
-  __shared__ int32_t st_slot[kFillStage], st_nbr[kFillStage], st_src[kFillStage];
-  const int64_t u0 = (int64_t)blockIdx.x * kB;
-  const int64_t u = u0 + threadIdx.x;
-  // tptr is an exclusive scan of the forest degrees (n + 1 entries), so the
-  // workgroup's entries are [J0, J1), cut at Lcap
-  const uint32_t J0 = tptr[u0];
-  const int64_t ue = (u0 + kB < (int64_t)n) ? u0 + kB : (int64_t)n;
-  const uint32_t J1 = min(tptr[ue], (uint32_t)Lcap);
-  const bool staged = J1 <= J0 || J1 - J0 <= (uint32_t)kFillStage;  // the same for every lane
-  if (u < n) {
-    const int32_t a = clampi(row_ptr[u], 0, nnz), b = clampi(row_ptr[u + 1], a, nnz);
-    uint32_t j = tptr[u];
-    for (int32_t wd = a >> 5; a < b && wd <= (b - 1) >> 5; ++wd) {
-      uint32_t x = bits_in(tbits, a, b, wd);
-      while (x) {
-        const int bit = __ffs((int)x) - 1;
-        x &= x - 1;
-        const int32_t k = (wd << 5) + bit;
-        if (j >= (uint32_t)Lcap) {  // only with a malformed CSR (flagged)
-          x = 0;
-          wd = b;
-          break;
-        }
-        if (staged) {
-          st_slot[j - J0] = k;
-          st_nbr[j - J0] = col[k];
-          st_src[j - J0] = (int32_t)u;
-        } else {
-          tslot[j] = k;
-          tnbr[j] = col[k];
-          tsrc[j] = (int32_t)u;
-        }
-        ++j;
+__global__ __launch_bounds__(kB) void k_roots(const int32_t* __restrict__ cc, const int32_t* __restrict__ first,
+                                             int32_t n, int32_t* __restrict__ roots, int32_t* __restrict__ heads,
+                                             int32_t* __restrict__ sc) {
+  __shared__ int32_t cnt[2], base;  // roots of this workgroup, its linked vertices; where its roots go
+  if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t v0 = (int64_t)blockIdx.x * (kB * kRootPer) + threadIdx.x;
+  uint32_t is = 0;
+  int32_t linked = 0, at = 0;
+#pragma unroll
+  for (int i = 0; i < kRootPer; ++i) {
+    const int64_t v = v0 + i * kB;
+    if (v >= n) break;
+    if (cc[v] != (int32_t)v) ++linked;
+    else if (first[v] >= 0) is |= 1u << i;
+  }
+  for (int d = 32; d >= 1; d >>= 1) linked += __shfl_xor(linked, d, 64);
+  if (__lane_id() == 0 && linked) atomicAdd(&cnt[1], linked);
+  if (is) at = atomicAdd(&cnt[0], __popc(is));
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (cnt[0]) base = atomicAdd(sc + FS_ROOTS, cnt[0]);
+    if (cnt[1]) atomicAdd(sc + FS_LEN, 2 * cnt[1]);
+  }
+  __syncthreads();
+  for (int i = 0; is != 0; ++i, is >>= 1) {
+    if (!(is & 1u)) continue;
+    const int64_t v = v0 + i * kB;
+    roots[base + at] = (int32_t)v;
+    heads[base + at] = first[v];
+    ++at;
+  }
+}
+
+// The list of component i's root ends by going on to component i + 1 instead
+// of wrapping: its list head becomes -3 - (that component's first half-edge,
+// -1 after the last), below -1.
+__global__ void k_chain(const int32_t* __restrict__ roots, const int32_t* __restrict__ heads,
+                        int32_t* __restrict__ sc, int32_t* __restrict__ first) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int32_t nroots = sc[FS_ROOTS];
+  if (i >= nroots) return;
+  if (i == 0) sc[FS_HEAD] = heads[0];
+  first[roots[i]] = -3 - (i + 1 < nroots ? heads[i + 1] : -1);
+}
+
+// successors of both half-edges of edge e (one lane each edge, so the list
+// pointers and the successors move as pairs), tour weights cleared and every
+// vertex without a preorder. Each vertex's list wraps once, so of the 2n
+// successors n gather a list head; otherwise bound by streaming (44 us at
+// 2^22 vertices).
+__global__ void k_forest_succ(const int32_t* __restrict__ cc, const int4* __restrict__ erec,
+                              const int32_t* __restrict__ next, const int32_t* __restrict__ first, int32_t n,
+                              int32_t* __restrict__ succ, uint32_t* __restrict__ dw, int32_t* __restrict__ pre) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= n) return;
+  int32_t s0 = -2, s1 = -2;
+  if (cc[e] != (int32_t)e) {
+    const int2 nx = reinterpret_cast<const int2*>(next)[e];
+    s0 = nx.y;  // succ(2e) = next(2e + 1), around the list of w
+    s1 = nx.x;
+    if (s0 < 0 || s1 < 0) {
+      const int4 r = erec[e];
+      if (s0 < 0) {
+        const int32_t f = first[r.y];
+        s0 = f >= 0 ? f : -3 - f;
+      }
+      if (s1 < 0) {
+        const int32_t f = first[r.x];
+        s1 = f >= 0 ? f : -3 - f;
       }
     }
   }
-  if (!staged) return;
-  __syncthreads();
-  if (J1 <= J0) return;
-  for (uint32_t i = threadIdx.x; i < J1 - J0; i += kB) {
-    tslot[J0 + i] = st_slot[i];
-    tnbr[J0 + i] = st_nbr[i];
-    tsrc[J0 + i] = st_src[i];
-  }
+  reinterpret_cast<int2*>(succ)[e] = make_int2(s0, s1);
+  reinterpret_cast<uint2*>(dw)[e] = make_uint2(0u, 0u);
+  pre[e] = -1;
 }
 
-// scalars: [0] = L (forest half-edges), [1] = global head, [2] = reach
-// twin and cyclic-next successor of every forest half-edge; ids >= L unused
-__global__ void k_succ_csr(const int32_t* __restrict__ tnbr, const int32_t* __restrict__ tsrc,
-                           const uint32_t* __restrict__ tptr, int32_t n, int32_t Lcap,
-                           const int32_t* __restrict__ sc, int32_t* __restrict__ ttwin, int32_t* __restrict__ succ,
-                           uint32_t* __restrict__ status) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= Lcap) return;
-  const int32_t L = sc[0];
-  if (h >= L) {
-    succ[h] = -2;
-    return;
-  }
-  const int32_t u = tsrc[h], w = tnbr[h];
-  if ((uint32_t)u >= (uint32_t)n || (uint32_t)w >= (uint32_t)n) {  // malformed CSR only
-    flag(status, ST_BAD_CSR);
-    ttwin[h] = (int32_t)h;
-    succ[h] = -1;
-    return;
-  }
-  const int32_t beg = min((int32_t)tptr[w], L);
-  const int32_t end = clampi((int32_t)tptr[w + 1], beg, L);
-  int32_t lo = beg, hi = end;
-  while (lo < hi) {
-    const int32_t mid = lo + ((hi - lo) >> 1);
-    if (tnbr[mid] < u) lo = mid + 1;
-    else hi = mid;
-  }
-  int32_t t = lo;
-  if (t >= end || tnbr[t] != u) {
-    flag(status, ST_BAD_CSR);
-    t = (int32_t)h;
-  }
-  ttwin[h] = t;
-  succ[h] = (t + 1 < end) ? t + 1 : beg;  // next() wraps to the run start
-}
-
-// component roots in id order: root u has cc[u] == u and forest degree > 0.
-// rflag[u] = 1 for roots (scanned afterwards into rpos).
-__global__ void k_root_flags(const int32_t* __restrict__ cc, const uint32_t* __restrict__ tdeg, int32_t n,
-                             uint32_t* __restrict__ rflag) {
-  const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= n) return;
-  rflag[u] = (ld(cc + u) == (int32_t)u && tdeg[u] > 0) ? 1u : 0u;
-}
-
-__global__ void k_root_list(const uint32_t* __restrict__ rflag, const uint32_t* __restrict__ rpos, int32_t n,
-                            int32_t* __restrict__ roots) {
-  const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= n) return;
-  if (rflag[u]) roots[rpos[u]] = (int32_t)u;
-}
-
-__global__ void k_set_len(const uint32_t* __restrict__ tptr, int32_t n, int32_t* __restrict__ sc) {
-  const int32_t L = (int32_t)min(tptr[n], (uint32_t)(2 * (n - 1)));
-  sc[0] = L;    // forest half-edges
-  sc[1] = -1;   // head, set by k_link_roots
-  sc[2] = L;    // elements the head must reach
-}
-
-// tail of component i (the half-edge into its root from the root's last
-// forest neighbour) links to the head of component i+1
-__global__ void k_link_roots(const int32_t* __restrict__ roots, const uint32_t* __restrict__ rpos,
-                             const uint32_t* __restrict__ rflag, const uint32_t* __restrict__ tptr,
-                             const int32_t* __restrict__ ttwin, int32_t n, int32_t* __restrict__ succ,
-                             int32_t* __restrict__ sc) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int32_t nroots = (int32_t)(rpos[n - 1] + rflag[n - 1]);
-  const int32_t L = sc[0];
-  if (i == 0) sc[1] = (nroots > 0 && (int32_t)tptr[roots[0]] < L) ? (int32_t)tptr[roots[0]] : -1;
-  if (i >= nroots) return;
-  const int32_t r = roots[i];
-  const int32_t last = (int32_t)tptr[r + 1] - 1;
-  if (last < 0 || last >= L) return;  // only with a malformed CSR (flagged)
-  const int32_t tail = ttwin[last];
-  int32_t nxt = -1;
-  if (i + 1 < nroots) nxt = min((int32_t)tptr[roots[i + 1]], L - 1);
-  succ[tail] = nxt;
-}
-
-__global__ void k_rank_of(const uint64_t* __restrict__ packed, const int2* __restrict__ off, int32_t nsub,
-                          int32_t Lcap, const int32_t* __restrict__ sc, int32_t* __restrict__ rank,
-                          uint32_t* __restrict__ status) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= Lcap) return;
-  if (h >= sc[0]) return;
-  const uint64_t p = packed[h];
-  uint32_t s = (uint32_t)p;
+__device__ __forceinline__ int32_t rank_at(uint64_t pk, const int2* __restrict__ off, int32_t nsub, bool* bad) {
+  uint32_t s = (uint32_t)pk;
   if (s >= (uint32_t)nsub) {
-    flag(status, ST_BAD_INDEX);
+    *bad = true;
     s = 0;
   }
-  rank[h] = off[s].x + (int32_t)((p >> 32) & 0xffffu);
+  return off[s].x + (int32_t)((pk >> 32) & 0xffffu);
 }
 
-// per forest half-edge: direction, parent edge and subtree size of the
-// child, and the scan weight in tour order. Each vertex gets one record
-// vrec = {rank of its entering half-edge (or of its component's first
-// half-edge), subtree size, CSR slot of its parent edge at the parent,
-// slot of the same edge in its own row}; the two slots are -1 at a root.
-__global__ void k_direction(const int32_t* __restrict__ rank, const int32_t* __restrict__ ttwin,
-                            const int32_t* __restrict__ tsrc, const int32_t* __restrict__ tnbr,
-                            const int32_t* __restrict__ tslot, const uint32_t* __restrict__ tptr,
-                            const int32_t* cc, int32_t n, int32_t Lcap, const int32_t* __restrict__ sc,
-                            uint32_t* __restrict__ dw, int4* __restrict__ vrec, uint32_t* __restrict__ dd,
-                            uint32_t* __restrict__ status) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int32_t L = sc[0];
-  if (h >= L) {
-    if (h < Lcap) {
-      dw[h] = 0u;
-      if (dd) dd[h] = 0u;
+// Per forest edge: the rank of its half-edge that goes down (the earlier
+// one), the child's subtree size (negative if the child is u, the first end)
+// and the weight 1 at that rank. The twins are neighbours, so two sublist
+// offsets are gathered and one weight scattered per edge (125 us at 2^22
+// vertices; with twins apart and a record scattered to every vertex, 384 us
+// and 67 us for the ranks before it). HYBRID: +1 / -1 at both ranks, whose prefix
+// sum is the depth (component tours are balanced).
+template <bool HYBRID>
+__global__ void k_direction(const uint64_t* __restrict__ packed, const int2* __restrict__ off, int32_t nsub,
+                            const int32_t* __restrict__ cc, int32_t n, const int32_t* __restrict__ sc,
+                            int2* __restrict__ ds, uint32_t* __restrict__ dw, uint32_t* __restrict__ status) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= n) return;
+  int2 d = make_int2(-1, 0);
+  if (cc[e] != (int32_t)e) {
+    const ulonglong2 pk = reinterpret_cast<const ulonglong2*>(packed)[e];
+    const int32_t L = sc[FS_LEN];
+    bool bad = false;
+    const int32_t r0 = rank_at(pk.x, off, nsub, &bad), r1 = rank_at(pk.y, off, nsub, &bad);
+    if (bad || (uint32_t)r0 >= (uint32_t)L || (uint32_t)r1 >= (uint32_t)L) {
+      flag(status, ST_BAD_INDEX);
+    } else {
+      const int32_t rd = min(r0, r1), ru = max(r0, r1);
+      const int32_t size = (ru - rd + 1) >> 1;
+      d = make_int2(rd, r0 < r1 ? size : -size);
+      dw[rd] = 1u;
+      if (HYBRID) dw[ru] = 0xffffffffu;
     }
-    return;
   }
-  const int32_t r = rank[h];
-  const int32_t t = ttwin[h];
-  const int32_t u = tsrc[h], w = tnbr[h];
-  if ((uint32_t)t >= (uint32_t)L || (uint32_t)u >= (uint32_t)n || (uint32_t)w >= (uint32_t)n) {
-    flag(status, ST_BAD_INDEX);
-    return;
-  }
-  const int32_t rt = rank[t];
-  const bool down = r < rt;
-  const bool head = (h == (int64_t)tptr[u]) && (ld(cc + u) == u);
-  if ((uint32_t)r >= (uint32_t)L) {
-    flag(status, ST_BAD_INDEX);
-    return;
-  }
-  dw[r] = (uint32_t)down + (uint32_t)head;
-  if (dd) dd[r] = down ? 1u : 0xffffffffu;  // +1 / -1: a prefix sum gives the depth (component tours are balanced)
-  if (down) vrec[w] = make_int4(r, (rt - r + 1) >> 1, tslot[h], tslot[t]);
-  if (head) {
-    const int32_t tail = ttwin[clampi((int32_t)tptr[u + 1] - 1, 0, L - 1)];
-    vrec[u] = make_int4(r, ((rank[tail] - r + 1) >> 1) + 1, -1, -1);
-  }
+  ds[e] = d;
 }
 
-// preorder of every vertex (-1 if isolated), and the vertex's subtree size
-// and forest-edge slots stored by preorder for the bridge test
-__global__ void k_preorder(const int4* __restrict__ vrec, const uint32_t* __restrict__ I, int32_t n, int32_t Lcap,
-                           int32_t* __restrict__ pre, int4* __restrict__ byp) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  const int4 vr = vrec[v];
-  const int32_t r = vr.x;
-  if (r < 0 || r >= Lcap) {
-    pre[v] = -1;
-    return;
+// the rank at which every component starts; its weight counts the root too
+__global__ void k_root_rank(const int32_t* __restrict__ heads, const uint64_t* __restrict__ packed,
+                            const int2* __restrict__ off, int32_t nsub, const int32_t* __restrict__ sc,
+                            int32_t* __restrict__ rrank, uint32_t* __restrict__ dw, uint32_t* __restrict__ status) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= sc[FS_ROOTS]) return;
+  bool bad = false;
+  int32_t r = rank_at(packed[heads[i]], off, nsub, &bad);
+  if (bad || (uint32_t)r >= (uint32_t)sc[FS_LEN]) {
+    flag(status, ST_BAD_INDEX);
+    r = 0;
   }
-  const int32_t ps = vr.z;
-  const int32_t p = (int32_t)I[r] - (ps < 0 ? 2 : 1);
-  pre[v] = p;
-  if ((uint32_t)p < (uint32_t)n) byp[p] = make_int4(vr.y, ps, vr.w, 0);
+  rrank[i] = r;
+  dw[r] = 2u;
 }
 
-// per vertex: min / max preorder over itself and its non-forest neighbours,
-// stored at its own preorder position (the paper's segreduce). 16 lanes
-// share a row: they read its slots side by side and combine with shuffles.
+// preorder of every child from the scanned weights, its slot of the parent
+// edge, and by preorder {subtree size, the parent edge's slot at the parent,
+// the slot at the child}. Bound by its scatters (4, 4 and 16 bytes per edge,
+// which cost the same) and the gathered weight: 170 us at 2^22 vertices.
+__global__ void k_preorder(const int2* __restrict__ ds, const int4* __restrict__ erec,
+                           const uint32_t* __restrict__ I, int32_t n, int32_t* __restrict__ pre,
+                           int32_t* __restrict__ uslot, int4* __restrict__ byp) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= n) return;
+  const int2 d = ds[e];
+  if (d.x < 0) return;
+  const int4 r = erec[e];
+  const bool down = d.y > 0;  // u is the parent
+  const int32_t child = down ? r.y : r.x, ps = down ? r.z : r.w, us = down ? r.w : r.z;
+  const int32_t p = (int32_t)I[d.x] - 1;
+  if ((uint32_t)p >= (uint32_t)n) return;  // only after a flagged error
+  pre[child] = p;
+  uslot[child] = us;
+  byp[p] = make_int4(abs(d.y), ps, us, 0);
+}
+
+// the same for the components' roots, which have no parent edge: a component
+// ends where the next one starts
+__global__ void k_root_preorder(const int32_t* __restrict__ roots, const int32_t* __restrict__ rrank,
+                                const uint32_t* __restrict__ I, int32_t n, const int32_t* __restrict__ sc,
+                                int32_t* __restrict__ pre, int32_t* __restrict__ uslot, int4* __restrict__ byp) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int32_t nroots = sc[FS_ROOTS];
+  if (i >= nroots) return;
+  const int32_t r = rrank[i], end = i + 1 < nroots ? rrank[i + 1] : sc[FS_LEN];
+  const int32_t p = (int32_t)I[r] - 2;
+  if ((uint32_t)p >= (uint32_t)n) return;
+  pre[roots[i]] = p;
+  uslot[roots[i]] = -1;
+  byp[p] = make_int4(((end - r) >> 1) + 1, -1, -1, 0);
+}
+
+// per vertex: min / max preorder over itself and its neighbours, the parent
+// edge's own slot left out, stored at its preorder position (the paper's
+// segreduce) as one 8-byte store. 16 lanes share a row: they read its slots
+// side by side and combine with shuffles.
 constexpr int kRowLanes = 16;
 
 __global__ __launch_bounds__(kB) void k_minmax(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-                                              const uint32_t* __restrict__ tbits, const int32_t* __restrict__ pre,
-                                              int32_t n, int32_t nnz, int32_t* __restrict__ amin,
-                                              int32_t* __restrict__ amax) {
+                                              const int32_t* __restrict__ uslot, const int32_t* __restrict__ pre,
+                                              int32_t n, int32_t nnz, int2* __restrict__ amm) {
   const int sub = threadIdx.x & (kRowLanes - 1);
   const int64_t groups = (int64_t)gridDim.x * (blockDim.x / kRowLanes);
   // rows stride over the grid: 16 lanes per row would exceed the 2^32
@@ -519,10 +550,11 @@ __global__ __launch_bounds__(kB) void k_minmax(const int32_t* __restrict__ row_p
     const int32_t p = pre[u];
     if (p < 0 || p >= n) continue;    // isolated vertex (the whole row group skips together)
     const int32_t a = clampi(row_ptr[u], 0, nnz), b = clampi(row_ptr[u + 1], a, nnz);
+    const int32_t up = uslot[u];
     int32_t mn = p, mx = p;
     for (int64_t kk = (int64_t)a + sub; kk < b; kk += kRowLanes) {  // b may lie within one stride of 2^31
       const int32_t k = (int32_t)kk;
-      if ((tbits[k >> 5] >> (k & 31)) & 1u) continue;
+      if (k == up) continue;
       const int32_t w = col[k];
       if ((uint32_t)w >= (uint32_t)n) continue;
       const int32_t pw = pre[w];
@@ -534,10 +566,7 @@ __global__ __launch_bounds__(kB) void k_minmax(const int32_t* __restrict__ row_p
       mn = min(mn, __shfl_xor(mn, o, kRowLanes));
       mx = max(mx, __shfl_xor(mx, o, kRowLanes));
     }
-    if (sub == 0) {
-      amin[p] = mn;
-      amax[p] = mx;
-    }
+    if (sub == 0) amm[p] = make_int2(mn, mx);
   }
 }
 
@@ -549,16 +578,15 @@ __global__ __launch_bounds__(kB) void k_minmax(const int32_t* __restrict__ row_p
 // for maxima. Lane o of each B-lane group builds its two masks; lane B-1
 // also yields the block's extremes (level 0 of the sparse table).
 template <int LOG>
-__global__ __launch_bounds__(kB) void k_rmq_blocks(const int32_t* __restrict__ amin, const int32_t* __restrict__ amax,
-                                                  int32_t n, typename RmqMask<LOG>::type* __restrict__ mmin,
+__global__ __launch_bounds__(kB) void k_rmq_blocks(const int2* __restrict__ amm, int32_t n, typename RmqMask<LOG>::type* __restrict__ mmin,
                                                   typename RmqMask<LOG>::type* __restrict__ mmax,
                                                   int32_t* __restrict__ bmin, int32_t* __restrict__ bmax) {
   using M = typename RmqMask<LOG>::type;
   constexpr int B = 1 << LOG;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const bool ok = i < n;
-  const int32_t vmin = ok ? amin[i] : INT32_MAX;
-  const int32_t vmax = ok ? amax[i] : INT32_MIN;
+  const int2 v = ok ? amm[i] : make_int2(INT32_MAX, INT32_MIN);
+  const int32_t vmin = v.x, vmax = v.y;
   const int o = __lane_id() & (B - 1);
   M fmin = 0, fmax = 0;
   int32_t rmin = INT32_MAX, rmax = INT32_MIN;
@@ -598,7 +626,7 @@ __global__ void k_sparse_level(const int32_t* __restrict__ pmn, const int32_t* _
 
 template <int LOG>
 struct Rmq {
-  const int32_t *amin, *amax;
+  const int2* amm;
   const typename RmqMask<LOG>::type *mmin, *mmax;
   const int32_t* stmin;  // sparse table levels concatenated: level k at k * nb
   const int32_t* stmax;
@@ -611,8 +639,8 @@ __device__ __forceinline__ void rmq_in_block(const Rmq<LOG>& q, int32_t l, int32
   using M = typename RmqMask<LOG>::type;
   const int32_t base = r & ~((1 << LOG) - 1);
   const M keep = ~(M)0 << (l - base);
-  *mn = q.amin[base + RmqMask<LOG>::ctz(q.mmin[r] & keep)];
-  *mx = q.amax[base + RmqMask<LOG>::ctz(q.mmax[r] & keep)];
+  *mn = q.amm[base + RmqMask<LOG>::ctz(q.mmin[r] & keep)].x;
+  *mx = q.amm[base + RmqMask<LOG>::ctz(q.mmax[r] & keep)].y;
 }
 
 template <int LOG>
@@ -682,55 +710,64 @@ __global__ __launch_bounds__(kB) void k_bridge_test(const int4* __restrict__ byp
 __global__ void k_zero_i64(int64_t* p) { *p = 0; }
 
 // hybrid: parent, level and the two slots of the parent edge of every vertex
-// from the direction records and the depth prefix sums
-__global__ void k_hybrid_nodes(const int4* __restrict__ vrec, const uint32_t* __restrict__ depth_at,
-                               const int32_t* __restrict__ col, int32_t n, int32_t nnz, int32_t Lcap,
-                               int32_t* __restrict__ par, int32_t* __restrict__ lvl, int32_t* __restrict__ pslot,
-                               int32_t* __restrict__ uslot, uint32_t* __restrict__ status) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  const int4 r = vrec[v];
-  int32_t p = -1, l = -1, ps = -1, us = -1;
-  if (r.x >= 0 && r.x < Lcap) {
-    if (r.z < 0) {
-      p = -2;  // a component root
-      l = 0;
-    } else if ((uint32_t)r.w < (uint32_t)nnz && (uint32_t)r.z < (uint32_t)nnz) {
-      p = col[r.w];
-      l = (int32_t)depth_at[r.x];
-      ps = r.z;
-      us = r.w;
-    } else {
-      flag(status, ST_BAD_INDEX);
-    }
+// from the direction records and the depth prefix sums, and both slots of
+// every forest edge in a bitmask. Isolated vertices keep -1 everywhere.
+__global__ void k_hybrid_fill(int32_t n, int32_t words, int32_t* __restrict__ par, int32_t* __restrict__ lvl,
+                              int32_t* __restrict__ pslot, int32_t* __restrict__ uslot,
+                              uint32_t* __restrict__ tbits) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < max(n, words);
+       i += (int64_t)gridDim.x * blockDim.x) {
+    if (i < n) par[i] = lvl[i] = pslot[i] = uslot[i] = -1;
+    if (i < words) tbits[i] = 0u;
   }
-  par[v] = p;
-  lvl[v] = l;
-  pslot[v] = ps;
-  uslot[v] = us;
+}
+
+__global__ void k_hybrid_nodes(const int2* __restrict__ ds, const int4* __restrict__ erec,
+                               const uint32_t* __restrict__ depth_at, int32_t n, int32_t nnz,
+                               const int32_t* __restrict__ roots, const int32_t* __restrict__ sc,
+                               int32_t* __restrict__ par, int32_t* __restrict__ lvl, int32_t* __restrict__ pslot,
+                               int32_t* __restrict__ uslot, uint32_t* __restrict__ tbits) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= n) return;
+  if (e < sc[FS_ROOTS]) {
+    par[roots[e]] = -2;
+    lvl[roots[e]] = 0;
+  }
+  const int2 d = ds[e];
+  if (d.x < 0) return;
+  const int4 r = erec[e];
+  const bool down = d.y > 0;
+  const int32_t child = down ? r.y : r.x;
+  par[child] = down ? r.x : r.y;
+  lvl[child] = (int32_t)depth_at[d.x];
+  pslot[child] = down ? r.z : r.w;
+  uslot[child] = down ? r.w : r.z;
+  if ((uint32_t)r.z < (uint32_t)nnz) atomicOr(tbits + (r.z >> 5), 1u << (r.z & 31));
+  if ((uint32_t)r.w < (uint32_t)nnz) atomicOr(tbits + (r.w >> 5), 1u << (r.w & 31));
 }
 
 }  // namespace
 
-// Connectivity labels and a spanning forest (both slots of every forest
-// edge set in tbits): sampled hooking rounds, then the rows outside the
-// largest sampled component. cc[v] == v marks one root per component.
+// Connectivity labels (cc[v] == v at one root per component) and, with erec,
+// a spanning forest: sampled hooking rounds, then the rows outside the
+// largest sampled component. Edge e exists iff cc[e] != e; erec[e] = {u, w,
+// slot (u, w), -}, and first / next hold the half-edges 2e out of u
+// (k_link_in adds those out of w, and the slot (w, u)).
 int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, int32_t* cc,
-                    uint32_t* tbits, int32_t* big, hipStream_t s) {
-  const int32_t words = (int32_t)(((int64_t)nnz + 31) >> 5);
+                    int32_t* big, int4* erec, int32_t* first, int32_t* next, hipStream_t s) {
   const int gn = ceil_div(n, kB);
   const int grows = ceil_div(n, kRowsPerBlock);
+  const bool edges = erec != nullptr;
   {
-    ET_PROF(c, s, "k_check_csr");
-    hipLaunchKernelGGL(k_check_csr, dim3(gn), dim3(kB), 0, s, row_ptr, n, nnz, c->d_status);
+    ET_PROF(c, s, "k_forest_init");
+    const auto kern = edges ? k_forest_init<true> : k_forest_init<false>;
+    hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, erec, first, next, c->d_status);
   }
-  hipLaunchKernelGGL(k_iota, dim3(gn), dim3(kB), 0, s, cc, n);
-  hipLaunchKernelGGL(k_fill_i32, dim3(std::min(ceil_div(words, kB), 4096)), dim3(kB), 0, s,
-                     reinterpret_cast<int32_t*>(tbits), (int64_t)words, 0);
-  for (int j = 0; j < kSample; ++j) {
-    {
+  for (int j = 0; j < 2; ++j) {
+    if (j == 1) {
       ET_PROF(c, s, "k_hook_sample");
-      hipLaunchKernelGGL(k_hook_sample, dim3(gn), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, tbits, c->d_status, j);
+      const auto kern = edges ? k_hook_sample<true> : k_hook_sample<false>;
+      hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, erec, first, next, c->d_status);
     }
     {
       ET_PROF(c, s, "k_cc_compress");
@@ -743,27 +780,27 @@ int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t 
   }
   {
     ET_PROF(c, s, "k_hook_rest");
-    hipLaunchKernelGGL(k_hook_rest, dim3(grows), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, big, tbits,
+    const auto kern = edges ? k_hook_rest<true> : k_hook_rest<false>;
+    hipLaunchKernelGGL(kern, dim3(grows), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, big, erec, first, next,
                        c->d_status);
   }
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 }
 
 // Scratch of the Tarjan-Vishkin path of bridges_run: every array below, the
-// ranking's buffers (same scope) and the partials of its three scans.
+// ranking's buffers (same scope) and the partials of its scan.
 size_t bridges_scratch_bytes(const Ctx* c, int32_t n, int32_t nnz) {
   if (n <= 1 || nnz == 0) return 0;
-  const size_t N = (size_t)n, L = 2 * (size_t)(n - 1), words = ((size_t)nnz + 31) >> 5;
+  const size_t N = (size_t)n;
   const int rlog = c ? c->qs.rmq_log : QueryShape{}.rmq_log;
   const size_t nb = (N + (1u << rlog) - 1) >> rlog;
   size_t levels = 1;
   while (((size_t)1 << levels) <= nb) ++levels;
-  size_t b = scratch_block<int32_t>(N) + scratch_block<uint32_t>(words) + 2 * scratch_block<uint32_t>(N + 1) +
-             7 * scratch_block<int32_t>(L) + 3 * scratch_block<uint32_t>(N) + 2 * scratch_block<int4>(N) +
-             3 * scratch_block<int32_t>(N) + 2 * scratch_block<uint32_t>(N << (rlog - 5)) +
-             2 * scratch_block<int32_t>(levels * nb) + scratch_block<int32_t>(8);
-  b += list_rank_plan_bytes(c, (int32_t)L, 1, 0);
-  return b + scan_scratch_bytes((int64_t)N + 1) + scan_scratch_bytes((int64_t)N) + scan_scratch_bytes((int64_t)L);
+  size_t b = 7 * scratch_block<int32_t>(N) + 4 * scratch_block<int2>(N) + 2 * scratch_block<int4>(N) +
+             2 * scratch_block<uint32_t>(N << (rlog - 5)) + 2 * scratch_block<int32_t>(levels * nb) +
+             scratch_block<int32_t>(8);
+  b += list_rank_plan_bytes(c, (int32_t)(2 * N), 1, 0);
+  return b + scan_scratch_bytes((int64_t)(2 * N));
 }
 
 int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, uint32_t* mask,
@@ -776,27 +813,21 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
                        reinterpret_cast<int32_t*>(mask), (int64_t)words, 0);
   if (n <= 1 || nnz == 0) return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 
-  const int32_t Lcap = 2 * (n - 1);  // forest half-edges are at most 2(n-1)
+  const int32_t L2 = 2 * n;  // half-edge ids; edge ids are the vertices hooked as roots
   Scratch sc(c, s);
   int32_t* cc = sc.get<int32_t>(n);
-  uint32_t* tbits = sc.get<uint32_t>(words);
-  uint32_t* tdeg = sc.get<uint32_t>((size_t)n + 1);
-  uint32_t* tptr = sc.get<uint32_t>((size_t)n + 1);
-  int32_t* tslot = sc.get<int32_t>(Lcap);
-  int32_t* tnbr = sc.get<int32_t>(Lcap);
-  int32_t* tsrc = sc.get<int32_t>(Lcap);
-  int32_t* ttwin = sc.get<int32_t>(Lcap);
-  int32_t* succ = sc.get<int32_t>(Lcap);
-  int32_t* rank = sc.get<int32_t>(Lcap);
-  uint32_t* dw = sc.get<uint32_t>(Lcap);
-  uint32_t* rflag = sc.get<uint32_t>(n);
-  uint32_t* rpos = sc.get<uint32_t>(n);
+  int32_t* first = sc.get<int32_t>(n);
+  int2* next = sc.get<int2>(n);
+  int4* erec = sc.get<int4>(n);
   int32_t* roots = sc.get<int32_t>(n);
-  int4* vrec = sc.get<int4>(n);
+  int32_t* heads = sc.get<int32_t>(n);
+  int32_t* rrank = sc.get<int32_t>(n);
+  int2* succ = sc.get<int2>(n);
+  int2* dwp = sc.get<int2>(n);
   int32_t* pre = sc.get<int32_t>(n);
+  int32_t* uslot = sc.get<int32_t>(n);
   int4* byp = sc.get<int4>(n);
-  int32_t* amin = sc.get<int32_t>(n);
-  int32_t* amax = sc.get<int32_t>(n);
+  int2* amm = sc.get<int2>(n);
   const int rlog = c->qs.rmq_log;                        // range-minimum blocks of 2^rlog vertices
   uint32_t* mmin = sc.get<uint32_t>((size_t)n << (rlog - 5));
   uint32_t* mmax = sc.get<uint32_t>((size_t)n << (rlog - 5));
@@ -807,99 +838,93 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
   int32_t* stmax = sc.get<int32_t>((size_t)levels * nb);
   int32_t* scal = sc.get<int32_t>(8);
   if (sc.failed) return ET_ENOMEM;
+  uint32_t* dw = reinterpret_cast<uint32_t*>(dwp);
 
   const int gn = ceil_div(n, kB);
-  const int gl = ceil_div(Lcap, kB);
   // 1. spanning forest
   ET_PROF(c, s, "phase:bridges");
-  int rc = spanning_forest(c, row_ptr, col, n, nnz, cc, tbits, scal + 4, s);
+  hipLaunchKernelGGL(k_forest_scalars, dim3(1), dim3(1), 0, s, scal);
+  int rc = spanning_forest(c, row_ptr, col, n, nnz, cc, scal + FS_BIG, erec, first, reinterpret_cast<int32_t*>(next),
+                           s);
   if (rc) return rc;
-  // 2. forest CSR, twins, successors, component chaining
+  // 2. half-edge lists, component chaining, successors
   {
-    ET_PROF(c, s, "k_tree_deg");
-    hipLaunchKernelGGL(k_tree_deg, dim3(gn), dim3(kB), 0, s, row_ptr, tbits, n, nnz, tdeg);
-  }
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(1), 0, s, reinterpret_cast<int32_t*>(tdeg + n), (int64_t)1, 0);
-  rc = scan_u32(c, tdeg, tptr, (int64_t)n + 1, ScanOp::Add, true, s);
-  if (rc) return rc;
-  {
-    ET_PROF(c, s, "k_tree_fill");
-    hipLaunchKernelGGL(k_tree_fill, dim3(gn), dim3(kB), 0, s, row_ptr, col, tbits, tptr, n, nnz, Lcap, tslot, tnbr,
-                       tsrc);
+    ET_PROF(c, s, "k_link_in");
+    hipLaunchKernelGGL(k_link_in, dim3(gn), dim3(kB), 0, s, row_ptr, col, cc, erec, n, nnz, first,
+                       reinterpret_cast<int32_t*>(next), c->d_status);
   }
   {
-    ET_PROF(c, s, "k_root_flags");
-    hipLaunchKernelGGL(k_root_flags, dim3(gn), dim3(kB), 0, s, cc, tdeg, n, rflag);
-  }
-  rc = scan_u32(c, rflag, rpos, n, ScanOp::Add, true, s);
-  if (rc) return rc;
-  {
-    ET_PROF(c, s, "k_root_list");
-    hipLaunchKernelGGL(k_root_list, dim3(gn), dim3(kB), 0, s, rflag, rpos, n, roots);
-  }
-  hipLaunchKernelGGL(k_set_len, dim3(1), dim3(1), 0, s, tptr, n, scal);
-  {
-    ET_PROF(c, s, "k_succ_csr");
-    hipLaunchKernelGGL(k_succ_csr, dim3(gl), dim3(kB), 0, s, tnbr, tsrc, tptr, n, Lcap, scal, ttwin, succ,
-                       c->d_status);
+    ET_PROF(c, s, "k_roots");
+    hipLaunchKernelGGL(k_roots, dim3(ceil_div(n, kB * kRootPer)), dim3(kB), 0, s, cc, first, n, roots, heads, scal);
   }
   {
-    ET_PROF(c, s, "k_link_roots");
-    hipLaunchKernelGGL(k_link_roots, dim3(gn), dim3(kB), 0, s, roots, rpos, rflag, tptr, ttwin, n, succ, scal);
+    ET_PROF(c, s, "k_chain");
+    hipLaunchKernelGGL(k_chain, dim3(gn), dim3(kB), 0, s, roots, heads, scal, first);
+  }
+  {
+    ET_PROF(c, s, "k_forest_succ");
+    hipLaunchKernelGGL(k_forest_succ, dim3(gn), dim3(kB), 0, s, cc, erec, reinterpret_cast<int32_t*>(next), first, n,
+                       reinterpret_cast<int32_t*>(succ), dw, pre);
   }
   // 3. one list ranking, directions, preorder
   LRResult lr;
-  rc = list_rank_core(c, sc, succ, Lcap, scal + 1, 1, false, scal + 2, &lr, s, true);
+  rc = list_rank_core(c, sc, reinterpret_cast<int32_t*>(succ), L2, scal + FS_HEAD, 1, false, scal + FS_LEN, &lr, s,
+                      true);
   if (rc) return rc;
-  {
-    ET_PROF(c, s, "k_rank_of");
-    hipLaunchKernelGGL(k_rank_of, dim3(gl), dim3(kB), 0, s, lr.packed, lr.off, lr.nsub, Lcap, scal, rank,
-                       c->d_status);
-  }
-  hipLaunchKernelGGL(k_fill_i32, dim3(std::min(4 * (int64_t)gn, (int64_t)8192)), dim3(kB), 0, s,
-                     reinterpret_cast<int32_t*>(vrec), 4 * (int64_t)n, -1);
+  int2* ds = next;  // the list pointers are dead
   {
     ET_PROF(c, s, "k_direction");
-    hipLaunchKernelGGL(k_direction, dim3(gl), dim3(kB), 0, s, rank, ttwin, tsrc, tnbr, tslot, tptr, cc, n, Lcap, scal,
-                       dw, vrec, algo == kAlgoHybrid ? reinterpret_cast<uint32_t*>(succ) : nullptr, c->d_status);
+    const auto kern = algo == kAlgoHybrid ? k_direction<true> : k_direction<false>;
+    hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, lr.packed, lr.off, lr.nsub, cc, n, scal, ds, dw, c->d_status);
   }
   if (algo == kAlgoHybrid) {
     // the hybrid of Section 4.1: this rooted forest, levels from the tour,
     // then Chaitanya-Kothapalli marking instead of low / high
-    uint32_t* depth_at = reinterpret_cast<uint32_t*>(succ);  // the successors are dead after the ranking
-    rc = scan_u32(c, depth_at, depth_at, Lcap, ScanOp::Add, false, s);
+    rc = scan_u32(c, dw, dw, L2, ScanOp::Add, false, s);
     if (rc) return rc;
-    int32_t* par = pre;                                   // per-vertex arrays of the test phase are unused
-    int32_t* lvl = amin;
-    int32_t* pslot = amax;
-    int32_t* uslot = reinterpret_cast<int32_t*>(mmin);
+    int32_t* par = first;                                 // per-vertex arrays of the other phases are unused
+    int32_t* lvl = reinterpret_cast<int32_t*>(amm);
+    int32_t* pslot = pre;
+    uint32_t* tbits = sc.get<uint32_t>(words);
+    if (sc.failed) return ET_ENOMEM;
+    hipLaunchKernelGGL(k_hybrid_fill, dim3(std::min(ceil_div(std::max(n, words), kB), 4096)), dim3(kB), 0, s, n, words,
+                       par, lvl, pslot, uslot, tbits);
     {
       ET_PROF(c, s, "k_hybrid_nodes");
-      hipLaunchKernelGGL(k_hybrid_nodes, dim3(gn), dim3(kB), 0, s, vrec, depth_at, col, n, nnz, Lcap, par, lvl,
-                         pslot, uslot, c->d_status);
+      hipLaunchKernelGGL(k_hybrid_nodes, dim3(gn), dim3(kB), 0, s, ds, erec, dw, n, nnz, roots, scal, par, lvl, pslot,
+                         uslot, tbits);
     }
     return ck_mark(c, row_ptr, col, n, nnz, tbits, par, lvl, pslot, uslot, mask, s);
   }
-  rc = scan_u32(c, dw, dw, Lcap, ScanOp::Add, false, s);
+  {
+    ET_PROF(c, s, "k_root_rank");
+    hipLaunchKernelGGL(k_root_rank, dim3(gn), dim3(kB), 0, s, heads, lr.packed, lr.off, lr.nsub, scal, rrank, dw,
+                       c->d_status);
+  }
+  rc = scan_u32(c, dw, dw, L2, ScanOp::Add, false, s);
   if (rc) return rc;
   {
     ET_PROF(c, s, "k_preorder");
-    hipLaunchKernelGGL(k_preorder, dim3(gn), dim3(kB), 0, s, vrec, dw, n, Lcap, pre, byp);
+    hipLaunchKernelGGL(k_preorder, dim3(gn), dim3(kB), 0, s, ds, erec, dw, n, pre, uslot, byp);
   }
-  // 4. non-forest extremes by preorder
+  {
+    ET_PROF(c, s, "k_root_preorder");
+    hipLaunchKernelGGL(k_root_preorder, dim3(gn), dim3(kB), 0, s, roots, rrank, dw, n, scal, pre, uslot, byp);
+  }
+  // 4. extremes over the neighbours, by preorder
   {
     ET_PROF(c, s, "k_minmax");
     hipLaunchKernelGGL(k_minmax, dim3(std::min(ceil_div((int64_t)n * kRowLanes, kB), kMaxGrid)), dim3(kB), 0, s,
-                       row_ptr, col, tbits, pre, n, nnz, amin, amax);
+                       row_ptr, col, uslot, pre, n, nnz, amm);
   }
   // 5. range extremes
   {
     ET_PROF(c, s, "k_rmq_blocks");
     if (rlog == 6)
-      hipLaunchKernelGGL(k_rmq_blocks<6>, dim3(gn), dim3(kB), 0, s, amin, amax, n, reinterpret_cast<uint64_t*>(mmin),
+      hipLaunchKernelGGL(k_rmq_blocks<6>, dim3(gn), dim3(kB), 0, s, amm, n, reinterpret_cast<uint64_t*>(mmin),
                          reinterpret_cast<uint64_t*>(mmax), stmin, stmax);
     else
-      hipLaunchKernelGGL(k_rmq_blocks<5>, dim3(gn), dim3(kB), 0, s, amin, amax, n, mmin, mmax, stmin, stmax);
+      hipLaunchKernelGGL(k_rmq_blocks<5>, dim3(gn), dim3(kB), 0, s, amm, n, mmin, mmax, stmin, stmax);
   }
   for (int k = 1; k < levels; ++k) {
     ET_PROF(c, s, "k_sparse_level");
@@ -911,13 +936,13 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
   {
     ET_PROF(c, s, "k_bridge_test");
     if (rlog == 6) {
-      Rmq<6> q{amin, amax, reinterpret_cast<const uint64_t*>(mmin), reinterpret_cast<const uint64_t*>(mmax), stmin,
-               stmax, nb};
-      hipLaunchKernelGGL(k_bridge_test<6>, dim3(std::min(gn, kTestBlocks)), dim3(kB), 0, s, byp, dw, Lcap, n, q, mask,
+      Rmq<6> q{amm, reinterpret_cast<const uint64_t*>(mmin), reinterpret_cast<const uint64_t*>(mmax), stmin, stmax,
+               nb};
+      hipLaunchKernelGGL(k_bridge_test<6>, dim3(std::min(gn, kTestBlocks)), dim3(kB), 0, s, byp, dw, L2, n, q, mask,
                          c->d_bcount);
     } else {
-      Rmq<5> q{amin, amax, mmin, mmax, stmin, stmax, nb};
-      hipLaunchKernelGGL(k_bridge_test<5>, dim3(std::min(gn, kTestBlocks)), dim3(kB), 0, s, byp, dw, Lcap, n, q, mask,
+      Rmq<5> q{amm, mmin, mmax, stmin, stmax, nb};
+      hipLaunchKernelGGL(k_bridge_test<5>, dim3(std::min(gn, kTestBlocks)), dim3(kB), 0, s, byp, dw, L2, n, q, mask,
                          c->d_bcount);
     }
   }
