@@ -533,40 +533,156 @@ __global__ void k_root_preorder(const int32_t* __restrict__ roots, const int32_t
   byp[p] = make_int4(((end - r) >> 1) + 1, -1, -1, 0);
 }
 
-// per vertex: min / max preorder over itself and its neighbours, the parent
-// edge's own slot left out, stored at its preorder position (the paper's
-// segreduce) as one 8-byte store. 16 lanes share a row: they read its slots
-// side by side and combine with shuffles.
-constexpr int kRowLanes = 16;
+// Range passes over the slots of all rows, for a kernel that gathers a word
+// per neighbour. Such gathers run at 73 G/s from a 16 MiB array but at 190
+// G/s from 4 MiB, what one XCD's L2 holds. So a pass takes only the
+// neighbours with ids in [lo, hi), all workgroups the same ones, and the next
+// pass reads the columns again. A pass must then cost little besides its
+// gathers: a workgroup's rows are staged in LDS with coalesced loads, and
+// 2^glog lanes scan a row (its part in [lo, hi), found by binary search: rows
+// are sorted). Workgroups whose rows do not fit the stage read their slots
+// directly, all lanes together for the long rows.
+constexpr int kRowStage = 6144;   // staged slots of a workgroup's rows
+constexpr int kRowLoads = 8;      // column loads a lane issues together
+constexpr int kRowHeavy = 512;    // longer rows of an unstaged workgroup are taken by all its lanes
+constexpr int kRowLanesLog = 4;   // at most 16 lanes a row
 
+__device__ __forceinline__ void stage_slots(const int32_t* __restrict__ col, int32_t m, int32_t* st) {
+  for (int32_t i0 = threadIdx.x; i0 < m; i0 += kRowLoads * kB) {
+    int32_t x[kRowLoads];  // a lane's loads first, then their stores
+#pragma unroll
+    for (int j = 0; j < kRowLoads; ++j) x[j] = i0 + j * kB < m ? col[i0 + j * kB] : 0;
+#pragma unroll
+    for (int j = 0; j < kRowLoads; ++j)
+      if (i0 + j * kB < m) st[i0 + j * kB] = x[j];
+  }
+}
+
+// first staged slot of [x, e) with a neighbour of at least lo
+__device__ __forceinline__ int32_t range_start(const int32_t* st, int32_t x, int32_t e, int32_t lo) {
+  if (lo <= 0) return x;
+  while (x < e) {
+    const int32_t mid = (x + e) >> 1;
+    if (st[mid] < lo) x = mid + 1;
+    else e = mid;
+  }
+  return x;
+}
+
+// One pass per 1.5 * 2^20 vertices (6 MiB of words), at most three: the
+// extremes took, with 1 / 2 / 3 / 4 passes, 267 / 248 / 272 / 301 us at 2^21
+// vertices and 2^25 slots, 794 / 667 / 650 / 700 at 2^22 and 2^26, 1105 /
+// 1028 / 1001 / 1025 at 2^23 and 2^26, 2407 / 2336 / 2313 / 2365 at 2^24 and
+// 2^27; below 6 slots a row reading the rows again costs what the gathers
+// gain (253 / 256 / 270 at 2^22 and 2^24).
+int range_passes(int32_t n, int32_t nnz) {
+  constexpr int64_t kRangeVerts = 3 << 19;
+  if (nnz < 6 * (int64_t)n) return 1;
+  return (int)std::min<int64_t>(3, (n + kRangeVerts - 1) / kRangeVerts);
+}
+
+// lanes per row: one per 16 slots of an average row
+int row_lanes_log(int32_t n, int32_t nnz) {
+  int g = 0;
+  while (g < kRowLanesLog && ((int64_t)n << g) * 16 < nnz) ++g;
+  return g;
+}
+
+// per vertex: min / max preorder over itself and its neighbours, the parent
+// edge's own slot left out (the paper's segreduce), stored at its preorder
+// position as one 8-byte store.
+// Rows are scanned in range passes (above): `acc` carries a row's extremes
+// from pass to pass by vertex, and the last pass stores them by preorder. At
+// 2^22 vertices and 2^26 slots three passes take 650 us, one pass 795, and
+// one pass with 16 lanes a row combined by shuffles 891 (with passes that
+// version was issue-bound, 350 us for each further one).
+template <bool FIRST, bool LAST>
 __global__ __launch_bounds__(kB) void k_minmax(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                                               const int32_t* __restrict__ uslot, const int32_t* __restrict__ pre,
-                                              int32_t n, int32_t nnz, int2* __restrict__ amm) {
-  const int sub = threadIdx.x & (kRowLanes - 1);
-  const int64_t groups = (int64_t)gridDim.x * (blockDim.x / kRowLanes);
-  // rows stride over the grid: 16 lanes per row would exceed the 2^32
-  // work-items of one dispatch beyond 2^28 rows
-  for (int64_t u = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kRowLanes; u < n; u += groups) {
-    const int32_t p = pre[u];
-    if (p < 0 || p >= n) continue;    // isolated vertex (the whole row group skips together)
+                                              int32_t n, int32_t nnz, int32_t lo, int32_t hi, int glog,
+                                              int2* __restrict__ acc, int2* __restrict__ amm) {
+  __shared__ int32_t st[kRowStage];
+  __shared__ int32_t heavy[kB], nheavy;
+  __shared__ int2 wmm[kB / 64];
+  const int g = 1 << glog, rows = kB >> glog, sub = threadIdx.x & (g - 1);
+  const int64_t nblk = ((int64_t)n + rows - 1) / rows;
+  // row blocks stride over the grid (a dispatch holds < 2^32 work-items)
+  for (int64_t rb = blockIdx.x; rb < nblk; rb += gridDim.x) {
+    const int32_t r0 = (int32_t)(rb * rows);
+    const int cnt = min(rows, n - r0);
+    const int32_t A = clampi(row_ptr[r0], 0, nnz), B = clampi(row_ptr[r0 + cnt], A, nnz);
+    const bool staged = B - A <= kRowStage;  // the same for every lane
+    const int ri = threadIdx.x >> glog;
+    const int32_t u = r0 + min(ri, cnt - 1);
     const int32_t a = clampi(row_ptr[u], 0, nnz), b = clampi(row_ptr[u + 1], a, nnz);
     const int32_t up = uslot[u];
-    int32_t mn = p, mx = p;
-    for (int64_t kk = (int64_t)a + sub; kk < b; kk += kRowLanes) {  // b may lie within one stride of 2^31
-      const int32_t k = (int32_t)kk;
-      if (k == up) continue;
-      const int32_t w = col[k];
-      if ((uint32_t)w >= (uint32_t)n) continue;
-      const int32_t pw = pre[w];
-      mn = min(mn, pw);
-      mx = max(mx, pw);
+    int32_t p = (FIRST || LAST) ? pre[u] : 0, mn = p, mx = p;
+    if (!FIRST) {
+      const int2 x = acc[u];
+      mn = x.x;
+      mx = x.y;
     }
+    const bool own = ri < cnt && p >= 0 && p < n;  // not past the end, not isolated
+    if (threadIdx.x == 0) nheavy = 0;
+    if (staged) stage_slots(col + A, B - A, st);
+    __syncthreads();
+    if (own && staged && a >= A && b <= B) {
+      const int32_t e = b - A, ups = up - A;
+      for (int32_t x = range_start(st, a - A, e, lo) + sub; x < e; x += g) {
+        const int32_t w = st[x];
+        if (w >= hi) break;
+        if (x == ups || w < lo) continue;
+        const int32_t pw = pre[w];
+        mn = min(mn, pw);
+        mx = max(mx, pw);
+      }
+    } else if (own && b - a <= kRowHeavy) {
+      for (int64_t k = (int64_t)a + sub; k < b; k += g) {  // b may lie within one stride of 2^31
+        const int32_t w = col[k];
+        if (k == up || w < lo || w >= hi) continue;
+        const int32_t pw = pre[w];
+        mn = min(mn, pw);
+        mx = max(mx, pw);
+      }
+    } else if (own && sub == 0) {
+      heavy[atomicAdd(&nheavy, 1)] = ri;
+    }
+    for (int o = g >> 1; o > 0; o >>= 1) {
+      mn = min(mn, __shfl_xor(mn, o, 64));
+      mx = max(mx, __shfl_xor(mx, o, 64));
+    }
+    __syncthreads();
+    for (int h = 0; h < nheavy; ++h) {
+      const int hr = heavy[h];
+      const int32_t ha = clampi(row_ptr[r0 + hr], 0, nnz), hb = clampi(row_ptr[r0 + hr + 1], ha, nnz);
+      const int32_t hup = uslot[r0 + hr];
+      int32_t m0 = INT32_MAX, m1 = INT32_MIN;
+      for (int64_t k = (int64_t)ha + threadIdx.x; k < hb; k += kB) {
+        const int32_t w = col[k];
+        if (k == hup || w < lo || w >= hi) continue;
+        const int32_t pw = pre[w];
+        m0 = min(m0, pw);
+        m1 = max(m1, pw);
+      }
 #pragma unroll
-    for (int o = kRowLanes / 2; o > 0; o >>= 1) {
-      mn = min(mn, __shfl_xor(mn, o, kRowLanes));
-      mx = max(mx, __shfl_xor(mx, o, kRowLanes));
+      for (int o = 32; o > 0; o >>= 1) {
+        m0 = min(m0, __shfl_xor(m0, o, 64));
+        m1 = max(m1, __shfl_xor(m1, o, 64));
+      }
+      if (__lane_id() == 0) wmm[threadIdx.x >> 6] = make_int2(m0, m1);
+      __syncthreads();
+      if (ri == hr)
+        for (int w = 0; w < kB / 64; ++w) {
+          mn = min(mn, wmm[w].x);
+          mx = max(mx, wmm[w].y);
+        }
+      __syncthreads();
     }
-    if (sub == 0) amm[p] = make_int2(mn, mx);
+    if (own && sub == 0) {
+      if (LAST) amm[p] = make_int2(mn, mx);
+      else acc[u] = make_int2(mn, mx);
+    }
+    __syncthreads();  // the stage and the heavy list are rewritten by the next row block
   }
 }
 
@@ -914,8 +1030,18 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
   // 4. extremes over the neighbours, by preorder
   {
     ET_PROF(c, s, "k_minmax");
-    hipLaunchKernelGGL(k_minmax, dim3(std::min(ceil_div((int64_t)n * kRowLanes, kB), kMaxGrid)), dim3(kB), 0, s,
-                       row_ptr, col, uslot, pre, n, nnz, amm);
+    const int passes = range_passes(n, nnz), glog = row_lanes_log(n, nnz);
+    const int64_t step = ((int64_t)n + passes - 1) / passes;
+    const dim3 g(std::min(ceil_div(n, kB >> glog), kMaxGrid));
+    int2* acc = succ;  // the successors are dead
+    for (int p = 0; p < passes; ++p) {
+      const auto kern = passes == 1       ? k_minmax<true, true>
+                        : p == 0          ? k_minmax<true, false>
+                        : p == passes - 1 ? k_minmax<false, true>
+                                          : k_minmax<false, false>;
+      const int32_t lo = (int32_t)std::min<int64_t>(p * step, n), hi = (int32_t)std::min<int64_t>((p + 1) * step, n);
+      hipLaunchKernelGGL(kern, g, dim3(kB), 0, s, row_ptr, col, uslot, pre, n, nnz, lo, hi, glog, acc, amm);
+    }
   }
   // 5. range extremes
   {
