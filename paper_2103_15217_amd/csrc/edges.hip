@@ -128,9 +128,11 @@ __global__ void k_edge_dir(const int32_t* __restrict__ rank, const int32_t* __re
 __global__ void k_edge_node(const int4* __restrict__ vrec, const uint32_t* __restrict__ I, int32_t n, int32_t L,
                             int32_t root, int32_t* __restrict__ parent, int32_t* __restrict__ pre_out,
                             int32_t* __restrict__ size_out, int4* __restrict__ rec, uint32_t* __restrict__ inl_out,
-                            uint32_t* __restrict__ status) {
+                            uint32_t* __restrict__ plab, uint32_t* __restrict__ status) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n) return;
+  plab[v] = kUnusedLabel;  // the label table of inlabel_phase, n + 1 entries
+  if (v == n - 1) plab[n] = kUnusedLabel;
   int32_t par = -1, pre = 0, size = n, depth = 0;
   if (v != root) {
     const int4 r = vrec[v];
@@ -192,7 +194,7 @@ int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, i
   int32_t* parent = parent_out ? parent_out : scr.get<int32_t>((size_t)n);
   uint32_t* inl = scr.get<uint32_t>((size_t)n);
   int4* vrec = scr.get<int4>((size_t)n);
-  uint32_t* plab = scr.get<uint32_t>((size_t)n + 1);
+  uint32_t* plab = scr.get<uint32_t>(2 * ((size_t)n + 1));
   if (scr.failed) return ET_ENOMEM;
   const int gl = ceil_div(L, kB), gn = ceil_div(n, kB), gm = ceil_div(m, kB);
   int rc;
@@ -239,7 +241,7 @@ int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, i
     {
       ET_PROF(c, s, "k_edge_node");
       hipLaunchKernelGGL(k_edge_node, dim3(gn), dim3(kB), 0, s, vrec, dw, n, L, root, parent, t->d_pre, t->d_size,
-                         t->d_rec, inl, c->d_status);
+                         t->d_rec, inl, plab, c->d_status);
     }
   }
   return inlabel_phase(c, t, parent, inl, plab, s);

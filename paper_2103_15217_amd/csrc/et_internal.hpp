@@ -307,7 +307,9 @@ int sort_pairs_u32(Ctx* c, const uint32_t* keys, const int32_t* vals, int32_t n,
                    int32_t* vals_out, hipStream_t s);
 // tree.hip: head table, path labels and ascendants of a tree whose node
 // records {inlabel, -, depth, pre} and compact inlabels are written;
-// t->d_root[0] must hold the root id; plab needs n+1 slots of scratch
+// t->d_root[0] must hold the root id; plab: 2(n+1) slots of scratch, the
+// first n+1 filled with kUnusedLabel
+constexpr uint32_t kUnusedLabel = 0xffffffffu;
 int inlabel_phase(Ctx* c, et_tree* t, const int32_t* parent, const uint32_t* inl, uint32_t* plab, hipStream_t s);
 // edges.hip: tree tables from an unordered edge list (the DCEL construction)
 int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, int32_t root, int32_t* parent_out,

@@ -21,8 +21,9 @@
 //   6. ascendant(v) (the OR of 2^h over the labels of v's ancestors) only
 //      depends on v's path: it is the ascendant of the path above plus the
 //      path's own level bit. Labels on a root path have strictly decreasing
-//      levels, so one pass per level, from the highest down, fills a table
-//      by label; k_asc copies it into the node records.
+//      levels, so k_asc_label walks each label's chain of parent path labels
+//      (at most one link per level) into a table by label; k_asc copies it
+//      into the node records.
 #include "et_internal.hpp"
 
 namespace et {
@@ -62,9 +63,11 @@ __global__ void k_succ(const uint32_t* __restrict__ keys, const int32_t* __restr
 __global__ void k_node(const uint64_t* __restrict__ packed, const int2* __restrict__ off, int32_t nsub,
                        int32_t n, const int32_t* __restrict__ sc, int32_t* __restrict__ rank,
                        int32_t* __restrict__ pre_out, int32_t* __restrict__ size_out, int4* __restrict__ rec,
-                       uint32_t* __restrict__ inl_out, uint32_t* __restrict__ status) {
+                       uint32_t* __restrict__ inl_out, uint32_t* __restrict__ plab, uint32_t* __restrict__ status) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n) return;
+  plab[c] = kUnusedLabel;  // the label table of inlabel_phase, n + 1 entries
+  if (c == n - 1) plab[n] = kUnusedLabel;
   const int32_t root = sc[SC_ROOT];
   int32_t depth, pre, size, r0, r1;
   if (c == root) {
@@ -126,48 +129,107 @@ __global__ void k_head(const int32_t* __restrict__ parent, const int4* __restric
   }
 }
 
-// Ascendant of a path label I at level t = h(I): the ascendant of the path
-// it hangs from (a label of a strictly higher level, already done) plus bit
-// t. plab[] holds the parent path's label on entry and the ascendant on
-// exit; unused labels keep kUnused.
-constexpr uint32_t kUnused = 0xffffffffu;
+// Ascendant of every path label: the level bits along its chain of parent
+// path labels (plab; 0 ends it at the root's path). Levels strictly rise along
+// a chain, so it has at most one link per level. A parent path's label is an
+// ancestor of its child's in the binary tree of labels, so of an aligned range
+// of 2^LOG labels a chain only leaves to labels of level LOG and up. Two forms:
+//  - k_asc_chain, for trees whose launches cost more than their bytes: one
+//    launch, a lane follows its label's chain, in LDS inside the workgroup's
+//    range. Bound by the latency of the links above.
+//  - k_asc_upper, then k_asc_range, for large trees: the labels of level
+//    kAscLog and up first (their chains stay among themselves); then a
+//    workgroup takes its range level by level in LDS, so every label is one
+//    step instead of one per link (following chains there was issue-bound, 102
+//    us at 2^24 nodes), and the first link above the range is one gather.
+// One launch per level, the form before, took 177 us at 2^24 nodes (24
+// launches) and 41 us at 10^6; these take 53 and 12.
+constexpr int kAscChainLog = 8;
 
-__global__ void k_asc_level(uint32_t* __restrict__ plab, int32_t n, int t, uint32_t* __restrict__ status) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t I = ((2 * k + 1) << t);
-  if (I > n) return;
-  const uint32_t pl = plab[I];
-  if (pl == kUnused) return;
-  uint32_t up = 0;
-  if (pl != 0) {
-    if (pl <= (uint32_t)n && ctz32(pl) > t) up = plab[pl];
-    else flag(status, ST_BAD_INDEX);
+__global__ __launch_bounds__(kB) void k_asc_chain(const uint32_t* __restrict__ plab, int32_t n,
+                                                 uint32_t* __restrict__ asc_of_label, uint32_t* __restrict__ status) {
+  static_assert(kB == 1 << kAscChainLog, "a lane per label");
+  __shared__ uint32_t lp[kB];
+  const uint32_t I = (blockIdx.x << kAscChainLog) + threadIdx.x;
+  uint32_t pl = I >= 1 && I <= (uint32_t)n ? plab[I] : kUnusedLabel;
+  lp[threadIdx.x] = pl;
+  __syncthreads();
+  if (pl == kUnusedLabel) return;
+  int t = ctz32(I);
+  uint32_t acc = 1u << t;
+  while (pl != 0) {
+    if (pl > (uint32_t)n || ctz32(pl) <= t) {
+      flag(status, ST_BAD_INDEX);
+      break;
+    }
+    t = ctz32(pl);
+    acc |= 1u << t;
+    pl = (pl >> kAscChainLog) == blockIdx.x ? lp[pl & (kB - 1)] : plab[pl];
   }
-  plab[I] = up | (1u << t);
+  asc_of_label[I] = acc;
 }
 
-// The levels hi .. lo, each holding at most blockDim.x labels, in one
-// workgroup: one label per lane per level, a barrier between levels (the
-// labels of a level are read by the next one down).
-constexpr int kAscTop = 1024;
+constexpr int kAscLog = 10;
 
-__global__ __launch_bounds__(kAscTop) void k_asc_top(uint32_t* __restrict__ plab, int32_t n, int hi, int lo,
-                                                    uint32_t* __restrict__ status) {
-  for (int t = hi; t >= lo; --t) {
-    const int64_t I = ((2 * (int64_t)threadIdx.x + 1) << t);
-    if (I <= n) {
-      const uint32_t pl = plab[I];
-      if (pl != kUnused) {
-        uint32_t up = 0;
-        if (pl != 0) {
-          if (pl <= (uint32_t)n && ctz32(pl) > t) up = plab[pl];
-          else flag(status, ST_BAD_INDEX);
-        }
-        plab[I] = up | (1u << t);
-      }
-    }
-    __syncthreads();
+__global__ __launch_bounds__(kB) void k_asc_range(const uint32_t* __restrict__ plab, int32_t n,
+                                                 uint32_t* asc_of_label, uint32_t* __restrict__ status) {
+  constexpr int kN = 1 << kAscLog, kPer = kN / kB;
+  __shared__ uint32_t lp[kN];  // parent label inside the range as a position, 0 if the label is done
+  __shared__ uint32_t la[kN];  // ascendant
+  const uint32_t base = blockIdx.x << kAscLog;  // labels [base, base + kN) of 0 .. n
+  uint32_t pl[kPer];
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t I = base + threadIdx.x + j * kB;
+    pl[j] = I >= 1 && I <= (uint32_t)n ? plab[I] : kUnusedLabel;
   }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t i = threadIdx.x + j * kB;
+    uint32_t up = 0, a = 0;
+    if (pl[j] != kUnusedLabel && i != 0) {
+      const int t = ctz32(i);
+      a = 1u << t;
+      if (pl[j] != 0 && (pl[j] > (uint32_t)n || ctz32(pl[j]) <= t)) bad = true;
+      else if (pl[j] != 0 && (pl[j] >> kAscLog) == blockIdx.x && pl[j] != base) up = pl[j] - base;
+      else if (pl[j] != 0) a |= asc_of_label[pl[j]];
+    }
+    lp[i] = up;
+    la[i] = a;
+  }
+  for (int t = kAscLog - 2; t >= 0; --t) {  // (nothing in the range lies above its level kAscLog - 1)
+    __syncthreads();
+    for (uint32_t i = ((2 * threadIdx.x + 1) << t); i < (uint32_t)kN; i += (2 * kB) << t)
+      if (lp[i] != 0) la[i] |= la[lp[i]];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint32_t i = threadIdx.x + j * kB;
+    if (i != 0 && base + i <= (uint32_t)n) asc_of_label[base + i] = la[i];  // unused labels too: whole lines
+  }
+  if (bad) flag(status, ST_BAD_INDEX);
+}
+
+__global__ __launch_bounds__(kB) void k_asc_upper(const uint32_t* __restrict__ plab, int32_t n,
+                                                 uint32_t* __restrict__ asc_of_label, uint32_t* __restrict__ status) {
+  const int64_t I = ((int64_t)blockIdx.x * kB + threadIdx.x + 1) << kAscLog;
+  if (I > n) return;
+  uint32_t pl = plab[I];
+  if (pl == kUnusedLabel) return;
+  int t = ctz32((uint32_t)I);
+  uint32_t acc = 1u << t;
+  while (pl != 0) {
+    if (pl > (uint32_t)n || ctz32(pl) <= t) {
+      flag(status, ST_BAD_INDEX);
+      break;
+    }
+    t = ctz32(pl);
+    acc |= 1u << t;
+    pl = plab[pl];
+  }
+  asc_of_label[I] = acc;
 }
 
 __global__ void k_asc(int4* __restrict__ rec, const uint32_t* __restrict__ inl_of,
@@ -179,11 +241,6 @@ __global__ void k_asc(int4* __restrict__ rec, const uint32_t* __restrict__ inl_o
   if (inl >= 1u && inl <= (uint32_t)n) a = asc_of_label[inl];
   else flag(status, ST_BAD_INDEX);
   reinterpret_cast<int32_t*>(rec)[4 * v + 1] = (int32_t)a;
-}
-
-__global__ void k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t v) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
 }
 
 // n == 1: the root is the only node
@@ -407,7 +464,7 @@ size_t tree_build_scratch_bytes(const Ctx* c, int32_t n, int32_t batch) {
     b += scratch_block<int32_t>((size_t)n) + scratch_block<int32_t>((size_t)batch);  // n counts the virtual root
   }
   if (n <= 1) return b;
-  b += scratch_block<uint32_t>(2 * (size_t)n) + scratch_block<uint32_t>((size_t)n);
+  b += scratch_block<uint32_t>(2 * (size_t)n + 2) + scratch_block<uint32_t>((size_t)n);
   return b + group_by_parent_scratch_bytes(n) + list_rank_plan_bytes(c, 2 * n, 1, 0);
 }
 
@@ -421,7 +478,7 @@ int tree_build(Ctx* c, et_tree* t, const int32_t* parent, hipStream_t s) {
   }
   const int32_t L2 = 2 * n;          // half-edge id space (the tour uses 2(n-1) of them)
   Scratch scr(c, s);
-  uint32_t* kv = scr.get<uint32_t>((size_t)L2);  // sorted parents | children, later the path-label table
+  uint32_t* kv = scr.get<uint32_t>((size_t)L2 + 2);  // sorted parents | children, later the two tables by label
   if (scr.failed) return ET_ENOMEM;
   uint32_t* keys = kv;
   int32_t* vals = reinterpret_cast<int32_t*>(kv + n);
@@ -443,40 +500,41 @@ int tree_build(Ctx* c, et_tree* t, const int32_t* parent, hipStream_t s) {
     {
       ET_PROF(c, s, "k_node");
       hipLaunchKernelGGL(k_node, dim3(gn), dim3(kB), 0, s, lr.packed, lr.off, lr.nsub, n, sc, t->d_rank, t->d_pre,
-                         t->d_size, t->d_rec, inl, c->d_status);
+                         t->d_size, t->d_rec, inl, kv, c->d_status);
     }
   }
-  return inlabel_phase(c, t, parent, inl, kv, s);  // n+1 label slots: the grouping keys are dead by now
+  return inlabel_phase(c, t, parent, inl, kv, s);  // the grouping's keys and values are dead by now
 }
+
+constexpr int32_t kAscTwo = 1 << 20;  // nodes from which the ascendants take two launches
 
 int inlabel_phase(Ctx* c, et_tree* t, const int32_t* parent, const uint32_t* inl, uint32_t* plab, hipStream_t s) {
   const int32_t n = t->n;
   int32_t* sc = t->d_root;
   const int gn = ceil_div(n, kB);
+  uint32_t* asc = plab + n + 1;  // ascendant by label
   ET_PROF(c, s, "phase:inlabel");
-  hipLaunchKernelGGL(k_fill_u32, dim3(std::min(ceil_div((int64_t)n + 1, kB), 8192)), dim3(kB), 0, s, plab,
-                     (int64_t)n + 1, kUnused);
   {
     ET_PROF(c, s, "k_head");
     hipLaunchKernelGGL(k_head, dim3(gn), dim3(kB), 0, s, parent, t->d_rec, inl, n, sc, t->d_head, plab,
                        c->d_status);
   }
   {
-    ET_PROF(c, s, "k_asc_level");
-    int top = 0;
-    while ((2ll << top) <= n) ++top;  // highest level a label <= n can have
-    // labels (2k+1) 2^lv <= n of level lv: (n >> lv) / 2 + 1 candidates
-    int lo = top;
-    while (lo > 0 && (((int64_t)n >> (lo - 1)) / 2 + 1) <= kAscTop) --lo;
-    hipLaunchKernelGGL(k_asc_top, dim3(1), dim3(kAscTop), 0, s, plab, n, top, lo, c->d_status);
-    for (int lv = lo - 1; lv >= 0; --lv) {
-      const int64_t cand = ((int64_t)n >> lv) / 2 + 1;
-      hipLaunchKernelGGL(k_asc_level, dim3(ceil_div(cand, kB)), dim3(kB), 0, s, plab, n, lv, c->d_status);
+    ET_PROF(c, s, "k_asc_label");
+    // one launch / two launches: 7.3 / 11 us at 2^18 nodes, 9.6 / 11 at 2^19,
+    // 14 / 12 at 2^20, 24 / 14 at 2^21, 184 / 54 at 2^24
+    if (n >= kAscTwo) {
+      hipLaunchKernelGGL(k_asc_upper, dim3(ceil_div((int64_t)n >> kAscLog, kB)), dim3(kB), 0, s, plab, n, asc,
+                         c->d_status);
+      hipLaunchKernelGGL(k_asc_range, dim3((unsigned)(n >> kAscLog) + 1), dim3(kB), 0, s, plab, n, asc, c->d_status);
+    } else {
+      hipLaunchKernelGGL(k_asc_chain, dim3((unsigned)(n >> kAscChainLog) + 1), dim3(kB), 0, s, plab, n, asc,
+                         c->d_status);
     }
   }
   {
     ET_PROF(c, s, "k_asc");
-    hipLaunchKernelGGL(k_asc, dim3(gn), dim3(kB), 0, s, t->d_rec, inl, plab, n, c->d_status);
+    hipLaunchKernelGGL(k_asc, dim3(gn), dim3(kB), 0, s, t->d_rec, inl, asc, n, c->d_status);
   }
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 }
