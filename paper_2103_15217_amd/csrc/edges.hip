@@ -127,7 +127,8 @@ __global__ void k_edge_dir(const int32_t* __restrict__ rank, const int32_t* __re
 
 __global__ void k_edge_node(const int4* __restrict__ vrec, const uint32_t* __restrict__ I, int32_t n, int32_t L,
                             int32_t root, int32_t* __restrict__ parent, int32_t* __restrict__ pre_out,
-                            int32_t* __restrict__ size_out, int4* __restrict__ rec, uint32_t* __restrict__ inl_out,
+                            int32_t* __restrict__ size_out, uint32_t* __restrict__ inl_out,
+                            int32_t* __restrict__ depth_out,
                             uint32_t* __restrict__ plab, uint32_t* __restrict__ status) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n) return;
@@ -151,9 +152,8 @@ __global__ void k_edge_node(const int4* __restrict__ vrec, const uint32_t* __res
   parent[v] = par;
   pre_out[v] = pre;
   size_out[v] = size;
-  const uint32_t inl = inlabel_of(pre, size);
-  rec[v] = make_int4((int32_t)inl, 0, depth, pre);
-  inl_out[v] = inl;
+  inl_out[v] = inlabel_of(pre, size);
+  depth_out[v] = depth;
 }
 
 __global__ void k_single_edges(int32_t* __restrict__ sc, int32_t* __restrict__ succ, int32_t* __restrict__ rank,
@@ -224,6 +224,7 @@ int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, i
   LRResult lr;
   rc = list_rank_core(c, scr, t->d_succ, L, sc + SC_HEAD, 1, false, sc + SC_EXPECT, &lr, s);
   if (rc) return rc;
+  int32_t* depth = first;  // the run starts are dead
   uint32_t* dw = key;  // the sort keys are dead: down flags in tour order, then their scan
   {
     ET_PROF(c, s, "phase:nodes");
@@ -241,10 +242,10 @@ int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, i
     {
       ET_PROF(c, s, "k_edge_node");
       hipLaunchKernelGGL(k_edge_node, dim3(gn), dim3(kB), 0, s, vrec, dw, n, L, root, parent, t->d_pre, t->d_size,
-                         t->d_rec, inl, plab, c->d_status);
+                         inl, depth, plab, c->d_status);
     }
   }
-  return inlabel_phase(c, t, parent, inl, plab, s);
+  return inlabel_phase(c, t, parent, inl, depth, true, plab, s);
 }
 
 }  // namespace et

@@ -171,6 +171,17 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 }
 
+// Workgroups go to the eight XCDs in turn. This order gives each XCD a
+// contiguous range of the n items that a launch of n workgroups works on, so
+// what neighbouring items write near each other meets in one L2: XCD x =
+// blockIdx % 8 takes the x-th range (a bijection of [0, n) for any n).
+constexpr int kXcds = 8;
+__device__ __forceinline__ int32_t xcd_block(int32_t n) {
+  const int32_t b = (int32_t)blockIdx.x;
+  const int32_t q = n / kXcds, r = n % kXcds, x = b % kXcds;
+  return x * q + min(x, r) + b / kXcds;
+}
+
 __device__ __forceinline__ void flag(uint32_t* status, uint32_t bits) {
   atomicOr(status, bits);
 }
@@ -305,12 +316,14 @@ int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const 
 // radix.hip: stable sort of (key, value) pairs by the low `bits` key bits
 int sort_pairs_u32(Ctx* c, const uint32_t* keys, const int32_t* vals, int32_t n, int bits, uint32_t* keys_out,
                    int32_t* vals_out, hipStream_t s);
-// tree.hip: head table, path labels and ascendants of a tree whose node
-// records {inlabel, -, depth, pre} and compact inlabels are written;
-// t->d_root[0] must hold the root id; plab: 2(n+1) slots of scratch, the
-// first n+1 filled with kUnusedLabel
+// tree.hip: head table, path labels, ascendants and node records of a tree
+// whose preorder, compact inlabels and depths are written; t->d_root[0] must
+// hold the root id; plab: 2(n+1) slots of scratch, the first n+1 filled with
+// kUnusedLabel. depth may lie in the others (not kept: the records then take
+// the depth from t->d_rank, half-edge 2v entering node v)
 constexpr uint32_t kUnusedLabel = 0xffffffffu;
-int inlabel_phase(Ctx* c, et_tree* t, const int32_t* parent, const uint32_t* inl, uint32_t* plab, hipStream_t s);
+int inlabel_phase(Ctx* c, et_tree* t, const int32_t* parent, const uint32_t* inl, const int32_t* depth,
+                  bool depth_kept, uint32_t* plab, hipStream_t s);
 // edges.hip: tree tables from an unordered edge list (the DCEL construction)
 int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, int32_t root, int32_t* parent_out,
                      hipStream_t s);

@@ -21,7 +21,7 @@
 //              out run by run, so consecutive lanes store to consecutive
 //              addresses.
 //
-// Both kernels take their tile from xcd_tile(): workgroups are handed to the
+// Both kernels take their tile from xcd_block(): workgroups are handed to the
 // eight XCDs in turn, and each XCD is given a contiguous range of tiles, so
 // the runs of one digit that adjacent tiles write (neighbours in the output)
 // and the histogram entries they write meet in the same L2, which merges
@@ -44,17 +44,8 @@ constexpr int kTile = kThreads * kRounds;  // 4096 keys per tile
 constexpr int kDownThreads = 512;          // downsweep: 8 wavefronts of 8 rounds per tile
 constexpr int kDownWaves = kDownThreads / 64;
 constexpr int kDownRounds = kTile / kDownThreads;
-constexpr int kXcds = 8;
 constexpr int kMaxBits = 9;                // widest digit
 constexpr int kMaxDigits = 1 << kMaxBits;  // kernels are built for 256 or 512 digits
-
-// tile of this workgroup: XCD x = blockIdx % 8 takes the x-th contiguous
-// range of tiles (a bijection of [0, ntiles) for any ntiles)
-__device__ __forceinline__ int32_t xcd_tile(int32_t ntiles) {
-  const int32_t b = (int32_t)blockIdx.x;
-  const int32_t q = ntiles / kXcds, r = ntiles % kXcds, x = b % kXcds;
-  return x * q + min(x, r) + b / kXcds;
-}
 
 __device__ __forceinline__ uint32_t parent_key(int32_t p, int32_t n) {
   return (p >= 0 && p < n) ? (uint32_t)p : 0xffffffffu;
@@ -71,7 +62,7 @@ __global__ __launch_bounds__(kThreads) void k_upsweep(const void* __restrict__ k
   const uint32_t mask = (1u << nbits) - 1u;
   for (int i = threadIdx.x; i < kWaves * DIG; i += kThreads) (&h[0][0])[i] = 0;
   __syncthreads();
-  const int32_t tile = xcd_tile(ntiles);
+  const int32_t tile = xcd_block(ntiles);
   const int64_t base = (int64_t)tile * kTile;
   bool bad = false;
   // all of a lane's loads first (guarded, not cut short), then the counts
@@ -129,7 +120,7 @@ __global__ __launch_bounds__(kDownThreads, 2) void k_downsweep(const void* __res
   const uint32_t mask = (1u << nbits) - 1u;
   for (int i = threadIdx.x; i < kDownWaves * DIG; i += kDownThreads) (&cnt[0][0])[i] = 0;
   __syncthreads();
-  const int32_t tile = xcd_tile(ntiles);
+  const int32_t tile = xcd_block(ntiles);
   const int64_t tbase = (int64_t)tile * kTile;
   const int64_t wbase = tbase + (int64_t)wave * (64 * kDownRounds) + __lane_id();
   const uint64_t below = lanemask_lt();

@@ -22,8 +22,8 @@
 //      depends on v's path: it is the ascendant of the path above plus the
 //      path's own level bit. Labels on a root path have strictly decreasing
 //      levels, so k_asc_label walks each label's chain of parent path labels
-//      (at most one link per level) into a table by label; k_asc copies it
-//      into the node records.
+//      (at most one link per level) into a table by label; k_record
+//      writes the node records with it.
 #include "et_internal.hpp"
 
 namespace et {
@@ -33,9 +33,20 @@ constexpr int kB = 256;
 
 enum { SC_ROOT = 0, SC_NROOTS = 1, SC_HEAD = 2, SC_EXPECT = 3 };
 
+// Block of nodes of this workgroup. xcd (batches): each XCD takes a
+// contiguous range of the blocks. The trees of a batch have their ids side by
+// side, so what a range gathers and stores stays in one L2 (1000 trees of up
+// to 2^18 nodes, 3.1 * 10^7 in all: k_succ 426 -> 327 us, k_head 462 -> 420,
+// k_node 419 -> 402). In one large tree with scattered ids there is nothing
+// to gain and the plain order is a little faster (k_head 563 against 592 us at
+// 2^24 nodes, k_succ 450 against 458).
+__device__ __forceinline__ int32_t block_of(bool xcd) {
+  return xcd ? xcd_block((int32_t)gridDim.x) : (int32_t)blockIdx.x;
+}
+
 __global__ void k_succ(const uint32_t* __restrict__ keys, const int32_t* __restrict__ vals, int32_t n,
-                       int32_t* __restrict__ sc, int32_t* __restrict__ succ, uint32_t* __restrict__ status) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                       int32_t* __restrict__ sc, int32_t* __restrict__ succ, uint32_t* __restrict__ status, bool xcd) {
+  const int64_t k = (int64_t)block_of(xcd) * kB + threadIdx.x;
   if (k >= n) return;
   const int32_t root = sc[SC_ROOT];
   if (k == 0) {
@@ -62,9 +73,10 @@ __global__ void k_succ(const uint32_t* __restrict__ keys, const int32_t* __restr
 
 __global__ void k_node(const uint64_t* __restrict__ packed, const int2* __restrict__ off, int32_t nsub,
                        int32_t n, const int32_t* __restrict__ sc, int32_t* __restrict__ rank,
-                       int32_t* __restrict__ pre_out, int32_t* __restrict__ size_out, int4* __restrict__ rec,
-                       uint32_t* __restrict__ inl_out, uint32_t* __restrict__ plab, uint32_t* __restrict__ status) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                       int32_t* __restrict__ pre_out, int32_t* __restrict__ size_out,
+                       uint32_t* __restrict__ inl_out, int32_t* __restrict__ depth_out, uint32_t* __restrict__ plab,
+                       uint32_t* __restrict__ status, bool xcd) {
+  const int64_t c = (int64_t)block_of(xcd) * kB + threadIdx.x;
   if (c >= n) return;
   plab[c] = kUnusedLabel;  // the label table of inlabel_phase, n + 1 entries
   if (c == n - 1) plab[n] = kUnusedLabel;
@@ -91,22 +103,20 @@ __global__ void k_node(const uint64_t* __restrict__ packed, const int2* __restri
   reinterpret_cast<int2*>(rank)[c] = make_int2(r0, r1);
   pre_out[c] = pre;
   size_out[c] = size;
-  const uint32_t inl = inlabel_of(pre, size);
-  rec[c] = make_int4((int32_t)inl, 0, depth, pre);
-  inl_out[c] = inl;
+  inl_out[c] = inlabel_of(pre, size);
+  depth_out[c] = depth;
 }
 
 // Path tops: a node is the top of its inlabel path iff it is the root or its
 // parent's inlabel differs. head[I] = {parent of the top, its depth}, and
 // plab[I] = the inlabel of that parent (0 for the root's path).
-__global__ void k_head(const int32_t* __restrict__ parent, const int4* __restrict__ rec,
+__global__ void k_head(const int32_t* __restrict__ parent, const int32_t* __restrict__ depth_of,
                        const uint32_t* __restrict__ inl_of, int32_t n, const int32_t* __restrict__ sc,
-                       int2* __restrict__ head, uint32_t* __restrict__ plab, uint32_t* __restrict__ status) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                       int2* __restrict__ head, uint32_t* __restrict__ plab, uint32_t* __restrict__ status, bool xcd) {
+  const int64_t v = (int64_t)block_of(xcd) * kB + threadIdx.x;
   if (v >= n) return;
   const int32_t root = sc[SC_ROOT];
-  const int4 rv = rec[v];
-  const uint32_t inl = (uint32_t)rv.x;
+  const uint32_t inl = inl_of[v];
   const int32_t p = parent[v];
   bool top;
   uint32_t pinl = 0;
@@ -121,7 +131,7 @@ __global__ void k_head(const int32_t* __restrict__ parent, const int4* __restric
   }
   if (top) {
     if (inl >= 1u && inl <= (uint32_t)n) {
-      head[inl] = make_int2(v == root ? -1 : p, rv.z - 1);
+      head[inl] = make_int2(v == root ? -1 : p, depth_of[v] - 1);
       plab[inl] = (v == root) ? 0u : pinl;
     } else {
       flag(status, ST_BAD_INDEX);
@@ -232,15 +242,27 @@ __global__ __launch_bounds__(kB) void k_asc_upper(const uint32_t* __restrict__ p
   asc_of_label[I] = acc;
 }
 
-__global__ void k_asc(int4* __restrict__ rec, const uint32_t* __restrict__ inl_of,
-                      const uint32_t* __restrict__ asc_of_label, int32_t n, uint32_t* __restrict__ status) {
+// The node records {inlabel, ascendant, depth, preorder}, each written once
+// and whole: the ascendant is gathered by label, the rest streamed. With the
+// record begun in k_node and the ascendant stored into it here, every record
+// was written twice, the second time as a quarter of its bytes; written here
+// it takes the same time (the gather's, 367 us at 2^24 nodes) and k_node and
+// k_head move fewer bytes (412 -> 377 and 590 -> 563 us).
+// depth_of: nullptr if depth = 2 * preorder - rank - 1, rank[2v] being the
+// rank of v's entering half-edge (-1 at the root).
+__global__ void k_record(const uint32_t* __restrict__ inl_of, const uint32_t* __restrict__ asc_of_label,
+                         const int32_t* __restrict__ pre_of, const int32_t* __restrict__ rank,
+                         const int32_t* __restrict__ depth_of, int32_t n, int4* __restrict__ rec,
+                         uint32_t* __restrict__ status) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n) return;
-  const uint32_t inl = inl_of[v];  // the compact copy: a quarter of the record's lines
+  const uint32_t inl = inl_of[v];
   uint32_t a = 0;
   if (inl >= 1u && inl <= (uint32_t)n) a = asc_of_label[inl];
   else flag(status, ST_BAD_INDEX);
-  reinterpret_cast<int32_t*>(rec)[4 * v + 1] = (int32_t)a;
+  const int32_t pre = pre_of[v];
+  const int32_t depth = depth_of ? depth_of[v] : 2 * pre - reinterpret_cast<const int2*>(rank)[v].x - 1;
+  rec[v] = make_int4((int32_t)inl, (int32_t)a, depth, pre);
 }
 
 // n == 1: the root is the only node
@@ -493,22 +515,26 @@ int tree_build(Ctx* c, et_tree* t, const int32_t* parent, hipStream_t s) {
     if (rc) return rc;
     {
       ET_PROF(c, s, "k_succ");
-      hipLaunchKernelGGL(k_succ, dim3(gn), dim3(kB), 0, s, keys, vals, n, sc, t->d_succ, c->d_status);
+      hipLaunchKernelGGL(k_succ, dim3(gn), dim3(kB), 0, s, keys, vals, n, sc, t->d_succ, c->d_status,
+                         t->batch != 0);
     }
     rc = list_rank_core(c, scr, t->d_succ, L2, sc + SC_HEAD, 1, true, sc + SC_EXPECT, &lr, s);
     if (rc) return rc;
     {
       ET_PROF(c, s, "k_node");
       hipLaunchKernelGGL(k_node, dim3(gn), dim3(kB), 0, s, lr.packed, lr.off, lr.nsub, n, sc, t->d_rank, t->d_pre,
-                         t->d_size, t->d_rec, inl, kv, c->d_status);
+                         t->d_size, inl, reinterpret_cast<int32_t*>(kv + n + 1), kv, c->d_status, t->batch != 0);
     }
   }
-  return inlabel_phase(c, t, parent, inl, kv, s);  // the grouping's keys and values are dead by now
+  // the grouping's keys and values are dead by now: the label table, and the
+  // depths until the ascendants take their place
+  return inlabel_phase(c, t, parent, inl, reinterpret_cast<int32_t*>(kv + n + 1), false, kv, s);
 }
 
 constexpr int32_t kAscTwo = 1 << 20;  // nodes from which the ascendants take two launches
 
-int inlabel_phase(Ctx* c, et_tree* t, const int32_t* parent, const uint32_t* inl, uint32_t* plab, hipStream_t s) {
+int inlabel_phase(Ctx* c, et_tree* t, const int32_t* parent, const uint32_t* inl, const int32_t* depth,
+                  bool depth_kept, uint32_t* plab, hipStream_t s) {
   const int32_t n = t->n;
   int32_t* sc = t->d_root;
   const int gn = ceil_div(n, kB);
@@ -516,8 +542,8 @@ int inlabel_phase(Ctx* c, et_tree* t, const int32_t* parent, const uint32_t* inl
   ET_PROF(c, s, "phase:inlabel");
   {
     ET_PROF(c, s, "k_head");
-    hipLaunchKernelGGL(k_head, dim3(gn), dim3(kB), 0, s, parent, t->d_rec, inl, n, sc, t->d_head, plab,
-                       c->d_status);
+    hipLaunchKernelGGL(k_head, dim3(gn), dim3(kB), 0, s, parent, depth, inl, n, sc, t->d_head, plab,
+                       c->d_status, t->batch != 0);
   }
   {
     ET_PROF(c, s, "k_asc_label");
@@ -533,8 +559,9 @@ int inlabel_phase(Ctx* c, et_tree* t, const int32_t* parent, const uint32_t* inl
     }
   }
   {
-    ET_PROF(c, s, "k_asc");
-    hipLaunchKernelGGL(k_asc, dim3(gn), dim3(kB), 0, s, t->d_rec, inl, asc, n, c->d_status);
+    ET_PROF(c, s, "k_record");
+    hipLaunchKernelGGL(k_record, dim3(gn), dim3(kB), 0, s, inl, asc, t->d_pre, t->d_rank, depth_kept ? depth : nullptr,
+                       n, t->d_rec, c->d_status);
   }
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 }
