@@ -313,6 +313,9 @@ struct LRResult {
 int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const int32_t* heads,
                    int32_t nheads, bool tree_weights, const int32_t* expected_reach,
                    LRResult* out, hipStream_t s, bool empty_head_ok = false, int weighted = 0);
+// allows the ranking kernels their dynamic LDS on the current device (once,
+// when a context is created: the calls themselves then set nothing up)
+int list_rank_prepare();
 // radix.hip: stable sort of (key, value) pairs by the low `bits` key bits
 int sort_pairs_u32(Ctx* c, const uint32_t* keys, const int32_t* vals, int32_t n, int bits, uint32_t* keys_out,
                    int32_t* vals_out, hipStream_t s);

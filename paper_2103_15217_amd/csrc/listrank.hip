@@ -15,9 +15,11 @@
 //           continuation sublists so the local fields fit 16 bits.
 //  level k  The list of sublists is ranked the same way with the sublist
 //           lengths as weights, until it has at most kLdsMax elements.
-//  final    One workgroup ranks the last list in LDS by jumping predecessor
-//           pointers (Wyllie) and checks that every used element is reached
-//           from a head; offsets are then pushed back down the levels.
+//  final    One workgroup ranks the last list in LDS, again by sublists (a
+//           lane walks each, then predecessor pointers jump over them), and
+//           checks that every used element is reached from a head; offsets
+//           are then pushed back down the levels.
+// A list of at most kLdsDirect elements goes to the final level at once.
 //
 // Every walk is bounded and every gathered index is range checked, so a
 // malformed list (a cycle, a shared successor, an id out of range) sets a
@@ -28,7 +30,10 @@ namespace et {
 namespace {
 
 constexpr int kCap = 65535;        // level-1 sublist length cap (16-bit local fields)
-constexpr int kLdsMax = 4096;      // elements the final LDS kernel ranks
+constexpr int kLdsMax = 12288;     // elements the final LDS kernel ranks (10 bytes of LDS each)
+constexpr int kLdsDirect = 8192;   // elements of a list that goes to it whole
+constexpr int kLdsHeads = 1024;    // heads it takes; beyond, the final level is k_final_lds
+constexpr int kLdsMaxHeads = 4096; // elements k_final_lds ranks
 constexpr int kWalkThreads = 256;
 constexpr uint32_t kSalt = 0x9e3779b9u;
 
@@ -288,21 +293,284 @@ __global__ __launch_bounds__(kWalkThreads) void k_walkN(
 }
 
 // ------------------------------------------------------------------ final level (LDS)
-// Exclusive prefix (len, down) from each element's list head, by jumping
-// predecessor pointers in LDS. T <= kLdsMax. Elements whose predecessor
-// chain does not start at a head are unreachable (malformed input).
+// Exclusive prefix (len, down) of every element of a short list from its
+// list's head, by one workgroup: sublists once more, walked by a lane each at
+// LDS latency (60 ns a step, where a step of k_walkN waits for memory: about
+// 500 ns), then predecessor pointers jump over the at most 1024 + H sublists.
+// Against jumping over every element, limited to 4096, a list of sublists
+// needs one k_walkN and k_push_down level less: 10^6-node build 355 -> 345 us.
+// Bound by LDS bandwidth: the wavefronts' steps until their longest sublists
+// end. 20 us for 2000 elements, 34 for 8000.
+//   IN_REC   level records {next, len, down} (next == -3 unused); the heads
+//            are the H records from hb on
+//   IN_SUCC, IN_TREE, IN_PAIR   a whole list, as k_walk1's W = 0 (plain), W = 0
+//            (tree half-edges) and W > 0 inputs; the level-1 records are then
+//            one sublist per element (PAIR2: with the 16-byte records), or,
+//            where `rank` is given, the ranks are written themselves
+// Elements whose predecessor chain does not start at a head are unreachable
+// (malformed input), as are elements that no walk passes.
 constexpr int kFinalThreads = 1024;
-constexpr int kFinalPer = kLdsMax / kFinalThreads;
+constexpr int kFinalSub = 2;  // sublists per lane: 1024 by chunks, kLdsHeads by heads
+enum { IN_REC, IN_SUCC, IN_TREE, IN_PAIR, IN_PAIR2 };
+
+struct RankLds {  // bytes of the dynamic LDS of k_rank_lds
+  uint32_t dn, acl, acd, nxt, pred, top, hb, total;
+};
+
+__host__ __device__ inline RankLds rank_lds_layout(uint32_t T, uint32_t SM) {
+  RankLds l;
+  l.dn = 4 * T;
+  l.acl = 8 * T;
+  l.acd = l.acl + 4 * SM;
+  l.hb = l.acd + 4 * SM;
+  l.nxt = l.hb + 4 * ((SM + 31) / 32) + 16;
+  l.pred = l.nxt + 2 * ((T + 1) & ~1u);
+  l.top = l.pred + 2 * ((SM + 1) & ~1u);
+  l.total = l.top + 2 * ((SM + 1) & ~1u);
+  return l;
+}
+
+// smallest spacing that leaves at most 1024 chunks
+inline int rank_lds_ks(int32_t T) {
+  int ks = 0;
+  while (((T + (1 << ks) - 1) >> ks) > 1024) ++ks;
+  return ks;
+}
+
+// dynamic LDS of k_rank_lds for T elements and H heads
+inline uint32_t rank_lds_bytes(int32_t T, int32_t H) {
+  const int ks = rank_lds_ks(T);
+  return rank_lds_layout((uint32_t)T, (uint32_t)(((T + (1 << ks) - 1) >> ks) + H)).total;
+}
+
+template <int IN>
+__global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
+    const int32_t* __restrict__ in, int32_t T, const int32_t* __restrict__ heads, int32_t hb, int32_t H,
+    bool empty_ok, int ks, uint32_t salt, uint64_t* __restrict__ packed, int2* __restrict__ off,
+    int32_t* __restrict__ rank, const int32_t* __restrict__ expected, uint32_t* __restrict__ status) {
+  // NXT: the next element, kEnd or kUnused, kSplit set if the next element is
+  // a splitter (decided here, not in the dependent walk); kWalked | sublist
+  // once walked
+  constexpr uint32_t kEnd = 0x3fffu, kUnused = 0x3ffeu, kSplit = 0x4000u, kWalked = 0x8000u;
+  static_assert(kLdsMax <= 0x3ffe && 1024 + kLdsHeads <= 0x7fff, "the codes of NXT");
+  constexpr uint32_t kNone = 0xffffu;
+  constexpr bool kLen = IN == IN_REC;                    // element lengths other than 1
+  constexpr bool kDn = IN != IN_SUCC && IN != IN_TREE;   // element weights from the input
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int32_t S = (T + (1 << ks) - 1) >> ks, SM = S + H;
+  const RankLds lay = rank_lds_layout((uint32_t)T, (uint32_t)SM);
+  int32_t* LEN = reinterpret_cast<int32_t*>(lds);
+  int32_t* DN = reinterpret_cast<int32_t*>(lds + lay.dn);
+  int32_t* ACL = reinterpret_cast<int32_t*>(lds + lay.acl);
+  int32_t* ACD = reinterpret_cast<int32_t*>(lds + lay.acd);
+  uint32_t* HB = reinterpret_cast<uint32_t*>(lds + lay.hb);  // bit per sublist: starts at a head; then the reach
+  uint16_t* NXT = reinterpret_cast<uint16_t*>(lds + lay.nxt);
+  uint16_t* PRED = reinterpret_cast<uint16_t*>(lds + lay.pred);
+  uint16_t* TOP = reinterpret_cast<uint16_t*>(lds + lay.top);
+  const int hw = (SM + 31) / 32;
+  const int t = threadIdx.x;
+  bool bad = false, badhead = false;
+  for (int s = t; s < SM; s += kFinalThreads) {
+    PRED[s] = (uint16_t)kNone;
+    TOP[s] = (uint16_t)s;
+  }
+  for (int i = t; i <= hw; i += kFinalThreads) HB[i] = 0u;
+#pragma unroll 4
+  for (int32_t e = t; e < T; e += kFinalThreads) {
+    int32_t nx, l = 1, d = 0;
+    bool used;
+    if (IN == IN_REC) {
+      const int4 r = reinterpret_cast<const int4*>(in)[e];
+      nx = r.x;
+      used = nx != -3;
+      l = r.y;
+      d = r.z;
+    } else if (IN == IN_PAIR || IN == IN_PAIR2) {
+      const int2 r = reinterpret_cast<const int2*>(in)[e];
+      nx = r.x;
+      used = nx != -2;
+      d = r.y;
+    } else {
+      nx = in[e];
+      used = nx != -2;
+      if (IN == IN_TREE) d = (e & 1) == 0;
+    }
+    uint32_t code = kUnused;
+    if (used) {
+      code = nx == -1 ? kEnd : (uint32_t)nx;
+      if (nx < -1 || nx >= T) {
+        bad = true;
+        code = kEnd;
+      }
+      if (code != kEnd && is_splitter((int32_t)code, ks, salt)) code |= kSplit;
+    }
+    NXT[e] = (uint16_t)code;
+    if (kLen) LEN[e] = l;
+    if (kDn) DN[e] = d;
+  }
+  __syncthreads();
+  int32_t wl[kFinalSub], wd[kFinalSub], to[kFinalSub];
+#pragma unroll
+  for (int k = 0; k < kFinalSub; ++k) {
+    wl[k] = wd[k] = 0;
+    to[k] = -1;
+    const int32_t s = t + k * kFinalThreads;
+    if (s >= SM) continue;
+    int32_t e = -1;
+    if (s < S) {
+      e = splitter_of_chunk(s, ks, salt);
+      if (e >= T || NXT[e] == kUnused) e = -1;
+    } else {
+      const int32_t h = IN == IN_REC ? hb + (s - S) : heads[s - S];
+      if (!(h == -1 && empty_ok)) {
+        if (h < 0 || h >= T) {
+          badhead = true;
+        } else if (NXT[h] == kUnused) {
+          badhead = badhead || IN != IN_REC;
+        } else if (is_splitter(h, ks, salt)) {
+          // the head's own chunk walks it
+          const uint32_t bit = 1u << ((h >> ks) & 31);
+          if (atomicOr(&HB[(h >> ks) >> 5], bit) & bit) badhead = true;  // the same head twice
+        } else {
+          e = h;
+          atomicOr(&HB[s >> 5], 1u << (s & 31));
+        }
+      }
+    }
+    if (e >= 0) {
+      int32_t al = 0, ad = 0;
+      for (int32_t step = 0;; ++step) {
+        const uint32_t nx = NXT[e];
+        if ((nx & kWalked) || nx == kUnused || step >= T) {  // a second way into an element, or into no element
+          bad = true;
+          break;
+        }
+        NXT[e] = (uint16_t)(kWalked | (uint32_t)s);
+        const int32_t l = kLen ? LEN[e] : 1;
+        const int32_t d = kDn ? DN[e] : (IN == IN_TREE ? (int32_t)((e & 1) == 0) : 0);
+        LEN[e] = al;
+        if (IN != IN_SUCC) DN[e] = ad;
+        al += l;
+        ad = wadd(ad, d);
+        if (nx >= kEnd) {
+          if (nx & kSplit) {
+            to[k] = (int32_t)(nx & (kSplit - 1u)) >> ks;
+            PRED[to[k]] = (uint16_t)s;
+          }
+          break;
+        }
+        e = (int32_t)nx;
+      }
+      wl[k] = al;
+      wd[k] = ad;
+    }
+    ACL[s] = wl[k];
+    ACD[s] = wd[k];
+  }
+  if (bad) flag(status, ST_BAD_SUCC);
+  if (badhead) flag(status, ST_BAD_HEAD);
+  // at most clog2(SM) + 1 rounds; fewer once no pointer is left
+  for (int it = 0; it < 13; ++it) {
+    __syncthreads();
+    int32_t nl[kFinalSub], nd[kFinalSub];
+    uint32_t np[kFinalSub], nt[kFinalSub];
+    bool more = false;
+#pragma unroll
+    for (int k = 0; k < kFinalSub; ++k) {
+      const int32_t s = t + k * kFinalThreads;
+      if (it == 0 && to[k] >= 0 && PRED[to[k]] != s) flag(status, ST_BAD_SUCC);  // two sublists lead into one
+      np[k] = s < SM ? PRED[s] : kNone;
+      if (np[k] != kNone) {
+        if (it == 0 && ((HB[s >> 5] >> (s & 31)) & 1u)) flag(status, ST_BAD_HEAD);  // a head inside a list
+        const uint32_t q = np[k];
+        nl[k] = ACL[s] + ACL[q];
+        nd[k] = wadd(ACD[s], ACD[q]);
+        nt[k] = TOP[q];
+        np[k] = PRED[q];
+        more = true;
+      } else {
+        nt[k] = kNone;  // nothing to write
+      }
+    }
+    if (!__syncthreads_or(more)) break;
+#pragma unroll
+    for (int k = 0; k < kFinalSub; ++k) {
+      const int32_t s = t + k * kFinalThreads;
+      if (nt[k] != kNone) {
+        ACL[s] = nl[k];
+        ACD[s] = nd[k];
+        TOP[s] = (uint16_t)nt[k];
+        PRED[s] = (uint16_t)np[k];
+      }
+    }
+  }
+  int32_t mine = 0;
+  bool reached[kFinalSub];
+#pragma unroll
+  for (int k = 0; k < kFinalSub; ++k) {
+    const int32_t s = t + k * kFinalThreads;
+    reached[k] = false;
+    if (s >= SM) continue;
+    const uint32_t top = TOP[s];
+    reached[k] = PRED[s] == kNone && ((HB[top >> 5] >> (top & 31)) & 1u);
+    if (reached[k]) mine += wl[k];
+    ACL[s] -= wl[k];
+    ACD[s] = wsub(ACD[s], wd[k]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kFinalSub; ++k) {
+    const int32_t s = t + k * kFinalThreads;
+    if (s < SM) PRED[s] = reached[k];
+  }
+  for (int dd = 32; dd >= 1; dd >>= 1) mine += __shfl_xor(mine, dd, 64);
+  if (__lane_id() == 0 && mine) atomicAdd(&HB[hw], (uint32_t)mine);  // (the slot after the bits)
+  __syncthreads();
+  bool unreached = t == 0 && expected && (int32_t)HB[hw] != *expected;
+#pragma unroll 4
+  for (int32_t e = t; e < T; e += kFinalThreads) {
+    const uint32_t c = NXT[e];  // kWalked | sublist, or never walked
+    if (c == kUnused) {
+      if (IN == IN_SUCC && rank) rank[e] = -1;
+      continue;
+    }
+    int2 o = make_int2(0, 0);
+    if (c & kWalked) {
+      const uint32_t s = c & (kWalked - 1u);
+      o = make_int2(ACL[s] + LEN[e], IN != IN_SUCC ? wadd(ACD[s], DN[e]) : 0);
+      if (!PRED[s]) unreached = true;
+    } else {
+      unreached = true;
+    }
+    if (IN == IN_SUCC && rank) {
+      rank[e] = o.x;
+      continue;
+    }
+    off[e] = o;
+    if (IN == IN_SUCC) packed[e] = (uint64_t)(uint32_t)e;
+    if (IN == IN_TREE) packed[e] = (uint64_t)(uint32_t)e | ((uint64_t)((e & 1) == 0) << 48);
+    if (IN == IN_PAIR) packed[e] = (uint64_t)(uint32_t)e | ((uint64_t)(uint32_t)in[2 * e + 1] << 32);
+    if (IN == IN_PAIR2)
+      reinterpret_cast<ulonglong2*>(packed)[e] =
+          make_ulonglong2((uint64_t)(uint32_t)e, (uint64_t)(uint32_t)in[2 * e + 1]);
+  }
+  if (unreached) flag(status, ST_UNREACHED);
+}
+
+// The final level of lists with many heads (more sublists than the kernel
+// above has lanes for): predecessor pointers jump over every element. T <=
+// kLdsMaxHeads.
+constexpr int kFinalPer = kLdsMaxHeads / kFinalThreads;
 
 __global__ __launch_bounds__(kFinalThreads) void k_final_lds(const int4* __restrict__ rec, int32_t T,
                                                              int32_t hb, int32_t H, int2* __restrict__ off,
                                                              int32_t* __restrict__ reached,
                                                              const int32_t* __restrict__ expected,
                                                              uint32_t* __restrict__ status) {
-  __shared__ int32_t pred[kLdsMax];
-  __shared__ int32_t acl[kLdsMax];
-  __shared__ int32_t acd[kLdsMax];
-  __shared__ int32_t top[kLdsMax];
+  __shared__ int32_t pred[kLdsMaxHeads];
+  __shared__ int32_t acl[kLdsMaxHeads];
+  __shared__ int32_t acd[kLdsMaxHeads];
+  __shared__ int32_t top[kLdsMaxHeads];
   const int t = threadIdx.x;
   int32_t wl[kFinalPer], wd[kFinalPer];
   bool used[kFinalPer];
@@ -367,7 +635,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_final_lds(const int4* __restr
   if (threadIdx.x == 0 && expected && atomicAdd(reached, 0) != *expected) flag(status, ST_UNREACHED);
 }
 
-// Final level when many heads keep the list above kLdsMax: one lane per
+// Final level when many heads keep the list above kLdsMaxHeads: one lane per
 // head walks its (short) list.
 __global__ void k_final_walk(const int4* __restrict__ rec, int32_t T, int32_t hb, int32_t H,
                              int2* __restrict__ off, int32_t* __restrict__ reached,
@@ -527,10 +795,23 @@ struct LrPlan {
   uint64_t* packed = nullptr;
   int4* rec1 = nullptr;
   int32_t* ctr = nullptr;
+  bool direct = false;  // the whole list goes to k_rank_lds
   std::vector<LrLevel> lv;
 };
 
 static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weighted, LrPlan* pl) {
+  const int32_t lds_max = H <= kLdsHeads ? kLdsMax : kLdsMaxHeads;
+  // One workgroup ranks a short list by itself, one launch in place of three.
+  // Tree builds by this / by level 1 and a final level: 60 / 68 us at 2000
+  // half-edges, 74 / 80 at 8000, 91 / 87 at 12000; plain lists (whose ranks
+  // it writes itself) 16 / 29, 29 / 38 and 39 / 39 us
+  pl->direct = L <= kLdsDirect && H <= kLdsHeads;
+  if (pl->direct) {
+    pl->T1 = L;
+    pl->packed = sc.get<uint64_t>((size_t)L * (weighted == 2 ? 2 : 1));
+    pl->lv.assign(1, {nullptr, L, 0, nullptr, sc.get<int2>((size_t)L), 0, 0, 0});
+    return;
+  }
   // Level-1 splitter spacing K = 2^ks1 (a sublist averages K elements).
   // Shorter lists keep more, shorter sublists: below about 2^25 elements the
   // walk is bound by its dependent steps rather than by line fetches, so the
@@ -550,8 +831,12 @@ static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weight
   pl->lv.push_back({pl->rec1, pl->T1, pl->S1, nullptr, nullptr, 0, 0, 0});
   for (;;) {
     LrLevel& cur = pl->lv.back();
-    if (cur.T <= kLdsMax) break;
-    const int ks = c->lr.kn_log2;
+    if (cur.T <= lds_max) break;
+    // the context's spacing, or a smaller one that already fits the final
+    // level: the walk of a level lasts as long as its longest sublist, about
+    // 2^ks ln(sublists) dependent steps
+    int ks = std::min(2, c->lr.kn_log2);
+    while (ks < c->lr.kn_log2 && (((int64_t)cur.T + (1 << ks) - 1) >> ks) + H > lds_max) ++ks;
     const int32_t S = (int32_t)(((int64_t)cur.T + (1 << ks) - 1) >> ks);
     const int32_t Tn = S + H;
     if ((int64_t)Tn * 2 > cur.T) break;  // many heads: shrinking stalls
@@ -569,6 +854,18 @@ static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32
                             int32_t H, bool tree_weights, const int32_t* expected_reach, hipStream_t s,
                             bool empty_head_ok, int weighted) {
   const int32_t S1 = pl.S1, T1 = pl.T1, cont_max = pl.cont_max;
+  if (pl.direct) {
+    const int ks = rank_lds_ks(L);
+    const auto kern = tree_weights    ? k_rank_lds<IN_TREE>
+                      : weighted == 2 ? k_rank_lds<IN_PAIR2>
+                      : weighted      ? k_rank_lds<IN_PAIR>
+                                      : k_rank_lds<IN_SUCC>;
+    ET_PROF(c, s, "k_rank_lds");
+    hipLaunchKernelGGL(kern, dim3(1), dim3(kFinalThreads), rank_lds_bytes(L, H), s, succ, L, heads, 0, H,
+                       empty_head_ok, ks, kSalt,
+                       pl.packed, pl.lv[0].off, nullptr, expected_reach, c->d_status);
+    return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
+  }
   hipLaunchKernelGGL(k_lr_init, dim3(ceil_div(cont_max, 256)), dim3(256), 0, s, pl.ctr, pl.rec1, S1 + H, T1);
   const dim3 g1(walk_grid(S1 + H, pl.per_wave1));
   if (tree_weights) {
@@ -596,7 +893,13 @@ static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32
                        c->d_status);
   }
   const LrLevel& top = lv.back();
-  if (top.T <= kLdsMax) {
+  if (H <= kLdsHeads && top.T <= kLdsMax) {
+    const int ks = rank_lds_ks(top.T);
+    ET_PROF(c, s, "k_rank_lds");
+    hipLaunchKernelGGL(k_rank_lds<IN_REC>, dim3(1), dim3(kFinalThreads), rank_lds_bytes(top.T, H), s,
+                       reinterpret_cast<const int32_t*>(top.rec), top.T, nullptr, top.hb, H, false, ks,
+                       kSalt ^ (uint32_t)lv.size(), nullptr, top.off, nullptr, expected_reach, c->d_status);
+  } else if (top.T <= kLdsMaxHeads) {
     ET_PROF(c, s, "k_final_lds");
     hipLaunchKernelGGL(k_final_lds, dim3(1), dim3(kFinalThreads), 0, s, top.rec, top.T, top.hb, H, top.off,
                        pl.ctr + 1, expected_reach, c->d_status);
@@ -614,6 +917,17 @@ static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32
                        lv[k + 1].off, lv[k + 1].T, lv[k].off, c->d_status);
   }
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
+}
+
+int list_rank_prepare() {
+  for (const void* kern :
+       {reinterpret_cast<const void*>(k_rank_lds<IN_REC>), reinterpret_cast<const void*>(k_rank_lds<IN_SUCC>),
+        reinterpret_cast<const void*>(k_rank_lds<IN_TREE>), reinterpret_cast<const void*>(k_rank_lds<IN_PAIR>),
+        reinterpret_cast<const void*>(k_rank_lds<IN_PAIR2>)})
+    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)rank_lds_bytes(kLdsMax, kLdsHeads)) != hipSuccess)
+      return ET_EHIP;
+  return ET_OK;
 }
 
 int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const int32_t* heads,
@@ -638,6 +952,13 @@ static int list_rank_with(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len,
   LrPlan pl;
   list_rank_plan(c, sc, len, nheads, 0, &pl);
   if (sc.failed || sc.counting) return sc.failed ? ET_ENOMEM : ET_OK;
+  if (pl.direct) {  // sees every element itself: nothing to count, no records to add up
+    const int ks = rank_lds_ks(len);
+    ET_PROF(c, s, "k_rank_lds");
+    hipLaunchKernelGGL(k_rank_lds<IN_SUCC>, dim3(1), dim3(kFinalThreads), rank_lds_bytes(len, nheads), s, succ, len,
+                       heads, 0, nheads, false, ks, kSalt, nullptr, nullptr, rank, nullptr, c->d_status);
+    return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
+  }
   hipLaunchKernelGGL(k_set_scalar, dim3(1), dim3(1), 0, s, expected, 0);
   {
     ET_PROF(c, s, "k_count_used");
