@@ -244,7 +244,8 @@ int et_ctx_create(et_ctx** out) {
     delete ctx;
     return ET_ENOMEM;
   }
-  if (hipMemset(p, 0, 256) != hipSuccess || et::list_rank_prepare() != ET_OK) {
+  if (hipMemset(p, 0, 256) != hipSuccess || et::list_rank_prepare() != ET_OK ||
+      et::small_tree_prepare() != ET_OK) {
     (void)hipFree(p);
     delete ctx;
     return ET_EHIP;

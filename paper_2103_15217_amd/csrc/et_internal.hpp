@@ -393,6 +393,11 @@ int small_bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, const 
                       hipStream_t s);
 // small.hip: build and query many trees of at most 4096 nodes in one launch
 size_t small_batch_lds_bytes(int32_t max_nodes);
+// one tree of 2 .. kSmallTreeMax nodes into its tables, in one launch; prepare
+// as for list_rank_prepare
+constexpr int32_t kSmallTreeMax = 4096;
+int small_tree_prepare();
+int small_tree_build(Ctx* c, et_tree* t, const int32_t* parent, hipStream_t s);
 int small_batch_run(Ctx* c, const int32_t* parent, const int64_t* off, int32_t T, int64_t n_total,
                     int32_t max_nodes, const int64_t* qoff, const int32_t* qx, const int32_t* qy, int64_t q_total,
                     int32_t* out, int32_t* depth, int32_t* pre, int32_t* size, const int32_t* order,

@@ -1,11 +1,11 @@
 // Many small trees built and queried in one launch (Section 3.3: a batch of
 // LCA queries answered on trees that are preprocessed once; Section 2 and
-// 3.1 for what each tree goes through).
+// 3.1 for what each tree goes through), and the build of one small tree.
 //
-// A workgroup of 1024 lanes (256 when no tree has more than 1024 nodes and
-// the trees outnumber the compute units) takes one tree at a time from an
-// atomic counter, in the caller's order when one is given
-// (the grid is sized to what stays resident, so the launch is persistent)
+// In a batch a workgroup of 1024 lanes (256 when no tree has more than 1024
+// nodes and the trees outnumber the compute units) takes one tree at a time
+// from an atomic counter, in the caller's order when one is given (the grid is
+// sized to what stays resident, so the launch is persistent)
 // and runs the tree's whole path in LDS, reading only its parent array and
 // its queries from HBM and writing only the answers (and, on request, the
 // node statistics):
@@ -106,6 +106,322 @@ __device__ __forceinline__ uint64_t match_digit(bool valid, uint32_t d) {
 
 __device__ __forceinline__ uint16_t root_key(uint16_t p, uint32_t n) { return p == kEnd ? (uint16_t)n : p; }
 
+// A tree's tables in LDS and the steps that make them. Every step is run by
+// the whole workgroup, and ends with a barrier unless it says otherwise.
+template <int kFT>
+struct SmallTree {
+  static constexpr int kFW = kFT / 64;  // wavefronts per workgroup
+  static_assert(kFT * kRoundsMax >= kFSmall && kFW <= kWavesMax, "a lane holds at most kRoundsMax nodes");
+  uint16_t *P, *SUCC, *R0, *R1, *D0, *PLAB, *ORD0, *ORD1, *INL, *ASC, *DEP, *SUB;
+  uint32_t *HEAD, *CNT, *LDa;
+  int32_t* SC;
+  const int tid, lane, w;
+
+  __device__ __forceinline__ SmallTree(unsigned char* lds, uint32_t N)
+      : tid(threadIdx.x), lane(threadIdx.x & 63), w(threadIdx.x >> 6) {
+    const SmallLayout L = small_layout(N);
+    P = reinterpret_cast<uint16_t*>(lds + L.p);
+    SUCC = reinterpret_cast<uint16_t*>(lds + L.rb);
+    HEAD = reinterpret_cast<uint32_t*>(lds + L.rb);
+    CNT = reinterpret_cast<uint32_t*>(lds + L.rc);
+    R0 = reinterpret_cast<uint16_t*>(lds + L.rc);  // rank of 2c
+    R1 = R0 + N;                                    // rank of 2c + 1
+    D0 = R0 + 2 * N;                                // down count through 2c
+    PLAB = reinterpret_cast<uint16_t*>(lds + L.rc);
+    ORD0 = reinterpret_cast<uint16_t*>(lds + L.rd);
+    ORD1 = ORD0 + N;
+    INL = reinterpret_cast<uint16_t*>(lds + L.rd);
+    ASC = INL + N;
+    DEP = ASC + N;
+    // sublist next, and length << 16 | down count (both below 2^16, so one
+    // 32-bit add sums both), two buffers each (pointer jumping)
+    SUB = reinterpret_cast<uint16_t*>(lds + L.rf);
+    LDa = reinterpret_cast<uint32_t*>(lds + L.rf + 4 * kSubMax);
+    SC = reinterpret_cast<int32_t*>(lds + L.sc);
+  }
+  __device__ __forceinline__ uint16_t* NX(int b) const { return SUB + b * kSubMax; }
+  __device__ __forceinline__ uint32_t* LD(int b) const { return LDa + b * kSubMax; }
+
+  // scalars of a new tree (no barrier)
+  __device__ __forceinline__ void begin(bool ok) {
+    if (tid == 0) {
+      SC[S_NROOTS] = 0;
+      SC[S_BAD] = 0;
+      SC[S_FAIL] = ok ? 0 : 1;
+      SC[S_HEAD] = -1;
+    }
+  }
+
+  // 1. the tree's n parents into P, checked
+  __device__ __forceinline__ void parents(const int32_t* __restrict__ parent, uint32_t n, bool ok,
+                                          uint32_t* __restrict__ status) {
+    __syncthreads();
+    int32_t praw[kRoundsMax];  // all of a lane's parent loads first
+#pragma unroll
+    for (int r = 0; r < kRoundsMax; ++r) {
+      const uint32_t c = tid + r * kFT;
+      praw[r] = c < n ? parent[c] : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < kRoundsMax; ++r) {
+      const uint32_t c = tid + r * kFT;
+      if (c >= n) break;
+      const int32_t p = praw[r];
+      if (p == -1) {
+        P[c] = kEnd;
+        atomicAdd(&SC[S_NROOTS], 1);
+        SC[S_ROOT] = (int32_t)c;
+      } else if (p >= 0 && (uint32_t)p < n && (uint32_t)p != c) {
+        P[c] = (uint16_t)p;
+      } else {
+        P[c] = 0;
+        SC[S_BAD] = 1;
+      }
+    }
+    __syncthreads();
+    if (ok && (SC[S_NROOTS] != 1 || SC[S_BAD])) {
+      if (tid == 0) {
+        flag(status, SC[S_BAD] ? ST_BAD_PARENT : ST_ROOTS);
+        SC[S_FAIL] = 1;
+      }
+    }
+    __syncthreads();
+  }
+
+  // 2. and 3. children grouped by parent, successors
+  __device__ __forceinline__ void tour(uint32_t n, uint32_t root, uint32_t* __restrict__ status) {
+    const uint32_t E = 2 * n;
+    // 2. stable radix sort of child ids by parent id
+    for (uint32_t i = tid; i < n; i += kFT) ORD0[i] = (uint16_t)i;
+    uint16_t* src = ORD0;
+    uint16_t* dst = ORD1;
+    const int kbits = 32 - __clz((int)n);   // bits of the largest key (n, the root's)
+    const uint32_t seg = ((n + kFT - 1) / kFT) * 64;  // elements per wavefront, whole rounds
+    const int rounds = (int)(seg / 64);
+    const uint64_t below = lanemask_lt();
+    for (int sh = 0; sh < kbits; sh += kDigitBits) {
+      for (int i = tid; i < kCP * kFW; i += kFT) CNT[i] = 0;
+      __syncthreads();
+      uint32_t lr[kRoundsMax], dg[kRoundsMax];
+      uint16_t vv[kRoundsMax];
+#pragma unroll
+      for (int r = 0; r < kRoundsMax; ++r) {
+        if (r >= rounds) break;
+        const uint32_t idx = w * seg + r * 64 + lane;
+        const bool valid = idx < n;
+        const uint16_t v = valid ? src[idx] : (uint16_t)0;
+        const uint32_t d = valid ? ((uint32_t)root_key(P[v], n) >> sh) & (kDigits - 1) : 0u;
+        const uint64_t peers = match_digit(valid, d);
+        uint32_t old = 0;
+        if (valid) old = CNT[w * kCP + d];
+        if (valid && lane == __ffsll((unsigned long long)peers) - 1)
+          CNT[w * kCP + d] = old + (uint32_t)__popcll(peers);
+        lr[r] = old + (uint32_t)__popcll(peers & below);
+        dg[r] = d;
+        vv[r] = v;
+      }
+      __syncthreads();
+      // digit-major: digit d of wavefront w is number d * kFW + w in the scan
+      wg_scan_excl_at<kFT>(CNT, kDigits * kFW, SC + S_WSUM, [](int i) { return (i % kFW) * kCP + i / kFW; });
+#pragma unroll
+      for (int r = 0; r < kRoundsMax; ++r) {
+        if (r >= rounds) break;
+        const uint32_t idx = w * seg + r * 64 + lane;
+        if (idx < n) dst[CNT[w * kCP + dg[r]] + lr[r]] = vv[r];
+      }
+      __syncthreads();
+      uint16_t* tmp = src;
+      src = dst;
+      dst = tmp;
+    }
+    const uint16_t* ord = src;
+
+    // 3. successors; the root sorts last (position n-1)
+    for (uint32_t e = tid; e < E; e += kFT)
+      SUCC[e] = ((e >> 1) == root) ? kNoSucc : ((e & 1u) ? kEnd : (uint16_t)(e + 1));
+    __syncthreads();
+    for (uint32_t k = tid; k + 1 < n; k += kFT) {
+      const uint32_t c = ord[k];
+      const uint16_t p = P[c];
+      uint16_t nxt;
+      if (k + 2 < n && P[ord[k + 1]] == p) nxt = (uint16_t)(2 * ord[k + 1]);
+      else nxt = (p == root) ? kEnd : (uint16_t)(2 * p + 1);
+      SUCC[2 * c + 1] = nxt;
+      if (k == 0 || P[ord[k - 1]] != p) {
+        if (p == root) SC[S_HEAD] = (int32_t)(2 * c);
+        else SUCC[2 * p] = (uint16_t)(2 * c);
+      }
+    }
+    __syncthreads();
+    if (SC[S_HEAD] < 0) {  // the root has no child: the other nodes form cycles
+      if (tid == 0) {
+        flag(status, ST_UNREACHED);
+        SC[S_FAIL] = 1;
+      }
+    }
+    __syncthreads();
+  }
+
+  // 4. ranks and inclusive down counts of the half-edges
+  __device__ __forceinline__ void ranks(uint32_t n, uint32_t root, uint32_t* __restrict__ status) {
+    const uint32_t E = 2 * n;
+    // 4. sublists: both half-edges of every 2^m-th node id start one (so
+    // the runs down into and up out of a subtree both meet splitters),
+    // and so does the head; at most 1024 regular ones
+    const int m = max(0, clog2(n) - 9);
+    const uint32_t M = (1u << m) - 1u;
+    const uint32_t Sreg = 2 * ((n + M) >> m);
+    const uint32_t S = Sreg + 1;
+    const uint32_t head = (uint32_t)SC[S_HEAD];
+    const uint32_t hsub = ((head >> 1) & M) ? Sreg : (((head >> 1) >> m) << 1);
+    for (uint32_t s = tid; s < S; s += kFT) {
+      const uint32_t e0 = (s == Sreg) ? head : ((((s >> 1) << m) << 1) | (s & 1u));
+      const bool valid = (s == Sreg) ? ((head >> 1) & M) != 0 : (e0 < E && SUCC[e0] != kNoSucc);
+      uint32_t len = 0, dn = 0, nxs = kEnd;
+      if (valid) {
+        uint32_t e = e0;
+        for (;;) {
+          const uint32_t nx = SUCC[e];
+          SUCC[e] = (uint16_t)s;  // only this lane reads e's successor
+          if (e & 1u) {
+            R1[e >> 1] = (uint16_t)len;
+          } else {
+            R0[e >> 1] = (uint16_t)len;
+            D0[e >> 1] = (uint16_t)(dn + 1);
+          }
+          ++len;
+          dn += !(e & 1u);
+          if (nx == kEnd) break;
+          if (nx >= E || len >= E) {
+            SC[S_BAD] = 1;
+            break;
+          }
+          if (!((nx >> 1) & M)) {
+            nxs = (((nx >> 1) >> m) << 1) | (nx & 1u);
+            break;
+          }
+          e = nx;
+        }
+      }
+      NX(0)[s] = (uint16_t)nxs;
+      LD(0)[s] = (len << 16) | dn;
+    }
+    __syncthreads();
+    // suffix sums along the sublist list by pointer jumping
+    int cur = 0;
+    const int jumps = clog2(S) + 1;
+    for (int it = 0; it < jumps; ++it) {
+      for (uint32_t s = tid; s < S; s += kFT) {
+        const uint16_t nx = NX(cur)[s];
+        if (nx != kEnd && nx < S) {
+          NX(cur ^ 1)[s] = NX(cur)[nx];
+          LD(cur ^ 1)[s] = LD(cur)[s] + LD(cur)[nx];
+        } else {
+          NX(cur ^ 1)[s] = kEnd;
+          LD(cur ^ 1)[s] = LD(cur)[s];
+        }
+      }
+      __syncthreads();
+      cur ^= 1;
+    }
+    const uint32_t total = LD(cur)[hsub] >> 16, total_dn = LD(cur)[hsub] & 0xffffu;
+    if (tid == 0 && (SC[S_BAD] || total != E - 2)) {
+      flag(status, ST_UNREACHED);
+      SC[S_FAIL] = 1;
+    }
+    __syncthreads();
+    if (!SC[S_FAIL]) {
+      // each half-edge's rank and inclusive down count: its sublist's
+      // offset plus its value within the sublist
+      for (uint32_t c = tid; c < n; c += kFT) {
+        if (c == root) continue;
+        const uint32_t s0 = SUCC[2 * c], s1 = SUCC[2 * c + 1];
+        if (s0 >= S || s1 >= S) {  // not walked: cannot happen once the tour covers every half-edge
+          SC[S_BAD] = 1;
+          continue;
+        }
+        const uint32_t l0 = LD(cur)[s0];
+        R0[c] = (uint16_t)(R0[c] + total - (l0 >> 16));
+        D0[c] = (uint16_t)(D0[c] + total_dn - (l0 & 0xffffu));
+        R1[c] = (uint16_t)(R1[c] + total - (LD(cur)[s1] >> 16));
+      }
+    }
+    __syncthreads();
+    if (tid == 0 && SC[S_BAD] && !SC[S_FAIL]) {
+      flag(status, ST_UNREACHED);
+      SC[S_FAIL] = 1;
+    }
+    __syncthreads();
+  }
+
+  // 5. node statistics and inlabels; out(c, depth, pre, size) for every node c
+  // (no barrier: the ranks are still read)
+  template <typename Out>
+  __device__ __forceinline__ void stats(uint32_t n, uint32_t root, Out out) {
+    for (uint32_t c = tid; c < n; c += kFT) {  // (the sort buffers are dead)
+      int32_t dep, pre, size;
+      if (c == root) {
+        dep = 0;
+        pre = 0;
+        size = (int32_t)n;
+      } else {
+        const int32_t r0 = R0[c], d0 = D0[c], r1 = R1[c];
+        pre = d0;
+        dep = 2 * d0 - r0 - 1;
+        size = (r1 - r0 + 1) >> 1;
+      }
+      INL[c] = (uint16_t)inlabel_of(pre, size);
+      DEP[c] = (uint16_t)dep;
+      out(c, dep, pre, size);
+    }
+  }
+
+  // 5. path tops, parent path labels and ascendants (the ranks are dead: PLAB
+  // takes their place); no barrier at its end
+  __device__ __forceinline__ void labels(uint32_t n, uint32_t root) {
+    __syncthreads();
+    for (uint32_t I = tid; I <= n; I += kFT) PLAB[I] = kEnd;
+    __syncthreads();
+    // path tops: head[label] = {parent of the top, its depth}, plab = the parent's label
+    for (uint32_t v = tid; v < n; v += kFT) {
+      const uint16_t inl = INL[v];
+      const uint16_t p = P[v];
+      const bool is_root = v == root;
+      const uint16_t pinl = is_root ? (uint16_t)0 : INL[p];
+      if (is_root || pinl != inl) {
+        if (inl >= 1 && inl <= n) {
+          HEAD[inl] = (uint32_t)(is_root ? kEnd : p) | ((uint32_t)(uint16_t)(DEP[v] - 1) << 16);
+          PLAB[inl] = pinl;
+        } else {
+          SC[S_BAD] = 1;
+        }
+      }
+    }
+    __syncthreads();
+    // ascendant of each node: the level bits of the labels on its chain of
+    // parent path labels (levels strictly rise along it: at most 16 links)
+    for (uint32_t v = tid; v < n; v += kFT) {
+      uint32_t I = INL[v], acc = 0;
+      for (int k = 0; k < 16; ++k) {
+        if (I < 1 || I > n) {  // flagged where the labels were made
+          SC[S_BAD] = 1;
+          break;
+        }
+        const int lv = __ffs((int)I) - 1;
+        acc |= 1u << lv;
+        const uint32_t pl = PLAB[I];
+        if (pl == 0) break;  // the root's path
+        if (pl > n || (__ffs((int)pl) - 1) <= lv) {
+          SC[S_BAD] = 1;
+          break;
+        }
+        I = pl;
+      }
+      ASC[v] = (uint16_t)acc;
+    }
+  }
+};
+
 template <int kFT>
 __global__ __launch_bounds__(kFT, kFT == 1024 ? 8 : 1) void k_small_batch(
     const int32_t* __restrict__ parent, const int64_t* __restrict__ off, int32_t T, int64_t n_total, uint32_t N,
@@ -113,31 +429,12 @@ __global__ __launch_bounds__(kFT, kFT == 1024 ? 8 : 1) void k_small_batch(
     const int32_t* __restrict__ qy, int32_t* __restrict__ out, int32_t* __restrict__ depth_out,
     int32_t* __restrict__ pre_out, int32_t* __restrict__ size_out, const int32_t* __restrict__ order,
     uint32_t* __restrict__ counters, uint32_t* __restrict__ status) {
-  constexpr int kFW = kFT / 64;  // wavefronts per workgroup
-  static_assert(kFT * kRoundsMax >= kFSmall && kFW <= kWavesMax, "a lane holds at most kRoundsMax nodes");
   extern __shared__ __align__(16) unsigned char lds[];
-  const SmallLayout L = small_layout(N);
-  uint16_t* P = reinterpret_cast<uint16_t*>(lds + L.p);
-  uint16_t* SUCC = reinterpret_cast<uint16_t*>(lds + L.rb);
-  uint32_t* HEAD = reinterpret_cast<uint32_t*>(lds + L.rb);
-  uint32_t* CNT = reinterpret_cast<uint32_t*>(lds + L.rc);
-  uint16_t* R0 = reinterpret_cast<uint16_t*>(lds + L.rc);  // rank of 2c
-  uint16_t* R1 = R0 + N;                                     // rank of 2c + 1
-  uint16_t* D0 = R0 + 2 * N;                                 // down count through 2c
-  uint16_t* PLAB = reinterpret_cast<uint16_t*>(lds + L.rc);
-  uint16_t* ORD0 = reinterpret_cast<uint16_t*>(lds + L.rd);
-  uint16_t* ORD1 = ORD0 + N;
-  uint16_t* INL = reinterpret_cast<uint16_t*>(lds + L.rd);
-  uint16_t* ASC = INL + N;
-  uint16_t* DEP = ASC + N;
-  // sublist next, and length << 16 | down count (both below 2^16, so one
-  // 32-bit add sums both), two buffers each (pointer jumping)
-  uint16_t* SUB = reinterpret_cast<uint16_t*>(lds + L.rf);
-  uint32_t* LDa = reinterpret_cast<uint32_t*>(lds + L.rf + 4 * kSubMax);
-#define NX(b) (SUB + (b) * kSubMax)
-#define LD(b) (LDa + (b) * kSubMax)
-  int32_t* SC = reinterpret_cast<int32_t*>(lds + L.sc);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  SmallTree<kFT> tr(lds, N);
+  const uint16_t *INL = tr.INL, *ASC = tr.ASC, *DEP = tr.DEP;
+  const uint32_t* HEAD = tr.HEAD;
+  int32_t* SC = tr.SC;
+  const int tid = threadIdx.x;
 
   if (blockIdx.x == 0 && tid == 0) {
     if (off[0] != 0 || off[T] != n_total) flag(status, ST_BAD_PARENT);
@@ -159,268 +456,18 @@ __global__ __launch_bounds__(kFT, kFT == 1024 ? 8 : 1) void k_small_batch(
     if (!tree_ok && tid == 0) flag(status, ST_BAD_PARENT);
     const uint32_t n = tree_ok ? (uint32_t)nt : 0u;
 
-    // 1. parents
-    if (tid == 0) {
-      SC[S_NROOTS] = 0;
-      SC[S_BAD] = 0;
-      SC[S_FAIL] = tree_ok ? 0 : 1;
-      SC[S_HEAD] = -1;
-    }
-    __syncthreads();
-    int32_t praw[kRoundsMax];  // all of a lane's parent loads first
-#pragma unroll
-    for (int r = 0; r < kRoundsMax; ++r) {
-      const uint32_t c = tid + r * kFT;
-      praw[r] = c < n ? parent[base + c] : 0;
-    }
-#pragma unroll
-    for (int r = 0; r < kRoundsMax; ++r) {
-      const uint32_t c = tid + r * kFT;
-      if (c >= n) break;
-      const int32_t p = praw[r];
-      if (p == -1) {
-        P[c] = kEnd;
-        atomicAdd(&SC[S_NROOTS], 1);
-        SC[S_ROOT] = (int32_t)c;
-      } else if (p >= 0 && (uint32_t)p < n && (uint32_t)p != c) {
-        P[c] = (uint16_t)p;
-      } else {
-        P[c] = 0;
-        SC[S_BAD] = 1;
-      }
-    }
-    __syncthreads();
-    if (tree_ok && (SC[S_NROOTS] != 1 || SC[S_BAD])) {
-      if (tid == 0) {
-        flag(status, SC[S_BAD] ? ST_BAD_PARENT : ST_ROOTS);
-        SC[S_FAIL] = 1;
-      }
-    }
-    __syncthreads();
+    tr.begin(tree_ok);
+    tr.parents(parent + base, n, tree_ok, status);
     const uint32_t root = (uint32_t)SC[S_ROOT];
-    const uint32_t E = 2 * n;
-
-    if (!SC[S_FAIL] && n > 1) {
-      // 2. stable radix sort of child ids by parent id
-      for (uint32_t i = tid; i < n; i += kFT) ORD0[i] = (uint16_t)i;
-      uint16_t* src = ORD0;
-      uint16_t* dst = ORD1;
-      const int kbits = 32 - __clz((int)n);   // bits of the largest key (n, the root's)
-      const uint32_t seg = ((n + kFT - 1) / kFT) * 64;  // elements per wavefront, whole rounds
-      const int rounds = (int)(seg / 64);
-      const uint64_t below = lanemask_lt();
-      for (int sh = 0; sh < kbits; sh += kDigitBits) {
-        for (int i = tid; i < kCP * kFW; i += kFT) CNT[i] = 0;
-        __syncthreads();
-        uint32_t lr[kRoundsMax], dg[kRoundsMax];
-        uint16_t vv[kRoundsMax];
-#pragma unroll
-        for (int r = 0; r < kRoundsMax; ++r) {
-          if (r >= rounds) break;
-          const uint32_t idx = w * seg + r * 64 + lane;
-          const bool valid = idx < n;
-          const uint16_t v = valid ? src[idx] : (uint16_t)0;
-          const uint32_t d = valid ? ((uint32_t)root_key(P[v], n) >> sh) & (kDigits - 1) : 0u;
-          const uint64_t peers = match_digit(valid, d);
-          uint32_t old = 0;
-          if (valid) old = CNT[w * kCP + d];
-          if (valid && lane == __ffsll((unsigned long long)peers) - 1)
-            CNT[w * kCP + d] = old + (uint32_t)__popcll(peers);
-          lr[r] = old + (uint32_t)__popcll(peers & below);
-          dg[r] = d;
-          vv[r] = v;
-        }
-        __syncthreads();
-        // digit-major: digit d of wavefront w is number d * kFW + w in the scan
-        wg_scan_excl_at<kFT>(CNT, kDigits * kFW, SC + S_WSUM, [](int i) { return (i % kFW) * kCP + i / kFW; });
-#pragma unroll
-        for (int r = 0; r < kRoundsMax; ++r) {
-          if (r >= rounds) break;
-          const uint32_t idx = w * seg + r * 64 + lane;
-          if (idx < n) dst[CNT[w * kCP + dg[r]] + lr[r]] = vv[r];
-        }
-        __syncthreads();
-        uint16_t* tmp = src;
-        src = dst;
-        dst = tmp;
-      }
-      const uint16_t* ord = src;
-
-      // 3. successors; the root sorts last (position n-1)
-      for (uint32_t e = tid; e < E; e += kFT)
-        SUCC[e] = ((e >> 1) == root) ? kNoSucc : ((e & 1u) ? kEnd : (uint16_t)(e + 1));
-      __syncthreads();
-      for (uint32_t k = tid; k + 1 < n; k += kFT) {
-        const uint32_t c = ord[k];
-        const uint16_t p = P[c];
-        uint16_t nxt;
-        if (k + 2 < n && P[ord[k + 1]] == p) nxt = (uint16_t)(2 * ord[k + 1]);
-        else nxt = (p == root) ? kEnd : (uint16_t)(2 * p + 1);
-        SUCC[2 * c + 1] = nxt;
-        if (k == 0 || P[ord[k - 1]] != p) {
-          if (p == root) SC[S_HEAD] = (int32_t)(2 * c);
-          else SUCC[2 * p] = (uint16_t)(2 * c);
-        }
-      }
-      __syncthreads();
-      if (SC[S_HEAD] < 0) {  // the root has no child: the other nodes form cycles
-        if (tid == 0) {
-          flag(status, ST_UNREACHED);
-          SC[S_FAIL] = 1;
-        }
-      }
-      __syncthreads();
-    }
-    if (!SC[S_FAIL] && n > 1) {
-      // 4. sublists: both half-edges of every 2^m-th node id start one (so
-      // the runs down into and up out of a subtree both meet splitters),
-      // and so does the head; at most 1024 regular ones
-      const int m = max(0, clog2(n) - 9);
-      const uint32_t M = (1u << m) - 1u;
-      const uint32_t Sreg = 2 * ((n + M) >> m);
-      const uint32_t S = Sreg + 1;
-      const uint32_t head = (uint32_t)SC[S_HEAD];
-      const uint32_t hsub = ((head >> 1) & M) ? Sreg : (((head >> 1) >> m) << 1);
-      for (uint32_t s = tid; s < S; s += kFT) {
-        const uint32_t e0 = (s == Sreg) ? head : ((((s >> 1) << m) << 1) | (s & 1u));
-        const bool valid = (s == Sreg) ? ((head >> 1) & M) != 0 : (e0 < E && SUCC[e0] != kNoSucc);
-        uint32_t len = 0, dn = 0, nxs = kEnd;
-        if (valid) {
-          uint32_t e = e0;
-          for (;;) {
-            const uint32_t nx = SUCC[e];
-            SUCC[e] = (uint16_t)s;  // only this lane reads e's successor
-            if (e & 1u) {
-              R1[e >> 1] = (uint16_t)len;
-            } else {
-              R0[e >> 1] = (uint16_t)len;
-              D0[e >> 1] = (uint16_t)(dn + 1);
-            }
-            ++len;
-            dn += !(e & 1u);
-            if (nx == kEnd) break;
-            if (nx >= E || len >= E) {
-              SC[S_BAD] = 1;
-              break;
-            }
-            if (!((nx >> 1) & M)) {
-              nxs = (((nx >> 1) >> m) << 1) | (nx & 1u);
-              break;
-            }
-            e = nx;
-          }
-        }
-        NX(0)[s] = (uint16_t)nxs;
-        LD(0)[s] = (len << 16) | dn;
-      }
-      __syncthreads();
-      // suffix sums along the sublist list by pointer jumping
-      int cur = 0;
-      const int jumps = clog2(S) + 1;
-      for (int it = 0; it < jumps; ++it) {
-        for (uint32_t s = tid; s < S; s += kFT) {
-          const uint16_t nx = NX(cur)[s];
-          if (nx != kEnd && nx < S) {
-            NX(cur ^ 1)[s] = NX(cur)[nx];
-            LD(cur ^ 1)[s] = LD(cur)[s] + LD(cur)[nx];
-          } else {
-            NX(cur ^ 1)[s] = kEnd;
-            LD(cur ^ 1)[s] = LD(cur)[s];
-          }
-        }
-        __syncthreads();
-        cur ^= 1;
-      }
-      const uint32_t total = LD(cur)[hsub] >> 16, total_dn = LD(cur)[hsub] & 0xffffu;
-      if (tid == 0 && (SC[S_BAD] || total != E - 2)) {
-        flag(status, ST_UNREACHED);
-        SC[S_FAIL] = 1;
-      }
-      __syncthreads();
-      if (!SC[S_FAIL]) {
-        // each half-edge's rank and inclusive down count: its sublist's
-        // offset plus its value within the sublist
-        for (uint32_t c = tid; c < n; c += kFT) {
-          if (c == root) continue;
-          const uint32_t s0 = SUCC[2 * c], s1 = SUCC[2 * c + 1];
-          if (s0 >= S || s1 >= S) {  // not walked: cannot happen once the tour covers every half-edge
-            SC[S_BAD] = 1;
-            continue;
-          }
-          const uint32_t l0 = LD(cur)[s0];
-          R0[c] = (uint16_t)(R0[c] + total - (l0 >> 16));
-          D0[c] = (uint16_t)(D0[c] + total_dn - (l0 & 0xffffu));
-          R1[c] = (uint16_t)(R1[c] + total - (LD(cur)[s1] >> 16));
-        }
-      }
-      __syncthreads();
-      if (tid == 0 && SC[S_BAD] && !SC[S_FAIL]) {
-        flag(status, ST_UNREACHED);
-        SC[S_FAIL] = 1;
-      }
-      __syncthreads();
-    }
-
+    if (!SC[S_FAIL] && n > 1) tr.tour(n, root, status);
+    if (!SC[S_FAIL] && n > 1) tr.ranks(n, root, status);
     if (!SC[S_FAIL]) {
-      // 5. node statistics and inlabels (RD's sort buffers are dead)
-      for (uint32_t c = tid; c < n; c += kFT) {
-        int32_t dep, pre, size;
-        if (c == root) {
-          dep = 0;
-          pre = 0;
-          size = (int32_t)n;
-        } else {
-          const int32_t r0 = R0[c], d0 = D0[c], r1 = R1[c];
-          pre = d0;
-          dep = 2 * d0 - r0 - 1;
-          size = (r1 - r0 + 1) >> 1;
-        }
-        INL[c] = (uint16_t)inlabel_of(pre, size);
-        DEP[c] = (uint16_t)dep;
+      tr.stats(n, root, [&](uint32_t c, int32_t dep, int32_t pre, int32_t size) {
         if (depth_out) depth_out[base + c] = dep;
         if (pre_out) pre_out[base + c] = pre;
         if (size_out) size_out[base + c] = size;
-      }
-      __syncthreads();  // the ranks are dead from here: PLAB takes RC
-      for (uint32_t I = tid; I <= n; I += kFT) PLAB[I] = kEnd;
-      __syncthreads();
-      // path tops: head[label] = {parent of the top, its depth}, plab = the parent's label
-      for (uint32_t v = tid; v < n; v += kFT) {
-        const uint16_t inl = INL[v];
-        const uint16_t p = P[v];
-        const bool is_root = v == root;
-        const uint16_t pinl = is_root ? (uint16_t)0 : INL[p];
-        if (is_root || pinl != inl) {
-          if (inl >= 1 && inl <= n) {
-            HEAD[inl] = (uint32_t)(is_root ? kEnd : p) | ((uint32_t)(uint16_t)(DEP[v] - 1) << 16);
-            PLAB[inl] = pinl;
-          } else {
-            SC[S_BAD] = 1;
-          }
-        }
-      }
-      __syncthreads();
-      // ascendant of each node: the level bits of the labels on its chain of
-      // parent path labels (levels strictly rise along it: at most 16 links)
-      for (uint32_t v = tid; v < n; v += kFT) {
-        uint32_t I = INL[v], acc = 0;
-        for (int k = 0; k < 16; ++k) {
-          if (I < 1 || I > n) {  // flagged where the labels were made
-            SC[S_BAD] = 1;
-            break;
-          }
-          const int lv = __ffs((int)I) - 1;
-          acc |= 1u << lv;
-          const uint32_t pl = PLAB[I];
-          if (pl == 0) break;  // the root's path
-          if (pl > n || (__ffs((int)pl) - 1) <= lv) {
-            SC[S_BAD] = 1;
-            break;
-          }
-          I = pl;
-        }
-        ASC[v] = (uint16_t)acc;
-      }
+      });
+      tr.labels(n, root);
       __syncthreads();
       if (tid == 0 && SC[S_BAD]) flag(status, ST_BAD_INDEX);
     }
@@ -492,8 +539,68 @@ __global__ __launch_bounds__(kFT, kFT == 1024 ? 8 : 1) void k_small_batch(
       atomicExch(&counters[1], 0u);
     }
   }
-#undef NX
-#undef LD
+}
+
+// One tree of 2 to 4096 nodes built into its tables by one workgroup: the
+// same steps, with everything a multi-kernel build keeps written out. There a
+// build of that size is bound by its launches (about 17, each waiting for the
+// one before): build and 1000 queries took 43 us at 256 nodes, 54 at 1000, 73
+// at 3000 and 76 at 4096; here 20, 21, 45 and 55 (20 is what the host needs
+// for the two calls). 256 lanes instead of 1024 are no faster at 256 nodes and
+// 39 us at 1000.
+// On malformed input the tables hold values that no later call trips over.
+constexpr int kTreeLanes = 1024;
+
+__global__ __launch_bounds__(kTreeLanes) void k_small_tree(
+    const int32_t* __restrict__ parent, uint32_t n, uint32_t N, int32_t* __restrict__ root_out,
+    int32_t* __restrict__ succ, int32_t* __restrict__ rank, int32_t* pre_out, int32_t* __restrict__ size_out,
+    int4* __restrict__ rec, int2* __restrict__ head, uint32_t* __restrict__ status) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  SmallTree<kTreeLanes> tr(lds, N);
+  const int tid = threadIdx.x;
+  tr.begin(true);
+  tr.parents(parent, n, true, status);
+  const uint32_t root = (uint32_t)tr.SC[S_ROOT];
+  if (!tr.SC[S_FAIL]) {
+    tr.tour(n, root, status);
+    for (uint32_t e = tid; e < 2 * n; e += kTreeLanes) {
+      const uint16_t x = tr.SUCC[e];
+      succ[e] = x == kEnd ? -1 : x == kNoSucc ? -2 : (int32_t)x;
+    }
+    __syncthreads();  // the ranking writes over the successors
+  }
+  if (!tr.SC[S_FAIL]) tr.ranks(n, root, status);
+  if (tr.SC[S_FAIL]) {
+    for (uint32_t c = tid; c < n; c += kTreeLanes) {
+      reinterpret_cast<int2*>(succ)[c] = make_int2(-2, -2);
+      reinterpret_cast<int2*>(rank)[c] = make_int2(-1, -1);
+      pre_out[c] = 0;
+      size_out[c] = 1;
+      rec[c] = make_int4(1, 1, 0, 0);
+      head[c + 1] = make_int2(-1, -1);
+    }
+    if (tid == 0) root_out[0] = -1;
+    return;
+  }
+  tr.stats(n, root, [&](uint32_t c, int32_t, int32_t pre, int32_t size) {
+    reinterpret_cast<int2*>(rank)[c] =
+        c == root ? make_int2(-1, -1) : make_int2((int32_t)tr.R0[c], (int32_t)tr.R1[c]);
+    pre_out[c] = pre;
+    size_out[c] = size;
+  });
+  tr.labels(n, root);
+  for (uint32_t c = tid; c < n; c += kTreeLanes)  // (the lane's own ascendants and preorders)
+    rec[c] = make_int4((int32_t)tr.INL[c], (int32_t)tr.ASC[c], (int32_t)tr.DEP[c], pre_out[c]);
+  for (uint32_t I = tid + 1; I <= n; I += kTreeLanes) {
+    if (tr.PLAB[I] == kEnd) continue;  // no path has this label
+    const uint32_t h = tr.HEAD[I];
+    head[I] = make_int2((h & 0xffffu) == kEnd ? -1 : (int32_t)(h & 0xffffu), (int32_t)(int16_t)(h >> 16));
+  }
+  __syncthreads();
+  if (tid == 0) {
+    root_out[0] = (int32_t)root;
+    if (tr.SC[S_BAD]) flag(status, ST_BAD_INDEX);
+  }
 }
 
 }  // namespace
@@ -501,6 +608,21 @@ __global__ __launch_bounds__(kFT, kFT == 1024 ? 8 : 1) void k_small_batch(
 size_t small_batch_lds_bytes(int32_t max_nodes) {
   const uint32_t N = al64((uint32_t)std::max(max_nodes, 1));
   return small_layout(N).total;
+}
+
+int small_tree_prepare() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(k_small_tree), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)small_layout(kFMax).total) == hipSuccess
+             ? ET_OK
+             : ET_EHIP;
+}
+
+int small_tree_build(Ctx* c, et_tree* t, const int32_t* parent, hipStream_t s) {
+  const uint32_t n = (uint32_t)t->n, N = al64(n);
+  ET_PROF(c, s, "k_small_tree");
+  hipLaunchKernelGGL(k_small_tree, dim3(1), dim3(kTreeLanes), small_layout(N).total, s, parent, n, N, t->d_root,
+                     t->d_succ, t->d_rank, t->d_pre, t->d_size, t->d_rec, t->d_head, c->d_status);
+  return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 }
 
 int small_batch_run(Ctx* c, const int32_t* parent, const int64_t* off, int32_t T, int64_t n_total,

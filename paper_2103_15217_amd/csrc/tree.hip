@@ -498,6 +498,7 @@ int tree_build(Ctx* c, et_tree* t, const int32_t* parent, hipStream_t s) {
                        t->d_rec, t->d_head, c->d_status);
     return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
   }
+  if (n <= kSmallTreeMax) return small_tree_build(c, t, parent, s);
   const int32_t L2 = 2 * n;          // half-edge id space (the tour uses 2(n-1) of them)
   Scratch scr(c, s);
   uint32_t* kv = scr.get<uint32_t>((size_t)L2 + 2);  // sorted parents | children, later the two tables by label
