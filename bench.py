@@ -416,11 +416,11 @@ def query_engines(args, et, ctx, d, d_parent, d_qx, d_qy, grasps):
 BRIDGE_PHASES = {
     "spanning forest": ("k_forest_init", "k_hook_sample", "k_cc_compress", "k_big_component", "k_hook_rest"),
     "BFS": ("k_bfs_level", "k_bfs_slots"),
-    "Euler tour": ("k_link_in", "k_roots", "k_chain", "k_forest_succ", "k_root_rank", "k_root_preorder",
+    "Euler tour": ("k_link_in", "k_roots", "k_chain", "k_forest_succ",
                    "k_walk1<false>", "k_walkN", "k_final_lds", "k_final_walk", "k_push_down", "k_check_reached",
                    "k_rank_fix", "k_count_used", "k_direction", "k_preorder", "k_hybrid_nodes"),
     "marking": ("k_ck_mark", "k_ck_out"),
-    "low/high + test": ("k_minmax", "k_rmq_blocks", "k_sparse_level", "k_bridge_test"),
+    "low/high + test": ("k_minmax", "k_rmq_blocks", "k_sparse_levels", "k_bridge_test"),
 }
 
 

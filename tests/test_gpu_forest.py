@@ -58,6 +58,13 @@ GRAPHS = {
     "zigzag": lambda: _zigzag(4099), "two": lambda: gen.csr_from_pairs(2, [0], [1]),
     "loop_only": lambda: gen.csr_from_pairs(3, [1], [1]),
     "random": lambda: gen.random_multigraph(4097, 6000, seed=3),
+    # both sides of the sampling rule, and block counts at the sparse table's steps
+    "sparse_66000": lambda: gen.random_multigraph(66000, 150000, seed=4),
+    "dense_66000": lambda: gen.random_multigraph(66000, 400000, seed=5),
+    "slots_2to14": lambda: gen.random_multigraph(3000, 1 << 13, seed=6),
+    "slots_more": lambda: gen.random_multigraph(3000, (1 << 13) + 1, seed=7),
+    "blocks_64": lambda: gen.random_multigraph(2048, 2300, seed=8),
+    "blocks_129": lambda: gen.random_multigraph(4100, 5000, seed=9),
 }
 
 
