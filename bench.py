@@ -418,7 +418,7 @@ BRIDGE_PHASES = {
     "BFS": ("k_bfs_level", "k_bfs_slots"),
     "Euler tour": ("k_link_in", "k_roots", "k_chain", "k_forest_succ",
                    "k_walk1<false>", "k_walkN", "k_final_lds", "k_final_walk", "k_push_down", "k_check_reached",
-                   "k_rank_fix", "k_count_used", "k_direction", "k_preorder", "k_hybrid_nodes"),
+                   "k_rank_fix", "k_rank_lds", "k_direction", "k_preorder", "k_hybrid_nodes"),
     "marking": ("k_ck_mark", "k_ck_out"),
     "low/high + test": ("k_minmax", "k_rmq_blocks", "k_sparse_levels", "k_bridge_test"),
 }

@@ -447,13 +447,13 @@ __global__ void k_forest_succ(const int32_t* __restrict__ cc, const int4* __rest
   pre[e] = -1;
 }
 
-__device__ __forceinline__ int32_t rank_at(uint64_t pk, const int2* __restrict__ off, int32_t nsub, bool* bad) {
+__device__ __forceinline__ int32_t rank_at(uint64_t pk, OffWord off, int32_t nsub, bool* bad) {
   uint32_t s = (uint32_t)pk;
   if (s >= (uint32_t)nsub) {
     *bad = true;
     s = 0;
   }
-  return off[s].x + (int32_t)((pk >> 32) & 0xffffu);
+  return off.at(s) + (int32_t)((pk >> 32) & 0xffffu);
 }
 
 // Per forest edge: the rank of its half-edge that goes down (the earlier
@@ -468,7 +468,7 @@ __device__ __forceinline__ int32_t rank_at(uint64_t pk, const int2* __restrict__
 // so it puts a weight 1 on the half-edge before its start (the last one of the
 // component before it, which goes up), the first component none.
 template <bool HYBRID>
-__global__ void k_direction(const uint64_t* __restrict__ packed, const int2* __restrict__ off, int32_t nsub,
+__global__ void k_direction(const uint64_t* __restrict__ packed, OffWord off, int32_t nsub,
                             const int32_t* __restrict__ cc, const int32_t* __restrict__ first,
                             const int4* __restrict__ erec, int32_t n, const int32_t* __restrict__ sc,
                             int2* __restrict__ ds, uint32_t* __restrict__ dw, uint32_t* __restrict__ status) {
@@ -1031,7 +1031,7 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
   {
     ET_PROF(c, s, "k_direction");
     const auto kern = algo == kAlgoHybrid ? k_direction<true> : k_direction<false>;
-    hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, lr.packed, lr.off, lr.nsub, cc, first, erec, n, scal,
+    hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, lr.packed, lr.word, lr.nsub, cc, first, erec, n, scal,
                        ds, dw, c->d_status);
   }
   if (algo == kAlgoHybrid) {

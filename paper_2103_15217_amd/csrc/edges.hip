@@ -88,7 +88,7 @@ __global__ void k_dcel_succ(const int32_t* __restrict__ B, const uint32_t* __res
   succ[h ^ 1] = (nxt == sc[SC_HEAD]) ? -1 : nxt;
 }
 
-__global__ void k_ranks(const uint64_t* __restrict__ packed, const int2* __restrict__ off, int32_t nsub, int32_t L,
+__global__ void k_ranks(const uint64_t* __restrict__ packed, OffWord off, int32_t nsub, int32_t L,
                         int32_t* __restrict__ rank, uint32_t* __restrict__ status) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (h >= L) return;
@@ -98,7 +98,7 @@ __global__ void k_ranks(const uint64_t* __restrict__ packed, const int2* __restr
     flag(status, ST_BAD_INDEX);
     sub = 0;
   }
-  rank[h] = off[sub].x + (int32_t)((p >> 32) & 0xffffu);
+  rank[h] = off.at(sub) + (int32_t)((p >> 32) & 0xffffu);
 }
 
 // per edge: the half-edge that goes down, its child's record
@@ -228,7 +228,7 @@ int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, i
   uint32_t* dw = key;  // the sort keys are dead: down flags in tour order, then their scan
   {
     ET_PROF(c, s, "phase:nodes");
-    hipLaunchKernelGGL(k_ranks, dim3(gl), dim3(kB), 0, s, lr.packed, lr.off, lr.nsub, L, t->d_rank, c->d_status);
+    hipLaunchKernelGGL(k_ranks, dim3(gl), dim3(kB), 0, s, lr.packed, lr.word, lr.nsub, L, t->d_rank, c->d_status);
     hipLaunchKernelGGL(k_fill, dim3(std::min(gl, 8192)), dim3(kB), 0, s, reinterpret_cast<int32_t*>(dw),
                        (int64_t)L, 0);
     hipLaunchKernelGGL(k_fill, dim3(std::min(4 * (int64_t)gn, (int64_t)8192)), dim3(kB), 0, s,

@@ -299,10 +299,17 @@ int group_by_parent_impl(Ctx* c, const int32_t* parent, int32_t n, uint32_t* key
                          int32_t* vals_out, int32_t* succ, int32_t* scalars, hipStream_t s);
 
 // listrank.hip
+// one word of every entry of a table of words (sh 0) or of word pairs (sh 1)
+struct OffWord {
+  const int32_t* p = nullptr;
+  int sh = 0;
+  __device__ __forceinline__ int32_t at(uint32_t i) const { return p[(size_t)i << sh]; }
+};
 struct LRResult {
   // level-1 sublist decomposition, valid after list_rank_core
   uint64_t* packed = nullptr;  // per element: sublist id | local rank << 32 | inclusive local down << 48
   int2* off = nullptr;         // per level-1 sublist: {rank of its first element, down-count before it}
+  OffWord word;                // plain ranking: the ranks alone; weighted 1: the sums alone (off may not hold pairs then)
   int32_t nsub = 0;            // number of level-1 sublist slots
 };
 // tree_weights: element e counts as "down" iff e is even (tree half-edges).

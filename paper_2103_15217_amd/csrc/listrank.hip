@@ -54,13 +54,14 @@ __global__ void k_set_scalar(int32_t* __restrict__ p, int32_t v) { *p = v; }
 __device__ __forceinline__ int32_t wadd(int32_t a, int32_t b) { return (int32_t)((uint32_t)a + (uint32_t)b); }
 __device__ __forceinline__ int32_t wsub(int32_t a, int32_t b) { return (int32_t)((uint32_t)a - (uint32_t)b); }
 
-// start of a ranking: the continuation counter and the reached-element
-// count at zero, the continuation records [begin, end) marked unused
+// start of a ranking: the continuation counter and the counts of reached and
+// of used elements at zero, the continuation records [begin, end) marked unused
 __global__ void k_lr_init(int32_t* __restrict__ ctr, int4* __restrict__ rec, int32_t begin, int32_t end) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) {
     ctr[0] = 0;
     ctr[1] = 0;
+    ctr[2] = 0;
   }
   if (begin + i < end) rec[begin + i] = make_int4(-3, 0, 0, 0);
 }
@@ -347,7 +348,8 @@ template <int IN>
 __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
     const int32_t* __restrict__ in, int32_t T, const int32_t* __restrict__ heads, int32_t hb, int32_t H,
     bool empty_ok, int ks, uint32_t salt, uint64_t* __restrict__ packed, int2* __restrict__ off,
-    int32_t* __restrict__ rank, const int32_t* __restrict__ expected, uint32_t* __restrict__ status) {
+    int32_t* __restrict__ rank, int32_t* __restrict__ reached_out, const int32_t* __restrict__ expected,
+    uint32_t* __restrict__ status) {
   // NXT: the next element, kEnd or kUnused, kSplit set if the next element is
   // a splitter (decided here, not in the dependent walk); kWalked | sublist
   // once walked
@@ -526,6 +528,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
   for (int dd = 32; dd >= 1; dd >>= 1) mine += __shfl_xor(mine, dd, 64);
   if (__lane_id() == 0 && mine) atomicAdd(&HB[hw], (uint32_t)mine);  // (the slot after the bits)
   __syncthreads();
+  if (t == 0 && reached_out) *reached_out = (int32_t)HB[hw];
   bool unreached = t == 0 && expected && (int32_t)HB[hw] != *expected;
 #pragma unroll 4
   for (int32_t e = t; e < T; e += kFinalThreads) {
@@ -667,21 +670,28 @@ __global__ void k_check_reached(const int32_t* __restrict__ reached, const int32
   if (expected && *reached != *expected) flag(status, ST_UNREACHED);
 }
 
-// off_k[e] = off_{k+1}[el[e].sub] + (el[e].len, el[e].down) for used elements
+// off_k[e] = off_{k+1}[el[e].sub] + (el[e].len, el[e].down) for used elements.
+// CH 1 / 2: store the first / second word alone, compact. The elements gather
+// these offsets at random, and a plain ranking needs only the lengths, a scan
+// without ranks only the sums: half the table, a faster gather (k_rank_fix at
+// 2^25 elements, 2^21 sublists: 16 -> 8 MiB, 473 -> 365 us).
+template <int CH>
 __global__ void k_push_down(const int4* __restrict__ rec, const int4* __restrict__ el, int32_t T,
-                            const int2* __restrict__ off_up, int32_t T_up, int2* __restrict__ off,
+                            const int2* __restrict__ off_up, int32_t T_up, void* __restrict__ off,
                             uint32_t* __restrict__ status) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= T) return;
   if (rec[e].x == -3) return;
   const int4 x = el[e];
+  int2 v = make_int2(0, 0);
   if ((uint32_t)x.x >= (uint32_t)T_up) {
     flag(status, ST_BAD_INDEX);
-    off[e] = make_int2(0, 0);
-    return;
+  } else {
+    const int2 o = off_up[x.x];
+    v = make_int2(o.x + x.y, wadd(o.y, x.z));
   }
-  const int2 o = off_up[x.x];
-  off[e] = make_int2(o.x + x.y, wadd(o.y, x.z));
+  if (CH == 0) static_cast<int2*>(off)[e] = v;
+  else static_cast<int32_t*>(off)[e] = CH == 1 ? v.x : v.y;
 }
 
 // weighted list prefix sums: sum[e] = the weight sum before e's sublist +
@@ -689,7 +699,7 @@ __global__ void k_push_down(const int4* __restrict__ rec, const int4* __restrict
 // records). Unused slots get rank -1 and sum 0.
 template <bool RANK>
 __global__ void k_scan_fix(const int2* __restrict__ sw, const uint64_t* __restrict__ packed, int32_t L,
-                           const int2* __restrict__ off, int32_t T1, int32_t* __restrict__ rank,
+                           const int2* __restrict__ off, OffWord offw, int32_t T1, int32_t* __restrict__ rank,
                            int32_t* __restrict__ sum, uint32_t* __restrict__ status) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= L) return;
@@ -715,44 +725,64 @@ __global__ void k_scan_fix(const int2* __restrict__ sw, const uint64_t* __restri
     sum[e] = 0;
     return;
   }
-  const int2 o = off[sub];
-  if (RANK) rank[e] = o.x + (int32_t)lrank;
-  sum[e] = wadd(o.y, (int32_t)lsum);
+  if (RANK) {
+    const int2 o = off[sub];
+    rank[e] = o.x + (int32_t)lrank;
+    sum[e] = wadd(o.y, (int32_t)lsum);
+  } else {
+    sum[e] = wadd(offw.at(sub), (int32_t)lsum);
+  }
 }
 
-// generic rank: rank[e] = off[sub] + local rank, -1 for unused slots
-__global__ void k_rank_fix(const int32_t* __restrict__ succ, const uint64_t* __restrict__ packed, int32_t L,
-                           const int2* __restrict__ off, int32_t T1, int32_t* __restrict__ rank,
-                           uint32_t* __restrict__ status) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= L) return;
-  if (succ[e] == -2) {
-    rank[e] = -1;
-    return;
-  }
-  const uint64_t p = packed[e];
-  const uint32_t sub = (uint32_t)p;
-  if (sub >= (uint32_t)T1) {
-    flag(status, ST_BAD_INDEX);
-    rank[e] = -1;
-    return;
-  }
-  rank[e] = off[sub].x + (int32_t)((p >> 32) & 0xffffu);
-}
+// generic rank: rank[e] = off[sub] + local rank, -1 for unused slots. Counts
+// the used elements on the way (a pass of its own over the successors took 57
+// us at 2^25 elements), a workgroup per 256 * per elements so that the counter
+// sees few updates; kFixTogether of a lane's loads go together. Bound by the
+// gathered offsets.
+constexpr int kFixTogether = 4;
 
-__global__ void k_count_used(const int32_t* __restrict__ succ, int32_t L, int32_t* __restrict__ count) {
+__global__ __launch_bounds__(256) void k_rank_fix(const int32_t* __restrict__ succ, const uint64_t* __restrict__ packed,
+                                                  int32_t L, int per, OffWord off, int32_t T1,
+                                                  int32_t* __restrict__ rank, int32_t* __restrict__ used,
+                                                  uint32_t* __restrict__ status) {
   __shared__ int32_t part[4];
-  int32_t c = 0;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < L; e += (int64_t)gridDim.x * blockDim.x)
-    c += (succ[e] != -2);
-  for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
-  if (__lane_id() == 0) part[threadIdx.x >> 6] = c;
+  constexpr int kTogether = kFixTogether;
+  const int64_t base = (int64_t)blockIdx.x * (256 * per) + threadIdx.x;
+  int32_t count = 0;
+  bool bad = false;
+  for (int r0 = 0; r0 < per; r0 += kTogether) {
+    int32_t nx[kTogether], v[kTogether];
+    uint64_t pk[kTogether];
+#pragma unroll
+    for (int r = 0; r < kTogether; ++r) {
+      const int64_t e = base + (int64_t)(r0 + r) * 256;
+      nx[r] = e < L ? succ[e] : -2;
+      pk[r] = e < L ? packed[e] : 0ull;
+    }
+#pragma unroll
+    for (int r = 0; r < kTogether; ++r) {
+      v[r] = -1;
+      if (nx[r] == -2) continue;
+      ++count;
+      const uint32_t sub = (uint32_t)pk[r];
+      if (sub >= (uint32_t)T1) bad = true;
+      else v[r] = off.at(sub) + (int32_t)((pk[r] >> 32) & 0xffffu);
+    }
+#pragma unroll
+    for (int r = 0; r < kTogether; ++r) {
+      const int64_t e = base + (int64_t)(r0 + r) * 256;
+      if (e < L) rank[e] = v[r];
+    }
+  }
+  if (bad) flag(status, ST_BAD_INDEX);
+  for (int d = 32; d >= 1; d >>= 1) count += __shfl_xor(count, d, 64);
+  if (__lane_id() == 0) part[threadIdx.x >> 6] = count;
   __syncthreads();
-  if (threadIdx.x == 0) atomicAdd(count, part[0] + part[1] + part[2] + part[3]);
+  if (threadIdx.x == 0) atomicAdd(used, part[0] + part[1] + part[2] + part[3]);
 }
 
 // {successor, weight} pairs for the weighted walk, and the number of used
-// elements (successor other than -2) as in k_count_used
+// elements (successor other than -2)
 __global__ void k_pair_count(const int32_t* __restrict__ succ, const int32_t* __restrict__ w, int32_t L,
                              int2* __restrict__ sw, int32_t* __restrict__ count) {
   __shared__ int32_t part[4];
@@ -863,7 +893,7 @@ static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32
     ET_PROF(c, s, "k_rank_lds");
     hipLaunchKernelGGL(kern, dim3(1), dim3(kFinalThreads), rank_lds_bytes(L, H), s, succ, L, heads, 0, H,
                        empty_head_ok, ks, kSalt,
-                       pl.packed, pl.lv[0].off, nullptr, expected_reach, c->d_status);
+                       pl.packed, pl.lv[0].off, nullptr, nullptr, expected_reach, c->d_status);
     return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
   }
   hipLaunchKernelGGL(k_lr_init, dim3(ceil_div(cont_max, 256)), dim3(256), 0, s, pl.ctr, pl.rec1, S1 + H, T1);
@@ -898,7 +928,7 @@ static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32
     ET_PROF(c, s, "k_rank_lds");
     hipLaunchKernelGGL(k_rank_lds<IN_REC>, dim3(1), dim3(kFinalThreads), rank_lds_bytes(top.T, H), s,
                        reinterpret_cast<const int32_t*>(top.rec), top.T, nullptr, top.hb, H, false, ks,
-                       kSalt ^ (uint32_t)lv.size(), nullptr, top.off, nullptr, expected_reach, c->d_status);
+                       kSalt ^ (uint32_t)lv.size(), nullptr, top.off, nullptr, pl.ctr + 1, expected_reach, c->d_status);
   } else if (top.T <= kLdsMaxHeads) {
     ET_PROF(c, s, "k_final_lds");
     hipLaunchKernelGGL(k_final_lds, dim3(1), dim3(kFinalThreads), 0, s, top.rec, top.T, top.hb, H, top.off,
@@ -913,7 +943,11 @@ static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32
   }
   for (int k = (int)lv.size() - 2; k >= 0; --k) {
     ET_PROF(c, s, "k_push_down");
-    hipLaunchKernelGGL(k_push_down, dim3(ceil_div(lv[k].T, 256)), dim3(256), 0, s, lv[k].rec, lv[k].el, lv[k].T,
+    // the level-1 offsets compact where one word is enough
+    const auto kern = k > 0 || tree_weights || weighted == 2 ? k_push_down<0>
+                      : weighted                               ? k_push_down<2>
+                                                               : k_push_down<1>;
+    hipLaunchKernelGGL(kern, dim3(ceil_div(lv[k].T, 256)), dim3(256), 0, s, lv[k].rec, lv[k].el, lv[k].T,
                        lv[k + 1].off, lv[k + 1].T, lv[k].off, c->d_status);
   }
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
@@ -930,6 +964,13 @@ int list_rank_prepare() {
   return ET_OK;
 }
 
+// the level-1 offsets of a plain ranking (lengths) or of sums alone, as the
+// launches above leave them: compact if they come from a push-down
+static OffWord off_word(const LrPlan& pl, int weighted) {
+  const int32_t* p = reinterpret_cast<const int32_t*>(pl.lv[0].off);
+  return pl.lv.size() > 1 ? OffWord{p, 0} : OffWord{p + (weighted ? 1 : 0), 1};
+}
+
 int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const int32_t* heads,
                    int32_t nheads, bool tree_weights, const int32_t* expected_reach, LRResult* out,
                    hipStream_t s, bool empty_head_ok, int weighted) {
@@ -940,6 +981,7 @@ int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const 
                                   weighted);
   out->packed = pl.packed;
   out->off = pl.lv[0].off;
+  out->word = off_word(pl, weighted);
   out->nsub = pl.T1;
   return rc;
 }
@@ -948,7 +990,6 @@ int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const 
 // every buffer is reserved before the first launch.
 static int list_rank_with(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const int32_t* heads,
                           int32_t nheads, int32_t* rank, hipStream_t s) {
-  int32_t* expected = sc.get<int32_t>(1);
   LrPlan pl;
   list_rank_plan(c, sc, len, nheads, 0, &pl);
   if (sc.failed || sc.counting) return sc.failed ? ET_ENOMEM : ET_OK;
@@ -956,22 +997,19 @@ static int list_rank_with(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len,
     const int ks = rank_lds_ks(len);
     ET_PROF(c, s, "k_rank_lds");
     hipLaunchKernelGGL(k_rank_lds<IN_SUCC>, dim3(1), dim3(kFinalThreads), rank_lds_bytes(len, nheads), s, succ, len,
-                       heads, 0, nheads, false, ks, kSalt, nullptr, nullptr, rank, nullptr, c->d_status);
+                       heads, 0, nheads, false, ks, kSalt, nullptr, nullptr, rank, nullptr, nullptr, c->d_status);
     return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
   }
-  hipLaunchKernelGGL(k_set_scalar, dim3(1), dim3(1), 0, s, expected, 0);
-  {
-    ET_PROF(c, s, "k_count_used");
-    hipLaunchKernelGGL(k_count_used, dim3(std::min(ceil_div(len, 256), 2048)), dim3(256), 0, s, succ, len,
-                       expected);
-  }
-  int rc = list_rank_launch(c, pl, succ, len, heads, nheads, false, expected, s, false, 0);
+  int rc = list_rank_launch(c, pl, succ, len, heads, nheads, false, nullptr, s, false, 0);
   if (rc) return rc;
   {
     ET_PROF(c, s, "k_rank_fix");
-    hipLaunchKernelGGL(k_rank_fix, dim3(ceil_div(len, 256)), dim3(256), 0, s, succ, pl.packed, len, pl.lv[0].off,
-                       pl.T1, rank, c->d_status);
+    // elements per lane: few on a list whose blocks would not fill the GPU
+    const int per = kFixTogether * (len < (1 << 22) ? 1 : 4);
+    hipLaunchKernelGGL(k_rank_fix, dim3(ceil_div(len, 256 * per)), dim3(256), 0, s, succ, pl.packed, len, per,
+                       off_word(pl, 0), pl.T1, rank, pl.ctr + 2, c->d_status);
   }
+  hipLaunchKernelGGL(k_check_reached, dim3(1), dim3(1), 0, s, pl.ctr + 1, pl.ctr + 2, c->d_status);
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 }
 
@@ -1027,7 +1065,7 @@ int list_scan_generic(Ctx* c, const int32_t* succ, const int32_t* weights, int32
   {
     ET_PROF(c, s, rank ? "k_scan_fix<true>" : "k_scan_fix<false>");
     const auto kern = rank ? k_scan_fix<true> : k_scan_fix<false>;
-    hipLaunchKernelGGL(kern, dim3(ceil_div(len, 256)), dim3(256), 0, s, sw, r.packed, len, r.off, r.nsub, rank, sum,
+    hipLaunchKernelGGL(kern, dim3(ceil_div(len, 256)), dim3(256), 0, s, sw, r.packed, len, r.off, r.word, r.nsub, rank, sum,
                        c->d_status);
   }
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
