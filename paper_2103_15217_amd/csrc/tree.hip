@@ -44,31 +44,119 @@ __device__ __forceinline__ int32_t block_of(bool xcd) {
   return xcd ? xcd_block((int32_t)gridDim.x) : (int32_t)blockIdx.x;
 }
 
-__global__ void k_succ(const uint32_t* __restrict__ keys, const int32_t* __restrict__ vals, int32_t n,
-                       int32_t* __restrict__ sc, int32_t* __restrict__ succ, uint32_t* __restrict__ status, bool xcd) {
-  const int64_t k = (int64_t)block_of(xcd) * kB + threadIdx.x;
-  if (k >= n) return;
-  const int32_t root = sc[SC_ROOT];
-  if (k == 0) {
-    if (sc[SC_NROOTS] != 1) flag(status, ST_ROOTS);
-    sc[SC_EXPECT] = 2 * (n - 1);
-  }
+// Successor of the half-edge up out of the node at position k of the grouped
+// order; writes that of the half-edge down into its parent if it is the first
+// child (parents ascend with k, so these stores meet in few lines). false:
+// the root, or a node with an invalid parent (already flagged).
+__device__ __forceinline__ bool succ_at(const uint32_t* __restrict__ keys, const int32_t* __restrict__ vals, int32_t n,
+                                        int64_t k, int32_t root, int32_t* __restrict__ sc,
+                                        int32_t* __restrict__ succ, int32_t* c_out, int32_t* nxt_out) {
   const int32_t c = vals[k];
-  if (c == root) return;
+  if (c == root) return false;
   const uint32_t p = keys[k];
-  if (p >= (uint32_t)n) return;  // invalid parent, already flagged
+  if (p >= (uint32_t)n) return false;
   int64_t k2 = k + 1;
   if (k2 < n && vals[k2] == root) ++k2;
-  int32_t nxt;
-  if (k2 < n && keys[k2] == p) nxt = 2 * vals[k2];
-  else nxt = ((int32_t)p == root) ? -1 : (int32_t)(2 * p + 1);
-  succ[2 * c + 1] = nxt;
+  if (k2 < n && keys[k2] == p) *nxt_out = 2 * vals[k2];
+  else *nxt_out = ((int32_t)p == root) ? -1 : (int32_t)(2 * p + 1);
+  *c_out = c;
   int64_t k0 = k - 1;
   if (k0 >= 0 && vals[k0] == root) --k0;
   if (k0 < 0 || keys[k0] != p) {
     if ((int32_t)p == root) sc[SC_HEAD] = 2 * c;
     else succ[2 * p] = 2 * c;
   }
+  return true;
+}
+
+__device__ __forceinline__ void succ_scalars(int64_t k, int32_t n, int32_t* __restrict__ sc,
+                                             uint32_t* __restrict__ status) {
+  if (k != 0) return;
+  if (sc[SC_NROOTS] != 1) flag(status, ST_ROOTS);
+  sc[SC_EXPECT] = 2 * (n - 1);
+}
+
+__global__ void k_succ(const uint32_t* __restrict__ keys, const int32_t* __restrict__ vals, int32_t n,
+                       int32_t* __restrict__ sc, int32_t* __restrict__ succ, uint32_t* __restrict__ status, bool xcd) {
+  const int64_t k = (int64_t)block_of(xcd) * kB + threadIdx.x;
+  if (k >= n) return;
+  succ_scalars(k, n, sc, status);
+  int32_t c, nxt;
+  if (succ_at(keys, vals, n, k, sc[SC_ROOT], sc, succ, &c, &nxt)) succ[2 * c + 1] = nxt;
+}
+
+// The same for large trees in two passes. One store per node at a random
+// child is bound by the store rate (2^24 nodes: 455 us); here a workgroup
+// first sorts its 4096 {child, successor} pairs by ranges of children in LDS
+// and appends each range's pairs to that range's place in `pairs` (a child
+// occurs once, so range b owns [b << shift, (b + 1) << shift)), and the second
+// pass stores them, all of one range close together in time and on one XCD, so
+// that its stores fill lines in the L2: 329 us.
+constexpr int kPartThreads = 512;
+constexpr int kPartPer = 8;
+constexpr int kPartRanges = 512;  // at most; one lane each
+
+__global__ void k_part_init(int32_t* __restrict__ used) { used[threadIdx.x] = 0; }
+
+__global__ __launch_bounds__(kPartThreads) void k_succ_part(const uint32_t* __restrict__ keys,
+                                                           const int32_t* __restrict__ vals, int32_t n, int shift,
+                                                           int32_t* __restrict__ sc, int32_t* __restrict__ succ,
+                                                           int2* __restrict__ pairs, int32_t* __restrict__ used,
+                                                           uint32_t* __restrict__ status) {
+  constexpr int kTile = kPartThreads * kPartPer;
+  __shared__ int32_t cnt[kPartRanges], lstart[kPartRanges], wsum[kPartThreads / 64];
+  __shared__ int64_t gstart[kPartRanges];
+  __shared__ int2 st[kTile];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  cnt[t] = 0;
+  __syncthreads();
+  const int32_t root = sc[SC_ROOT];
+  const int64_t base = (int64_t)xcd_block((int32_t)gridDim.x) * kTile;
+  int2 pr[kPartPer];
+  int32_t at[kPartPer];
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r) {
+    const int64_t k = base + r * kPartThreads + t;
+    at[r] = -1;
+    if (k >= n) continue;
+    succ_scalars(k, n, sc, status);
+    if (succ_at(keys, vals, n, k, root, sc, succ, &pr[r].x, &pr[r].y)) at[r] = atomicAdd(&cnt[pr[r].x >> shift], 1);
+  }
+  __syncthreads();
+  // a lane per range: its start in the tile, its place in `pairs`
+  const int32_t c = cnt[t];
+  int32_t inc = c;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t u = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += u;
+  }
+  if (lane == 63) wsum[w] = inc;
+  __syncthreads();
+  int32_t before = 0, total = 0;
+  for (int i = 0; i < kPartThreads / 64; ++i) {
+    if (i < w) before += wsum[i];
+    total += wsum[i];
+  }
+  lstart[t] = before + inc - c;
+  if (c) gstart[t] = ((int64_t)t << shift) + atomicAdd(used + t, c) - lstart[t];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kPartPer; ++r)
+    if (at[r] >= 0) st[lstart[pr[r].x >> shift] + at[r]] = pr[r];
+  __syncthreads();
+  for (int32_t i = t; i < total; i += kPartThreads) {
+    const int2 p = st[i];
+    pairs[gstart[p.x >> shift] + i] = p;
+  }
+}
+
+__global__ void k_succ_store(const int2* __restrict__ pairs, const int32_t* __restrict__ used, int32_t n, int shift,
+                             int32_t* __restrict__ succ) {
+  const int64_t i = (int64_t)xcd_block((int32_t)gridDim.x) * kB + threadIdx.x;
+  if (i >= n || (i & ((1ll << shift) - 1)) >= used[i >> shift]) return;
+  const int2 p = pairs[i];
+  succ[2 * p.x + 1] = p.y;
 }
 
 __global__ void k_node(const uint64_t* __restrict__ packed, const int2* __restrict__ off, int32_t nsub,
@@ -486,9 +574,20 @@ size_t tree_build_scratch_bytes(const Ctx* c, int32_t n, int32_t batch) {
     b += scratch_block<int32_t>((size_t)n) + scratch_block<int32_t>((size_t)batch);  // n counts the virtual root
   }
   if (n <= 1) return b;
-  b += scratch_block<uint32_t>(2 * (size_t)n + 2) + scratch_block<uint32_t>((size_t)n);
+  b += scratch_block<uint32_t>(2 * (size_t)n + 2) + scratch_block<uint32_t>((size_t)n) +
+       scratch_block<int32_t>(kPartRanges);
   return b + group_by_parent_scratch_bytes(n) + list_rank_plan_bytes(c, 2 * n, 1, 0);
 }
+
+// Nodes from which the successors of one tree are stored in two passes. Up to
+// here the successor array and the grouped order that it is made from (16
+// bytes a node) stay in the 256 MB of Infinity Cache, which takes random
+// stores at twice the rate of HBM. Direct and in two passes, us: 2^22 nodes 64
+// and 75, 10M 166 and 180, 11M 213 and 199, 12M 283 and 214, 2^24 455 and 329,
+// 24M 668 and 458, 2^25 604 and 622, 40M 795 and 754, 2^26 2232 and 1299. Never
+// for a batch, whose children already lie in the order of its trees (2^24
+// nodes in 4096 trees: 323 and 538).
+constexpr int32_t kPartNodes = 12000000;
 
 int tree_build(Ctx* c, et_tree* t, const int32_t* parent, hipStream_t s) {
   const int32_t n = t->n;
@@ -508,13 +607,23 @@ int tree_build(Ctx* c, et_tree* t, const int32_t* parent, hipStream_t s) {
   const int gn = ceil_div(n, kB);
   LRResult lr;
   uint32_t* inl = scr.get<uint32_t>((size_t)n);  // inlabel of every node, compact for gathers
+  int32_t* used = scr.get<int32_t>(kPartRanges);
   if (scr.failed) return ET_ENOMEM;
   int rc;
   {
     ET_PROF(c, s, "phase:tour");
     rc = group_by_parent_impl(c, parent, n, keys, vals, t->d_succ, sc, s);
     if (rc) return rc;
-    {
+    if (!t->batch && n >= kPartNodes) {
+      int shift = 16;
+      while (((int64_t)n >> shift) >= kPartRanges) ++shift;
+      int2* pairs = reinterpret_cast<int2*>(t->d_rank);  // (written by k_node only)
+      ET_PROF(c, s, "k_succ");
+      hipLaunchKernelGGL(k_part_init, dim3(1), dim3(kPartRanges), 0, s, used);
+      hipLaunchKernelGGL(k_succ_part, dim3(ceil_div(n, kPartThreads * kPartPer)), dim3(kPartThreads), 0, s, keys, vals,
+                         n, shift, sc, t->d_succ, pairs, used, c->d_status);
+      hipLaunchKernelGGL(k_succ_store, dim3(gn), dim3(kB), 0, s, pairs, used, n, shift, t->d_succ);
+    } else {
       ET_PROF(c, s, "k_succ");
       hipLaunchKernelGGL(k_succ, dim3(gn), dim3(kB), 0, s, keys, vals, n, sc, t->d_succ, c->d_status,
                          t->batch != 0);
