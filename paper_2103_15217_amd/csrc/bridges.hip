@@ -40,6 +40,7 @@ namespace {
 
 constexpr int kB = 256;
 constexpr int kRowsPerBlock = 256;
+constexpr int32_t kLabelNodes = (1 << 20) + 1;  // vertices from which k_hook_rest gathers labels
 constexpr int kMaxGrid = 1 << 20;  // workgroups of a grid-stride launch (a dispatch holds < 2^32 work-items)
 
 __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
@@ -60,6 +61,7 @@ enum {
   FS_HEAD = 1,   // first half-edge of the chained tour, -1 if there is none
   FS_LEN = 2,    // forest half-edges
   FS_ROOTS = 3,  // components with an edge
+  FS_LABELS = 4,  // the vertices have labels
 };
 
 // Union-find over cc[]: roots satisfy cc[r] == r. A link always hangs the
@@ -167,6 +169,7 @@ __global__ void k_forest_init(const int32_t* __restrict__ row_ptr, const int32_t
     sc[FS_HEAD] = -1;
     sc[FS_LEN] = 0;
     sc[FS_ROOTS] = 0;
+    sc[FS_LABELS] = 0;
     if (count) *count = 0;
   }
   if (v >= n) return;
@@ -242,23 +245,26 @@ __global__ void k_hook_sample(const int32_t* __restrict__ row_ptr, const int32_t
   if (over) flag(status, ST_OVERFLOW);
 }
 
-__global__ void k_cc_compress(int32_t* cc, int32_t n) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < n) st(cc + v, cc_find(cc, (int32_t)v));
-}
-
-// The most frequent root among 1024 sampled vertices: the big component.
+// The big component: the most frequent root among 1024 sampled vertices.
+// With a table (where labels follow, below) also the roots that the most
+// samples have, ascending: their places are the labels. A root that has `least`
+// samples is in, the smallest number for which they fit.
 constexpr int kBigSample = 1024;
+constexpr int kLabelMax = 255;                             // labels; also "none of them"
+constexpr int kLabelRuns = kBigSample / (kLabelMax + 1);  // so many samples and they fit, but for one
 
-__global__ __launch_bounds__(kBigSample) void k_big_component(const int32_t* cc, int32_t n, int32_t* __restrict__ big) {
+__global__ __launch_bounds__(kBigSample) void k_big_component(int32_t* cc, int32_t n, int32_t* __restrict__ sc,
+                                                             int32_t* __restrict__ table) {
   __shared__ int32_t r[kBigSample];
-  __shared__ int32_t best, best_count;
+  __shared__ int32_t best, best_count, in, all[kLabelRuns], wsum[kLabelRuns][kBigSample / 64];
   const int t = threadIdx.x;
   const uint32_t v = mix32(0x2545f491u + (uint32_t)t) % (uint32_t)n;
-  r[t] = ld(cc + v);
+  r[t] = cc_find(cc, (int32_t)v);
   if (t == 0) {
     best = INT32_MAX;
     best_count = 0;
+    in = 0;
+    for (int l = 0; l < kLabelRuns; ++l) all[l] = 0;
   }
   __syncthreads();
   for (int k = 2; k <= kBigSample; k <<= 1) {  // bitonic sort
@@ -291,10 +297,60 @@ __global__ __launch_bounds__(kBigSample) void k_big_component(const int32_t* cc,
     len = lo - t;
     atomicMax(&best_count, len);
   }
+#pragma unroll
+  for (int l = 0; l < kLabelRuns; ++l) {
+    const uint64_t runs = __ballot(len > l);
+    if ((t & 63) == 0) {
+      wsum[l][t >> 6] = __popcll(runs);
+      atomicAdd(all + l, __popcll(runs));
+    }
+  }
   __syncthreads();
   if (len > 0 && len == best_count) atomicMin(&best, r[t]);
   __syncthreads();
-  if (t == 0) *big = best;
+  if (t == 0) sc[FS_BIG] = best;
+  if (!table) return;
+  int least = 1;
+  while (least < kLabelRuns && all[least - 1] > kLabelMax) ++least;
+  const uint64_t runs = __ballot(len >= least);
+  int at = __popcll(runs & ((1ull << (t & 63)) - 1));
+#pragma unroll
+  for (int i = 0; i < kBigSample / 64; ++i) at += i < (t >> 6) ? wsum[least - 1][i] : 0;
+  if (t <= kLabelMax) table[t] = INT32_MAX;
+  __syncthreads();  // (one workgroup: the roots come after the fill)
+  if (len >= least && at < kLabelMax) {
+    table[at] = r[t];
+    atomicAdd(&in, len);
+  }
+  __syncthreads();
+  // no labels if too many samples outside the big component have none
+  if (t == 0) sc[FS_LABELS] = (kBigSample - in) * 4 <= kBigSample - best_count;
+}
+
+// Full path compression. LABEL: also the label of every vertex, the place of
+// its root in the table of k_big_component, kLabelMax if it is not there.
+// Vertices of one label below kLabelMax are in one tree.
+template <bool LABEL>
+__global__ __launch_bounds__(kB) void k_cc_compress(int32_t* cc, int32_t n, const int32_t* __restrict__ sc,
+                                                   const int32_t* __restrict__ table, uint8_t* __restrict__ label) {
+  __shared__ int32_t tab[LABEL ? kLabelMax + 1 : 1];
+  const int64_t v = (int64_t)blockIdx.x * kB + threadIdx.x;
+  const bool named = LABEL && sc[FS_LABELS];
+  if (LABEL) {
+    static_assert(kB == kLabelMax + 1, "one table entry a lane");
+    tab[threadIdx.x] = table[threadIdx.x];
+    __syncthreads();
+  }
+  if (v >= n) return;
+  const int32_t r = cc_find(cc, (int32_t)v);
+  st(cc + v, r);
+  if (named) {
+    int at = 0;  // first entry of at least r; the last one is INT32_MAX
+#pragma unroll
+    for (int h = (kLabelMax + 1) / 2; h > 0; h >>= 1)
+      if (tab[at + h - 1] < r) at += h;
+    label[v] = (uint8_t)(tab[at] == r ? at : kLabelMax);
+  }
 }
 
 // Remaining phase: rows of vertices outside the big component hook every
@@ -302,37 +358,113 @@ __global__ __launch_bounds__(kBigSample) void k_big_component(const int32_t* cc,
 // already inside one tree; any other edge is seen from an endpoint outside.
 // The lanes of one row run side by side here, so the list insertion is an
 // exchange.
-template <bool EDGES>
+// Sampled (ALL false): a workgroup closes up its rows that are left and deals
+// their slots to the lanes, PER neighbouring ones at a time. Nearly all slots
+// are inside one tree; bound by the gathers that find this out: of the label
+// where there are labels (a byte a vertex, so that the table of a graph of
+// 2^22 vertices stays in a 4 MiB L2), else of the parent. At 2^22 vertices and
+// 2^26 slots in 513 components 433 us with labels, 675 without; a connected
+// graph of 2^21 vertices and 2^25 slots 16 us (67 when the slots of all rows
+// were dealt out and dropped one by one).
+// ALL: no sampling came before; every row and slot goes to the hook.
+template <bool EDGES, bool ALL, int PER>
 __global__ __launch_bounds__(kB) void k_hook_rest(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-                                                 int32_t n, int32_t nnz, int32_t* cc, const int32_t* __restrict__ bigp,
-                                                 int rows, int4* __restrict__ erec, int32_t* first,
-                                                 int32_t* __restrict__ next, uint32_t* __restrict__ status) {
-  __shared__ int32_t rp[kRowsPerBlock + 1];
-  __shared__ uint8_t skip[kRowsPerBlock];
+                                                 int32_t n, int32_t nnz, int32_t* cc, const int32_t* __restrict__ sc,
+                                                 const uint8_t* __restrict__ label, int rows,
+                                                 int4* __restrict__ erec, int32_t* first, int32_t* __restrict__ next,
+                                                 uint32_t* __restrict__ status) {
+  __shared__ int32_t start[kRowsPerBlock + 1];  // of the rows left: first slot in their numbering,
+  __shared__ int32_t slot[kRowsPerBlock];       // first slot in col,
+  __shared__ int32_t vert[kRowsPerBlock];       // vertex,
+  __shared__ int32_t tree[kRowsPerBlock];       // label, or -1 - an ancestor
+  __shared__ int32_t wdeg[kB / 64], wcnt[kB / 64];
+  static_assert(kRowsPerBlock == kB, "a lane per row");
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int32_t r0 = blockIdx.x * rows;
-  const int cnt = min(rows, n - r0);
-  const int32_t big = *bigp;
-  for (int i = threadIdx.x; i <= cnt; i += kB) rp[i] = clampi(row_ptr[r0 + i], 0, nnz);
-  for (int i = threadIdx.x; i < cnt; i += kB) skip[i] = (cc_find(cc, r0 + i) == big);
-  __syncthreads();
-  const int32_t kbeg = rp[0], kend = rp[cnt];
-  bool bad = false, over = false;
-  // 64-bit counter: kend may lie within one stride of 2^31
-  for (int64_t kk = (int64_t)kbeg + threadIdx.x; kk < kend; kk += kB) {
-    const int32_t k = (int32_t)kk;
-    const int ri = row_of(rp, cnt, k);
-    if (skip[ri]) continue;
-    const int32_t u = r0 + ri;
-    const int32_t w = col[k];
-    if ((uint32_t)w >= (uint32_t)n) {
-      bad = true;
-      continue;
+  const int32_t big = ALL ? -1 : sc[FS_BIG];
+  const bool named = !ALL && sc[FS_LABELS];
+  int32_t a = 0, b = 0, mine = 0;
+  bool keep = false, bad = false, over = false;
+  if (t < rows && r0 + t < n) {
+    a = row_ptr[r0 + t];
+    b = row_ptr[r0 + t + 1];
+    bad = a < 0 || a > b || b > nnz;
+    keep = a < b;
+    if (!ALL) {
+      const int32_t root = cc_find(cc, r0 + t);
+      mine = named ? (int32_t)label[r0 + t] : kLabelMax;
+      if (mine == kLabelMax) mine = -1 - root;
+      keep = keep && root != big;
     }
-    if (w == u || (k > rp[ri] && col[k - 1] == w)) continue;
-    const int32_t e = cc_hook(cc, u, w, big, &over);
-    if (EDGES && e >= 0) {
-      erec[e] = make_int4(u, w, k, -1);
-      next[2 * e] = atomicExch(first + u, 2 * e);
+  }
+  if (__syncthreads_or(bad)) return;  // flagged at the start of the forest
+  const uint64_t kept = __ballot(keep);
+  const int32_t deg = keep ? b - a : 0;
+  int32_t inc = deg;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t x = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += x;
+  }
+  if (lane == 63) {
+    wdeg[wv] = inc;
+    wcnt[wv] = __popcll(kept);
+  }
+  __syncthreads();
+  int32_t total = 0, cnt = 0, at = __popcll(kept & ((1ull << lane) - 1)), from = inc - deg;
+#pragma unroll
+  for (int i = 0; i < kB / 64; ++i) {
+    if (i < wv) {
+      from += wdeg[i];
+      at += wcnt[i];
+    }
+    total += wdeg[i];
+    cnt += wcnt[i];
+  }
+  if (keep) {
+    start[at] = from;
+    slot[at] = a;
+    vert[at] = r0 + t;
+    tree[at] = mine;
+  }
+  if (t == 0) start[cnt] = total;
+  __syncthreads();
+  // 64-bit counter: total may lie within one stride of 2^31
+  for (int64_t base = (int64_t)t * PER; base < total; base += kB * PER) {
+    int j = row_of(start, cnt, (int32_t)base);
+    int32_t row[PER], k[PER], w[PER], other[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int64_t x = base + i;
+      if (i > 0 && x < total && (int32_t)x >= start[j + 1]) ++j;  // (rows that are left have slots)
+      row[i] = j;
+      k[i] = x < total ? slot[j] + ((int32_t)x - start[j]) : -1;
+      w[i] = k[i] >= 0 ? col[k[i]] : 0;
+      if ((uint32_t)w[i] >= (uint32_t)n) {
+        bad = true;
+        k[i] = -1;
+        w[i] = 0;
+      }
+    }
+    if (!ALL) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) other[i] = named ? (int32_t)label[w[i]] : -1 - ldc(cc + w[i]);
+      if (named) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+          if (other[i] == kLabelMax) other[i] = -1 - ldc(cc + w[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      if (k[i] < 0 || (!ALL && other[i] == tree[row[i]])) continue;
+      const int32_t u = vert[row[i]];
+      if (w[i] == u || (k[i] > slot[row[i]] && col[k[i] - 1] == w[i])) continue;
+      const int32_t e = cc_hook(cc, u, w[i], big, &over);
+      if (EDGES && e >= 0) {
+        erec[e] = make_int4(u, w[i], k[i], -1);
+        next[2 * e] = atomicExch(first + u, 2 * e);
+      }
     }
   }
   if (bad) flag(status, ST_BAD_CSR);
@@ -891,10 +1023,10 @@ __global__ void k_hybrid_nodes(const int2* __restrict__ ds, const int4* __restri
 // largest sampled component. Edge e exists iff cc[e] != e; erec[e] = {u, w,
 // slot (u, w), -}, and first / next hold the half-edges 2e out of u
 // (k_link_in adds those out of w, and the slot (w, u)). sc: 8 scalars (FS_*).
-// mask and count (optional) are cleared on the way.
+// mask and count (optional) are cleared on the way. work: n words of scratch.
 int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, int32_t* cc,
                     int32_t* sc, int4* erec, int32_t* first, int32_t* next, uint32_t* mask, int64_t* count,
-                    hipStream_t s) {
+                    int32_t* work, hipStream_t s) {
   const int32_t words = (int32_t)(((int64_t)nnz + 31) >> 5);
   const int gn = ceil_div(n, kB);
   // rows of a workgroup: fewer on a small graph, so that its rows are spread
@@ -919,26 +1051,41 @@ int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t 
   // at 16 slots: 84 / 78 (1000), 139 / 111 (5000), 313 / 318 (2 * 10^5), 434 /
   // 423 (4 * 10^5).
   const bool sample = nnz > 8 * (int64_t)n || (nnz > (1 << 14) && n < (1 << 16)) || n >= (1 << 19);
-  for (int j = 0; j < 2 && sample; ++j) {
-    if (j == 1) {
+  // Labels where the parents (4 bytes a vertex) are more than an XCD's 4 MiB
+  // L2 holds. Whole call without / with them, us: 2^20 vertices 870 / 885 (4
+  // slots a vertex, connected), 949 / 939 (16), 951 / 952 (16, many
+  // components); 2^21 1332 / 1330, 1431 / 1448, 1609 / 1575; 2^22 2287 / 2281,
+  // 3088 / 2872, 3362 / 3134; 2^23 4210 / 4208, 5737 / 5674, 6842 / 6860 (there
+  // too many components to name). They cost one kernel's climb and count, 10 us.
+  const bool labels = sample && n >= kLabelNodes;
+  int32_t* table = labels ? work : nullptr;
+  uint8_t* label = reinterpret_cast<uint8_t*>(work + kLabelMax + 1);
+  const auto compress = [&](bool named) {
+    ET_PROF(c, s, "k_cc_compress");
+    const auto kern = named ? k_cc_compress<true> : k_cc_compress<false>;
+    hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, cc, n, sc, table, label);
+  };
+  if (sample) {
+    compress(false);
+    {
       ET_PROF(c, s, "k_hook_sample");
       const auto kern = edges ? k_hook_sample<true> : k_hook_sample<false>;
       hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, erec, first, next, c->d_status);
     }
+    if (!labels) compress(false);
     {
-      ET_PROF(c, s, "k_cc_compress");
-      hipLaunchKernelGGL(k_cc_compress, dim3(gn), dim3(kB), 0, s, cc, n);
+      ET_PROF(c, s, "k_big_component");
+      hipLaunchKernelGGL(k_big_component, dim3(1), dim3(kBigSample), 0, s, cc, n, sc, table);
     }
-  }
-  if (sample) {
-    ET_PROF(c, s, "k_big_component");
-    hipLaunchKernelGGL(k_big_component, dim3(1), dim3(kBigSample), 0, s, cc, n, sc + FS_BIG);
+    if (labels) compress(true);
   }
   {
     ET_PROF(c, s, "k_hook_rest");
-    const auto kern = edges ? k_hook_rest<true> : k_hook_rest<false>;
-    hipLaunchKernelGGL(kern, dim3(grows), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, sc + FS_BIG, rows, erec,
-                       first, next, c->d_status);
+    const auto kern = !sample                  ? (edges ? k_hook_rest<true, true, 1> : k_hook_rest<false, true, 1>)
+                      : rows == kRowsPerBlock ? (edges ? k_hook_rest<true, false, 4> : k_hook_rest<false, false, 4>)
+                                               : (edges ? k_hook_rest<true, false, 1> : k_hook_rest<false, false, 1>);
+    hipLaunchKernelGGL(kern, dim3(grows), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, sc, label, rows, erec, first,
+                       next, c->d_status);
   }
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 }
@@ -1001,7 +1148,7 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
   // 1. spanning forest
   ET_PROF(c, s, "phase:bridges");
   int rc = spanning_forest(c, row_ptr, col, n, nnz, cc, scal, erec, first, reinterpret_cast<int32_t*>(next), mask,
-                           c->d_bcount, s);
+                           c->d_bcount, pre, s);
   if (rc) return rc;
   // 2. half-edge lists, component chaining, successors
   {

@@ -332,7 +332,7 @@ int bridges_ck_bfs(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n
   if (sc.failed) return ET_ENOMEM;
   ET_PROF(c, s, "phase:bridges_ck");
   // connectivity labels only choose one search root per component
-  int rc = spanning_forest(c, row_ptr, col, n, nnz, cc, scal, nullptr, nullptr, nullptr, nullptr, nullptr, s);
+  int rc = spanning_forest(c, row_ptr, col, n, nnz, cc, scal, nullptr, nullptr, nullptr, nullptr, nullptr, par, s);
   if (rc) return rc;
   hipLaunchKernelGGL(k_fill32, dim3(std::min(ceil_div(words, kB), 4096)), dim3(kB), 0, s,
                      reinterpret_cast<int32_t*>(tbits), (int64_t)words, 0);
