@@ -5,16 +5,16 @@
 // parent array as input the half-edges of node x are its children, and a
 // stable sort of the child ids by parent id puts every node's children next
 // to each other in ascending id order, which is all the successor step
-// needs. This is an LSD radix sort over the ceil(log2 n) key bits with 8-bit
-// digits (3 passes at n = 2^24, 4 at 2^27), or 9-bit digits for short
-// arrays where that saves a pass (2 passes of 9 and 8 bits at 2^17):
+// needs. This is an LSD radix sort over the ceil(log2 n) key bits, in as few
+// passes as the digits of plan_passes() allow (2 of 9 and 8 bits at n = 2^17, 2
+// of 11 and 10 at 2^21, 3 of 8 at 2^24, 3 of 9 at 2^27):
 //
 //   upsweep    per 4096-element tile, a digit histogram (one LDS histogram
 //              per wavefront), stored digit-major so that one exclusive scan
 //              gives every (digit, tile) its output offset;
 //   scan       the array scan of scan.hip;
 //   downsweep  512 lanes per tile; each wavefront ranks its 8 rounds of 64
-//              keys stably: 8 ballots find the lanes that share a digit, the
+//              keys stably: a ballot a bit finds the lanes that share a digit, the
 //              lowest such lane bumps the wavefront's LDS counter for that
 //              digit, and the eight wavefront counters are chained per
 //              digit. The tile is then sorted by digit in LDS and written
@@ -44,8 +44,7 @@ constexpr int kTile = kThreads * kRounds;  // 4096 keys per tile
 constexpr int kDownThreads = 512;          // downsweep: 8 wavefronts of 8 rounds per tile
 constexpr int kDownWaves = kDownThreads / 64;
 constexpr int kDownRounds = kTile / kDownThreads;
-constexpr int kMaxBits = 9;                // widest digit
-constexpr int kMaxDigits = 1 << kMaxBits;  // kernels are built for 256 or 512 digits
+constexpr int kMaxBits = 11;               // widest digit; kernels are built for 256 to 2048 digits
 
 __device__ __forceinline__ uint32_t parent_key(int32_t p, int32_t n) {
   return (p >= 0 && p < n) ? (uint32_t)p : 0xffffffffu;
@@ -111,14 +110,14 @@ __global__ __launch_bounds__(kDownThreads, 2) void k_downsweep(const void* __res
                                                         uint32_t* __restrict__ keys_out,
                                                         int32_t* __restrict__ vals_out) {
   constexpr int kPer = (DIG + kDownThreads - 1) / kDownThreads;  // digits owned by one thread in the tile scan
-  __shared__ uint32_t cnt[kDownWaves][DIG];
+  __shared__ __align__(16) uint16_t cnt[kDownWaves][DIG];  // (a wavefront has 512 keys, a tile 4096)
   __shared__ uint32_t lstart[DIG];   // tile-local start of each digit's run
   __shared__ uint32_t gstart[DIG];   // global start of this tile's run of each digit
   __shared__ uint32_t skey[kTile];
   __shared__ int32_t sval[kTile];
   const int wave = threadIdx.x >> 6;
   const uint32_t mask = (1u << nbits) - 1u;
-  for (int i = threadIdx.x; i < kDownWaves * DIG; i += kDownThreads) (&cnt[0][0])[i] = 0;
+  for (int i = threadIdx.x; i < kDownWaves * DIG / 2; i += kDownThreads) reinterpret_cast<uint32_t*>(&cnt[0][0])[i] = 0;
   __syncthreads();
   const int32_t tile = xcd_block(ntiles);
   const int64_t tbase = (int64_t)tile * kTile;
@@ -141,7 +140,7 @@ __global__ __launch_bounds__(kDownThreads, 2) void k_downsweep(const void* __res
     const uint32_t dg = (key[r] >> shift) & mask;
     uint64_t peers = __ballot(valid);
 #pragma unroll
-    for (int b = 0; b < (DIG > 256 ? 9 : 8); ++b) {
+    for (int b = 0; b < (DIG > 1024 ? 11 : DIG > 512 ? 10 : DIG > 256 ? 9 : 8); ++b) {
       if (b >= nbits) break;
       const bool bit = (dg >> b) & 1u;
       const uint64_t bal = __ballot(bit);
@@ -150,7 +149,7 @@ __global__ __launch_bounds__(kDownThreads, 2) void k_downsweep(const void* __res
     const uint32_t lower = (uint32_t)__popcll(peers & below);
     const uint32_t c0 = cnt[wave][dg];
     rnk[r] = c0 + lower;
-    if (valid && lower == 0) cnt[wave][dg] = c0 + (uint32_t)__popcll(peers);
+    if (valid && lower == 0) cnt[wave][dg] = (uint16_t)(c0 + (uint32_t)__popcll(peers));
   }
   __syncthreads();
   // per digit: chain the wave counters, then an exclusive scan over digits
@@ -167,7 +166,7 @@ __global__ __launch_bounds__(kDownThreads, 2) void k_downsweep(const void* __res
 #pragma unroll
         for (int w = 0; w < kDownWaves; ++w) {
           const uint32_t c = cnt[w][d];
-          cnt[w][d] = td;  // exclusive prefix over the waves
+          cnt[w][d] = (uint16_t)td;  // exclusive prefix over the waves
           td += c;
         }
         gstart[d] = offsets[(int64_t)d * ntiles + tile];
@@ -228,16 +227,44 @@ __global__ void k_reset_root(int32_t* __restrict__ scalars) {
   scalars[1] = 0;
 }
 
-// Digit widths of the passes over `bits` key bits of n keys, balanced. A
-// 9-bit pass costs more than an 8-bit one (runs per tile half as long, a
-// larger LDS footprint per workgroup), so 9-bit digits are used
-// only for sorts of at most 2^21 keys, where the number of passes (each a
-// few launches) matters more than their bandwidth.
+// Digit widths of the passes over `bits` key bits of n keys, balanced: as few
+// passes as digits of 9 bits allow, or of 11 bits up to 2^21 keys. Longer
+// digits make shorter runs in a tile and more histogram entries, and where the
+// tiles are no more than two a compute unit a saved pass (four launches) is
+// worth more than both: widest digit 8 / 9 / 10 / 11 bits, time of the Euler
+// tour in us, 245 / 214 (66000 nodes, 2 passes of 9), 310 / 309 / 296 (300000),
+// 430 / 428 / 392 (2^20), 552 / 552 / 554 / 519 (2^21). At 2.5M nodes 11 bits
+// cost 604 / 616, at 4M 775 / 819. For the longest arrays the traffic counts,
+// three passes of 9 bits before four of 7 (2^25 nodes 5299 / 5219, 2^26 11305 /
+// 11267) but not of 10 (2^27: 24175 with 9, 24449 with 10).
 int plan_passes(int bits, int64_t n, int* width) {
-  const int p8 = (bits + 7) / 8, p9 = (bits + kMaxBits - 1) / kMaxBits;
-  const int passes = (n <= (1 << 21)) ? std::min(p8, p9) : p8;
+  const int widest = n <= (1 << 21) ? kMaxBits : 9;
+  const int passes = (bits + widest - 1) / widest;
   for (int p = 0; p < passes; ++p) width[p] = bits / passes + (p < bits % passes ? 1 : 0);
   return passes;
+}
+
+int key_bits(int64_t n) {
+  int bits = 1;
+  while (bits < 31 && (1ll << bits) < n) ++bits;
+  return bits;
+}
+
+// entries of the widest pass's histogram (the first digit is the widest)
+int64_t hist_entries(int bits, int32_t n) {
+  int width[8];
+  plan_passes(bits, n, width);
+  return ((int64_t)1 << width[0]) * ceil_div(n, kTile);
+}
+
+// the kernels for a digit width
+template <bool FIRST>
+auto upsweep_for(int nbits) {
+  return nbits > 10 ? k_upsweep<FIRST, 2048> : nbits > 9 ? k_upsweep<FIRST, 1024> : nbits > 8 ? k_upsweep<FIRST, 512> : k_upsweep<FIRST, 256>;
+}
+template <bool FIRST>
+auto downsweep_for(int nbits) {
+  return nbits > 10 ? k_downsweep<FIRST, 2048> : nbits > 9 ? k_downsweep<FIRST, 1024> : nbits > 8 ? k_downsweep<FIRST, 512> : k_downsweep<FIRST, 256>;
 }
 
 }  // namespace
@@ -245,9 +272,13 @@ int plan_passes(int bits, int64_t n, int* width) {
 // histograms of every tile and the ping-pong keys and values, plus the
 // largest histogram scan's partials
 size_t group_by_parent_scratch_bytes(int32_t n) {
-  const int32_t ntiles = ceil_div(n, kTile);
-  return scratch_block<uint32_t>((size_t)kMaxDigits * ntiles) + scratch_block<uint32_t>((size_t)n) +
-         scratch_block<int32_t>((size_t)n) + scan_scratch_bytes((int64_t)kMaxDigits * ntiles);
+  int width[8];
+  const int passes = plan_passes(key_bits(n), n, width);
+  size_t scan = 0;
+  for (int p = 0; p < passes; ++p)
+    scan = std::max(scan, scan_scratch_bytes(((int64_t)1 << width[p]) * ceil_div(n, kTile)));
+  return scratch_block<uint32_t>((size_t)hist_entries(key_bits(n), n)) + scratch_block<uint32_t>((size_t)n) +
+         scratch_block<int32_t>((size_t)n) + scan;
 }
 
 // keys_out / vals_out receive the stable order; scalars[0] = root, scalars[1]
@@ -255,13 +286,12 @@ size_t group_by_parent_scratch_bytes(int32_t n) {
 // succ[2c+1] to -2 (the successor step writes it), both root ids to -2.
 int group_by_parent_impl(Ctx* c, const int32_t* parent, int32_t n, uint32_t* keys_out, int32_t* vals_out,
                          int32_t* succ, int32_t* scalars, hipStream_t s) {
-  int bits = 1;
-  while (bits < 31 && (1ll << bits) < n) ++bits;
+  const int bits = key_bits(n);
   int width[8];
   const int passes = plan_passes(bits, n, width);
   const int32_t ntiles = ceil_div(n, kTile);
   Scratch sc(c, s);
-  uint32_t* hist = sc.get<uint32_t>((size_t)kMaxDigits * ntiles);
+  uint32_t* hist = sc.get<uint32_t>((size_t)hist_entries(bits, n));
   uint32_t* tk = sc.get<uint32_t>((size_t)n);
   int32_t* tv = sc.get<int32_t>((size_t)n);
   if (sc.failed) return ET_ENOMEM;
@@ -275,12 +305,12 @@ int group_by_parent_impl(Ctx* c, const int32_t* parent, int32_t n, uint32_t* key
     int32_t* vout = to_out ? vals_out : tv;
     if (p == 0) {
       ET_PROF(c, s, "k_upsweep<true>");
-      const auto kern = (nbits > 8) ? k_upsweep<true, 512> : k_upsweep<true, 256>;
+      const auto kern = upsweep_for<true>(nbits);
       hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kThreads), 0, s, kin, n, shift, nbits, ntiles, hist, succ, scalars,
                          c->d_status);
     } else {
       ET_PROF(c, s, "k_upsweep<false>");
-      const auto kern = (nbits > 8) ? k_upsweep<false, 512> : k_upsweep<false, 256>;
+      const auto kern = upsweep_for<false>(nbits);
       hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kThreads), 0, s, kin, n, shift, nbits, ntiles, hist, succ, scalars,
                          c->d_status);
     }
@@ -288,12 +318,12 @@ int group_by_parent_impl(Ctx* c, const int32_t* parent, int32_t n, uint32_t* key
     if (rc) return rc;
     if (p == 0) {
       ET_PROF(c, s, "k_downsweep<true>");
-      const auto kern = (nbits > 8) ? k_downsweep<true, 512> : k_downsweep<true, 256>;
+      const auto kern = downsweep_for<true>(nbits);
       hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kDownThreads), 0, s, kin, vin, n, shift, nbits, ntiles, hist, kout,
                          vout);
     } else {
       ET_PROF(c, s, "k_downsweep<false>");
-      const auto kern = (nbits > 8) ? k_downsweep<false, 512> : k_downsweep<false, 256>;
+      const auto kern = downsweep_for<false>(nbits);
       hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kDownThreads), 0, s, kin, vin, n, shift, nbits, ntiles, hist, kout,
                          vout);
     }
@@ -314,7 +344,7 @@ int sort_pairs_u32(Ctx* c, const uint32_t* keys, const int32_t* vals, int32_t n,
   const int passes = plan_passes(bits, n, width);
   const int32_t ntiles = ceil_div(n, kTile);
   Scratch sc(c, s);
-  uint32_t* hist = sc.get<uint32_t>((size_t)kMaxDigits * ntiles);
+  uint32_t* hist = sc.get<uint32_t>((size_t)hist_entries(bits, n));
   uint32_t* tk = sc.get<uint32_t>((size_t)n);
   int32_t* tv = sc.get<int32_t>((size_t)n);
   if (sc.failed) return ET_ENOMEM;
@@ -327,7 +357,7 @@ int sort_pairs_u32(Ctx* c, const uint32_t* keys, const int32_t* vals, int32_t n,
     int32_t* vout = to_out ? vals_out : tv;
     {
       ET_PROF(c, s, "k_upsweep<false>");
-      const auto kern = (nbits > 8) ? k_upsweep<false, 512> : k_upsweep<false, 256>;
+      const auto kern = upsweep_for<false>(nbits);
       hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kThreads), 0, s, kin, n, shift, nbits, ntiles, hist, nullptr,
                          nullptr, c->d_status);
     }
@@ -335,7 +365,7 @@ int sort_pairs_u32(Ctx* c, const uint32_t* keys, const int32_t* vals, int32_t n,
     if (rc) return rc;
     {
       ET_PROF(c, s, "k_downsweep<false>");
-      const auto kern = (nbits > 8) ? k_downsweep<false, 512> : k_downsweep<false, 256>;
+      const auto kern = downsweep_for<false>(nbits);
       hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kDownThreads), 0, s, kin, vin, n, shift, nbits, ntiles, hist, kout,
                          vout);
     }
