@@ -30,30 +30,6 @@ __global__ void k_fill(int32_t* __restrict__ p, int64_t n, int32_t v) {
     p[i] = v;
 }
 
-// both ends of every half-edge; ids out of range or a self-loop are flagged
-// and replaced by 0 so that every later index stays in bounds
-__global__ void k_expand(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev, int32_t m, int32_t n,
-                         int32_t* __restrict__ srcA, uint32_t* __restrict__ dst_key, int32_t* __restrict__ ids,
-                         uint32_t* __restrict__ status) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= 2 * (int64_t)m) return;
-  int32_t a = eu[h >> 1], b = ev[h >> 1];
-  if ((uint32_t)a >= (uint32_t)n || (uint32_t)b >= (uint32_t)n || a == b) {
-    flag(status, ST_BAD_PARENT);
-    a = 0;
-    b = 0;
-  }
-  srcA[h] = (h & 1) ? b : a;
-  dst_key[h] = (uint32_t)((h & 1) ? a : b);
-  ids[h] = (int32_t)h;
-}
-
-__global__ void k_src_key(const int32_t* __restrict__ order, const int32_t* __restrict__ srcA, int32_t L,
-                          uint32_t* __restrict__ key) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < L) key[k] = (uint32_t)srcA[order[k]];
-}
-
 __global__ void k_run_first(const uint32_t* __restrict__ srcB, int32_t L, int32_t* __restrict__ first) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= L) return;
@@ -103,25 +79,21 @@ __global__ void k_ranks(const uint64_t* __restrict__ packed, OffWord off, int32_
 
 // per edge: the half-edge that goes down, its child's record
 // {parent, subtree size, rank of the entering half-edge}, and the down flag
-// at that rank
-__global__ void k_edge_dir(const int32_t* __restrict__ rank, const int32_t* __restrict__ srcA, int32_t m,
-                           int32_t n, int32_t L, uint32_t* __restrict__ dw, int4* __restrict__ vrec,
-                           uint32_t* __restrict__ status) {
+// at that rank. Bound by its two scatters (3M edges: 99 us). Finding the ranks
+// here too, instead of in k_ranks, took 160 us for both where they take 130.
+__global__ void k_edge_dir(const int2* __restrict__ rank, HalfEdges he, int32_t m, int32_t L,
+                           uint32_t* __restrict__ dw, int4* __restrict__ vrec, uint32_t* __restrict__ status) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= m) return;
-  const int32_t r0 = rank[2 * i], r1 = rank[2 * i + 1];
-  if ((uint32_t)r0 >= (uint32_t)L || (uint32_t)r1 >= (uint32_t)L) {
+  const int2 r = rank[i];
+  if ((uint32_t)r.x >= (uint32_t)L || (uint32_t)r.y >= (uint32_t)L) {
     flag(status, ST_BAD_INDEX);
     return;
   }
-  const int64_t down = (r0 < r1) ? 2 * i : 2 * i + 1;
-  const int32_t rd = min(r0, r1), ru = max(r0, r1);
-  const int32_t child = srcA[down ^ 1], par = srcA[down];
-  if ((uint32_t)child >= (uint32_t)n) {
-    flag(status, ST_BAD_INDEX);
-    return;
-  }
-  vrec[child] = make_int4(par, (ru - rd + 1) >> 1, rd, 0);
+  const bool down = r.x < r.y;  // from u to v
+  const int32_t rd = min(r.x, r.y), ru = max(r.x, r.y);
+  const int32_t u = (int32_t)he.clamp(he.u[i]), v = (int32_t)he.clamp(he.v[i]);
+  vrec[down ? v : u] = make_int4(down ? u : v, (ru - rd + 1) >> 1, rd, 0);
   dw[rd] = 1u;
 }
 
@@ -182,14 +154,12 @@ int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, i
   }
   const int32_t m = n - 1;
   const int32_t L = 2 * m;
-  int bits = 1;
-  while (bits < 31 && (1ll << bits) < n) ++bits;
+  const HalfEdges he{eu, ev, n};
   Scratch scr(c, s);
-  int32_t* srcA = scr.get<int32_t>((size_t)L);
   uint32_t* key = scr.get<uint32_t>((size_t)L);
-  int32_t* ids = scr.get<int32_t>((size_t)L);
-  uint32_t* key2 = scr.get<uint32_t>((size_t)L);
   int32_t* ord = scr.get<int32_t>((size_t)L);
+  uint32_t* key2 = scr.get<uint32_t>((size_t)L);
+  int32_t* ids = scr.get<int32_t>((size_t)L);
   int32_t* first = scr.get<int32_t>((size_t)n);
   int32_t* parent = parent_out ? parent_out : scr.get<int32_t>((size_t)n);
   uint32_t* inl = scr.get<uint32_t>((size_t)n);
@@ -200,17 +170,7 @@ int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, i
   int rc;
   {
     ET_PROF(c, s, "phase:dcel");
-    {
-      ET_PROF(c, s, "k_expand");
-      hipLaunchKernelGGL(k_expand, dim3(gl), dim3(kB), 0, s, eu, ev, m, n, srcA, key, ids, c->d_status);
-    }
-    rc = sort_pairs_u32(c, key, ids, L, bits, key2, ord, s);  // by target
-    if (rc) return rc;
-    {
-      ET_PROF(c, s, "k_src_key");
-      hipLaunchKernelGGL(k_src_key, dim3(gl), dim3(kB), 0, s, ord, srcA, L, key);
-    }
-    rc = sort_pairs_u32(c, key, ord, L, bits, key2, ids, s);  // then stably by source: B = ids, sources = key2
+    rc = sort_half_edges(c, he, L, key, ord, key2, ids, s);  // B = ids, sources = key2
     if (rc) return rc;
     hipLaunchKernelGGL(k_fill, dim3(std::min(gn, 4096)), dim3(kB), 0, s, first, (int64_t)n, -1);
     hipLaunchKernelGGL(k_run_first, dim3(gl), dim3(kB), 0, s, key2, L, first);
@@ -235,7 +195,8 @@ int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, i
                        reinterpret_cast<int32_t*>(vrec), 4 * (int64_t)n, -1);
     {
       ET_PROF(c, s, "k_edge_dir");
-      hipLaunchKernelGGL(k_edge_dir, dim3(gm), dim3(kB), 0, s, t->d_rank, srcA, m, n, L, dw, vrec, c->d_status);
+      hipLaunchKernelGGL(k_edge_dir, dim3(gm), dim3(kB), 0, s, reinterpret_cast<const int2*>(t->d_rank), he, m, L, dw,
+                         vrec, c->d_status);
     }
     rc = scan_u32(c, dw, dw, L, ScanOp::Add, false, s);
     if (rc) return rc;

@@ -324,9 +324,18 @@ int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const 
 // allows the ranking kernels their dynamic LDS on the current device (once,
 // when a context is created: the calls themselves then set nothing up)
 int list_rank_prepare();
-// radix.hip: stable sort of (key, value) pairs by the low `bits` key bits
-int sort_pairs_u32(Ctx* c, const uint32_t* keys, const int32_t* vals, int32_t n, int bits, uint32_t* keys_out,
-                   int32_t* vals_out, hipStream_t s);
+// The half-edges of an edge list: 2i goes from u[i] to v[i], 2i + 1 back. The
+// ends are the caller's: clamp() makes an index in [0, n) of one.
+struct HalfEdges {
+  const int32_t* u = nullptr;
+  const int32_t* v = nullptr;
+  int32_t n = 0;
+  __device__ __forceinline__ int32_t source(int64_t h) const { return ((h & 1) ? v : u)[h >> 1]; }
+  __device__ __forceinline__ int32_t target(int64_t h) const { return ((h & 1) ? u : v)[h >> 1]; }
+  __device__ __forceinline__ uint32_t clamp(int32_t x) const { return (uint32_t)x < (uint32_t)n ? (uint32_t)x : 0u; }
+};
+int sort_half_edges(Ctx* c, HalfEdges he, int32_t L, uint32_t* key0, int32_t* val0, uint32_t* key1, int32_t* val1,
+                    hipStream_t s);
 // tree.hip: head table, path labels, ascendants and node records of a tree
 // whose preorder, compact inlabels and depths are written; t->d_root[0] must
 // hold the root id; plab: 2(n+1) slots of scratch, the first n+1 filled with

@@ -50,10 +50,16 @@ __device__ __forceinline__ uint32_t parent_key(int32_t p, int32_t n) {
   return (p >= 0 && p < n) ? (uint32_t)p : 0xffffffffu;
 }
 
+// What a first pass reads: a parent array (values: the node ids) or the targets
+// of the half-edges of an edge list (values: the half-edge ids); later passes
+// read the keys and values of the pass before.
+enum SortIn { IN_KEYS, IN_PARENT, IN_TARGET };
+
 // scalars[0] = root id, scalars[1] = number of roots
-template <bool FIRST, int DIG>
-__global__ __launch_bounds__(kThreads) void k_upsweep(const void* __restrict__ keys_in, int32_t n, int shift,
-                                                      int nbits, int32_t ntiles, uint32_t* __restrict__ hist,
+template <SortIn IN, int DIG>
+__global__ __launch_bounds__(kThreads) void k_upsweep(const void* __restrict__ keys_in, HalfEdges he, int32_t n,
+                                                      int shift, int nbits, int32_t ntiles,
+                                                      uint32_t* __restrict__ hist,
                                                       int32_t* __restrict__ succ, int32_t* __restrict__ scalars,
                                                       uint32_t* __restrict__ status) {
   __shared__ uint32_t h[kWaves][DIG];
@@ -69,14 +75,20 @@ __global__ __launch_bounds__(kThreads) void k_upsweep(const void* __restrict__ k
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     const int64_t idx = base + r * kThreads + threadIdx.x;
-    raw[r] = idx < n ? static_cast<const uint32_t*>(keys_in)[idx] : 0u;
+    if (IN == IN_TARGET) raw[r] = idx < n ? (uint32_t)he.target(idx) : 0u;
+    else raw[r] = idx < n ? static_cast<const uint32_t*>(keys_in)[idx] : 0u;
   }
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     const int64_t idx = base + r * kThreads + threadIdx.x;
     if (idx >= n) break;
     uint32_t key;
-    if (FIRST) {
+    if (IN == IN_TARGET) {
+      // the other half-edge of the edge is the neighbouring lane's
+      const uint32_t x = raw[r], y = (uint32_t)__shfl_xor((int32_t)x, 1, 64);
+      if (x >= (uint32_t)he.n || x == y) bad = true;
+      key = he.clamp((int32_t)x);
+    } else if (IN == IN_PARENT) {
       const int32_t p = (int32_t)raw[r];
       key = parent_key(p, n);
       if (p == -1) {
@@ -102,10 +114,13 @@ __global__ __launch_bounds__(kThreads) void k_upsweep(const void* __restrict__ k
     hist[(int64_t)d * ntiles + tile] = h[0][d] + h[1][d] + h[2][d] + h[3][d];
 }
 
-template <bool FIRST, int DIG>
+// BY_SOURCE: the last pass by target gives out every half-edge with its source
+// for a key. The gather (6M half-edges: 95 us in a kernel of its own, 24 MB out
+// and in again) is made from the sorted tile, all of a lane's loads together.
+template <SortIn IN, bool BY_SOURCE, int DIG>
 __global__ __launch_bounds__(kDownThreads, 2) void k_downsweep(const void* __restrict__ keys_in,
-                                                        const int32_t* __restrict__ vals_in, int32_t n, int shift,
-                                                        int nbits, int32_t ntiles,
+                                                        const int32_t* __restrict__ vals_in, HalfEdges he, int32_t n,
+                                                        int shift, int nbits, int32_t ntiles,
                                                         const uint32_t* __restrict__ offsets,
                                                         uint32_t* __restrict__ keys_out,
                                                         int32_t* __restrict__ vals_out) {
@@ -130,7 +145,10 @@ __global__ __launch_bounds__(kDownThreads, 2) void k_downsweep(const void* __res
   for (int r = 0; r < kDownRounds; ++r) {
     const int64_t idx = wbase + r * 64;
     const bool valid = idx < n;
-    if (FIRST) {
+    if (IN == IN_TARGET) {
+      key[r] = valid ? he.clamp(he.target(idx)) : 0u;
+      val[r] = (int32_t)idx;
+    } else if (IN == IN_PARENT) {
       key[r] = valid ? parent_key(static_cast<const int32_t*>(keys_in)[idx], n) : 0u;
       val[r] = (int32_t)idx;
     } else {
@@ -209,6 +227,13 @@ __global__ __launch_bounds__(kDownThreads, 2) void k_downsweep(const void* __res
   __syncthreads();
   // write the tile out digit run by digit run: consecutive lanes, consecutive addresses
   const int valid_in_tile = (int)min<int64_t>((int64_t)kTile, n - tbase);
+  if (BY_SOURCE) {
+#pragma unroll
+    for (int r = 0; r < kDownRounds; ++r) {
+      const int i = r * kDownThreads + threadIdx.x;
+      key[r] = i < valid_in_tile ? (uint32_t)he.source(sval[i]) : 0u;
+    }
+  }
 #pragma unroll
   for (int r = 0; r < kDownRounds; ++r) {
     const int i = r * kDownThreads + threadIdx.x;
@@ -216,7 +241,7 @@ __global__ __launch_bounds__(kDownThreads, 2) void k_downsweep(const void* __res
       const uint32_t k = skey[i];
       const uint32_t dg = (k >> shift) & mask;
       const uint32_t pos = gstart[dg] + (uint32_t)i - lstart[dg];
-      keys_out[pos] = k;
+      keys_out[pos] = BY_SOURCE ? he.clamp((int32_t)key[r]) : k;
       vals_out[pos] = sval[i];
     }
   }
@@ -258,13 +283,39 @@ int64_t hist_entries(int bits, int32_t n) {
 }
 
 // the kernels for a digit width
-template <bool FIRST>
+template <SortIn IN>
 auto upsweep_for(int nbits) {
-  return nbits > 10 ? k_upsweep<FIRST, 2048> : nbits > 9 ? k_upsweep<FIRST, 1024> : nbits > 8 ? k_upsweep<FIRST, 512> : k_upsweep<FIRST, 256>;
+  return nbits > 10  ? k_upsweep<IN, 2048>
+         : nbits > 9 ? k_upsweep<IN, 1024>
+         : nbits > 8 ? k_upsweep<IN, 512>
+                     : k_upsweep<IN, 256>;
 }
-template <bool FIRST>
+template <SortIn IN, bool BY_SOURCE>
 auto downsweep_for(int nbits) {
-  return nbits > 10 ? k_downsweep<FIRST, 2048> : nbits > 9 ? k_downsweep<FIRST, 1024> : nbits > 8 ? k_downsweep<FIRST, 512> : k_downsweep<FIRST, 256>;
+  return nbits > 10  ? k_downsweep<IN, BY_SOURCE, 2048>
+         : nbits > 9 ? k_downsweep<IN, BY_SOURCE, 1024>
+         : nbits > 8 ? k_downsweep<IN, BY_SOURCE, 512>
+                     : k_downsweep<IN, BY_SOURCE, 256>;
+}
+
+// one pass: histograms, their scan, the scatter
+template <SortIn IN, bool BY_SOURCE>
+int sort_pass(Ctx* c, const void* kin, const int32_t* vin, HalfEdges he, int32_t n, int shift, int nbits,
+              uint32_t* hist, uint32_t* kout, int32_t* vout, int32_t* succ, int32_t* scalars, hipStream_t s) {
+  const int32_t ntiles = ceil_div(n, kTile);
+  {
+    ET_PROF(c, s, IN == IN_KEYS ? "k_upsweep<false>" : "k_upsweep<true>");
+    hipLaunchKernelGGL(upsweep_for<IN>(nbits), dim3(ntiles), dim3(kThreads), 0, s, kin, he, n, shift, nbits, ntiles,
+                       hist, succ, scalars, c->d_status);
+  }
+  const int rc = scan_u32(c, hist, hist, ((int64_t)1 << nbits) * ntiles, ScanOp::Add, true, s);
+  if (rc) return rc;
+  {
+    ET_PROF(c, s, IN == IN_KEYS ? "k_downsweep<false>" : "k_downsweep<true>");
+    hipLaunchKernelGGL((downsweep_for<IN, BY_SOURCE>(nbits)), dim3(ntiles), dim3(kDownThreads), 0, s, kin, vin, he, n,
+                       shift, nbits, ntiles, hist, kout, vout);
+  }
+  return ET_OK;
 }
 
 }  // namespace
@@ -289,7 +340,6 @@ int group_by_parent_impl(Ctx* c, const int32_t* parent, int32_t n, uint32_t* key
   const int bits = key_bits(n);
   int width[8];
   const int passes = plan_passes(bits, n, width);
-  const int32_t ntiles = ceil_div(n, kTile);
   Scratch sc(c, s);
   uint32_t* hist = sc.get<uint32_t>((size_t)hist_entries(bits, n));
   uint32_t* tk = sc.get<uint32_t>((size_t)n);
@@ -299,76 +349,43 @@ int group_by_parent_impl(Ctx* c, const int32_t* parent, int32_t n, uint32_t* key
   const void* kin = parent;
   const int32_t* vin = nullptr;
   for (int p = 0, shift = 0; p < passes; shift += width[p], ++p) {
-    const int nbits = width[p];
     const bool to_out = ((passes - 1 - p) % 2) == 0;
     uint32_t* kout = to_out ? keys_out : tk;
     int32_t* vout = to_out ? vals_out : tv;
-    if (p == 0) {
-      ET_PROF(c, s, "k_upsweep<true>");
-      const auto kern = upsweep_for<true>(nbits);
-      hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kThreads), 0, s, kin, n, shift, nbits, ntiles, hist, succ, scalars,
-                         c->d_status);
-    } else {
-      ET_PROF(c, s, "k_upsweep<false>");
-      const auto kern = upsweep_for<false>(nbits);
-      hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kThreads), 0, s, kin, n, shift, nbits, ntiles, hist, succ, scalars,
-                         c->d_status);
-    }
-    int rc = scan_u32(c, hist, hist, (int64_t)(1 << nbits) * ntiles, ScanOp::Add, true, s);
+    const auto pass = p == 0 ? sort_pass<IN_PARENT, false> : sort_pass<IN_KEYS, false>;
+    const int rc = pass(c, kin, vin, HalfEdges{}, n, shift, width[p], hist, kout, vout, succ, scalars, s);
     if (rc) return rc;
-    if (p == 0) {
-      ET_PROF(c, s, "k_downsweep<true>");
-      const auto kern = downsweep_for<true>(nbits);
-      hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kDownThreads), 0, s, kin, vin, n, shift, nbits, ntiles, hist, kout,
-                         vout);
-    } else {
-      ET_PROF(c, s, "k_downsweep<false>");
-      const auto kern = downsweep_for<false>(nbits);
-      hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kDownThreads), 0, s, kin, vin, n, shift, nbits, ntiles, hist, kout,
-                         vout);
-    }
     kin = kout;
     vin = vout;
   }
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 }
 
-// Stable sort of (key, value) pairs by the low `bits` bits of the key, with
-// the same kernels: keys_out / vals_out receive the sorted pairs; the inputs
-// are left as they are.
-int sort_pairs_u32(Ctx* c, const uint32_t* keys, const int32_t* vals, int32_t n, int bits, uint32_t* keys_out,
-                   int32_t* vals_out, hipStream_t s) {
-  if (n <= 0) return ET_OK;
-  bits = std::max(1, std::min(bits, 32));
+// The half-edges of an edge list in lexicographic order of {source, target}:
+// stably by target, then stably by source, in passes over the half-edge ids
+// between {key0, val0} and {key1, val1}; key1 / val1 receive the sources and
+// the ids. Ends out of range are flagged (as are self-loops) and count as 0.
+int sort_half_edges(Ctx* c, HalfEdges he, int32_t L, uint32_t* key0, int32_t* val0, uint32_t* key1, int32_t* val1,
+                    hipStream_t s) {
+  const int bits = key_bits(he.n);
   int width[8];
-  const int passes = plan_passes(bits, n, width);
-  const int32_t ntiles = ceil_div(n, kTile);
+  const int passes = plan_passes(bits, L, width);
   Scratch sc(c, s);
-  uint32_t* hist = sc.get<uint32_t>((size_t)hist_entries(bits, n));
-  uint32_t* tk = sc.get<uint32_t>((size_t)n);
-  int32_t* tv = sc.get<int32_t>((size_t)n);
+  uint32_t* hist = sc.get<uint32_t>((size_t)hist_entries(bits, L));
   if (sc.failed) return ET_ENOMEM;
-  const void* kin = keys;
-  const int32_t* vin = vals;
-  for (int p = 0, shift = 0; p < passes; shift += width[p], ++p) {
-    const int nbits = width[p];
-    const bool to_out = ((passes - 1 - p) % 2) == 0;
-    uint32_t* kout = to_out ? keys_out : tk;
-    int32_t* vout = to_out ? vals_out : tv;
-    {
-      ET_PROF(c, s, "k_upsweep<false>");
-      const auto kern = upsweep_for<false>(nbits);
-      hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kThreads), 0, s, kin, n, shift, nbits, ntiles, hist, nullptr,
-                         nullptr, c->d_status);
-    }
-    int rc = scan_u32(c, hist, hist, (int64_t)(1 << nbits) * ntiles, ScanOp::Add, true, s);
+  const void* kin = nullptr;
+  const int32_t* vin = nullptr;
+  for (int q = 0, shift = 0; q < 2 * passes; ++q) {
+    const int p = q % passes;
+    if (p == 0) shift = 0;
+    const bool last_by_target = q == passes - 1;
+    const auto pass = q == 0 ? (last_by_target ? sort_pass<IN_TARGET, true> : sort_pass<IN_TARGET, false>)
+                             : (last_by_target ? sort_pass<IN_KEYS, true> : sort_pass<IN_KEYS, false>);
+    uint32_t* kout = (q & 1) ? key1 : key0;  // an even number of passes: the last one is odd
+    int32_t* vout = (q & 1) ? val1 : val0;
+    const int rc = pass(c, kin, vin, he, L, shift, width[p], hist, kout, vout, nullptr, nullptr, s);
     if (rc) return rc;
-    {
-      ET_PROF(c, s, "k_downsweep<false>");
-      const auto kern = downsweep_for<false>(nbits);
-      hipLaunchKernelGGL(kern, dim3(ntiles), dim3(kDownThreads), 0, s, kin, vin, n, shift, nbits, ntiles, hist, kout,
-                         vout);
-    }
+    shift += width[p];
     kin = kout;
     vin = vout;
   }
