@@ -317,10 +317,13 @@ struct LRResult {
 // weighted 1 or 2: succ holds {successor, weight} int32 pairs and the
 // weights are summed instead (sublist sums in the second channel of
 // out->off); packed then holds {sublist, inclusive local sum} per element
-// (1), or two words {sublist | local rank << 32, inclusive local sum} (2)
+// (1), or two words {sublist | local rank << 32, inclusive local sum} (2).
+// local_len: if the list runs through stretches of the array one after the
+// other (a batch of trees), their average length, else 0
 int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const int32_t* heads,
                    int32_t nheads, bool tree_weights, const int32_t* expected_reach,
-                   LRResult* out, hipStream_t s, bool empty_head_ok = false, int weighted = 0);
+                   LRResult* out, hipStream_t s, bool empty_head_ok = false, int weighted = 0,
+                   int32_t local_len = 0);
 // allows the ranking kernels their dynamic LDS on the current device (once,
 // when a context is created: the calls themselves then set nothing up)
 int list_rank_prepare();

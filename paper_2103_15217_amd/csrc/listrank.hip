@@ -74,14 +74,15 @@ __global__ void k_lr_init(int32_t* __restrict__ ctr, int4* __restrict__ rec, int
 // 16-bit field, so the record is {sublist, local sum} (W = 1, 8 bytes) or,
 // when ranks are wanted too, {sublist | local rank << 32, local sum}
 // (W = 2, 16 bytes).
+// block: the workgroup's place in the order of the sublists.
 template <bool TREE, int W>
 __device__ __forceinline__ void walk1_body(
     const int32_t* __restrict__ succ, int32_t L, const int32_t* __restrict__ heads, int32_t H, int ks,
     uint32_t salt, int32_t S, int32_t per_wave, uint64_t* __restrict__ packed, int4* __restrict__ srec,
     int32_t* __restrict__ cont_ctr, int32_t cont_base, int32_t cont_max, bool empty_ok,
-    uint32_t* __restrict__ status) {
+    uint32_t* __restrict__ status, int32_t block) {
   constexpr int kStride = W > 0 ? 2 : 1;  // int32 words per element in succ
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int64_t wave = ((int64_t)block * blockDim.x + threadIdx.x) >> 6;
   const int32_t total = S + H;
   int32_t next_id = (int32_t)min<int64_t>(wave * per_wave, total);
   const int32_t end_id = (int32_t)min<int64_t>((int64_t)next_id + per_wave, total);
@@ -196,14 +197,19 @@ __device__ __forceinline__ void walk1_body(
   }
 }
 
+// Bound by random accesses, a load and a store per element (2^25 elements 1.1
+// ms, 30 G/s; a random tree's 2^25 half-edges 865 us). Fewer wavefronts at a
+// time are slower, and so are shorter runs of sublists per wavefront, unless
+// the lists are local (see list_rank_launch): then xcd hands each XCD a
+// contiguous range of the sublists.
 template <bool TREE>
 __global__ __launch_bounds__(kWalkThreads) void k_walk1(
     const int32_t* __restrict__ succ, int32_t L, const int32_t* __restrict__ heads, int32_t H, int ks,
     uint32_t salt, int32_t S, int32_t per_wave, uint64_t* __restrict__ packed, int4* __restrict__ srec,
     int32_t* __restrict__ cont_ctr, int32_t cont_base, int32_t cont_max, bool empty_ok,
-    uint32_t* __restrict__ status) {
+    uint32_t* __restrict__ status, bool xcd) {
   walk1_body<TREE, 0>(succ, L, heads, H, ks, salt, S, per_wave, packed, srec, cont_ctr, cont_base, cont_max,
-                      empty_ok, status);
+                      empty_ok, status, xcd ? xcd_block((int32_t)gridDim.x) : (int32_t)blockIdx.x);
 }
 
 // the same walk over {successor, weight} pairs, summing the weights; RANK:
@@ -215,7 +221,7 @@ __global__ __launch_bounds__(kWalkThreads) void k_walk1w(
     int32_t* __restrict__ cont_ctr, int32_t cont_base, int32_t cont_max, bool empty_ok,
     uint32_t* __restrict__ status) {
   walk1_body<false, RANK ? 2 : 1>(sw, L, heads, H, ks, salt, S, per_wave, packed, srec, cont_ctr, cont_base,
-                                  cont_max, empty_ok, status);
+                                  cont_max, empty_ok, status, (int32_t)blockIdx.x);
 }
 
 // ------------------------------------------------------------------ level k >= 2
@@ -880,9 +886,11 @@ static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weight
   for (auto& l : pl->lv) l.off = sc.get<int2>((size_t)l.T);
 }
 
+constexpr int32_t kLocalXcd = 1 << 20;  // elements of a list up to which an XCD keeps its own stretch
+
 static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32_t L, const int32_t* heads,
                             int32_t H, bool tree_weights, const int32_t* expected_reach, hipStream_t s,
-                            bool empty_head_ok, int weighted) {
+                            bool empty_head_ok, int weighted, int32_t local_len) {
   const int32_t S1 = pl.S1, T1 = pl.T1, cont_max = pl.cont_max;
   if (pl.direct) {
     const int ks = rank_lds_ks(L);
@@ -897,20 +905,33 @@ static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32
     return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
   }
   hipLaunchKernelGGL(k_lr_init, dim3(ceil_div(cont_max, 256)), dim3(256), 0, s, pl.ctr, pl.rec1, S1 + H, T1);
-  const dim3 g1(walk_grid(S1 + H, pl.per_wave1));
+  // Where the lists are local (a batch of trees: a tree's half-edges lie
+  // together) a wavefront takes one round of sublists only, so that the
+  // workgroups in flight cover a short stretch of the array, whose lines stay
+  // in the cache until all their elements are passed; and where two such trees
+  // fit an XCD's L2, each XCD takes its own stretch. Level 1 in us, as for one
+  // list / one round / one round and a stretch per XCD: 4096 trees of 2^12
+  // nodes 880 / 693 / 595, 300 of 2^16 1110 / 949 / 753, 64 of 2^18 1016 / 831 /
+  // 735, 16 of 2^20 976 / 858 / 902, 4 of 2^22 1015 / 923 / 1096; one tree of
+  // 2^24 866 / 901 / 900.
+  const bool local = local_len > 0;
+  const int32_t per_wave1 = local ? 64 : pl.per_wave1;
+  const dim3 g1(walk_grid(S1 + H, per_wave1));
   if (tree_weights) {
     ET_PROF(c, s, "k_walk1<true>");
     hipLaunchKernelGGL(k_walk1<true>, g1, dim3(kWalkThreads), 0, s, succ, L, heads, H, pl.ks1, kSalt, S1,
-                       pl.per_wave1, pl.packed, pl.rec1, pl.ctr, S1 + H, cont_max, empty_head_ok, c->d_status);
+                       per_wave1, pl.packed, pl.rec1, pl.ctr, S1 + H, cont_max, empty_head_ok, c->d_status,
+                       local && local_len <= kLocalXcd);
   } else if (weighted) {
     ET_PROF(c, s, weighted == 2 ? "k_walk1w<true>" : "k_walk1w<false>");
     const auto kern = weighted == 2 ? k_walk1w<true> : k_walk1w<false>;
-    hipLaunchKernelGGL(kern, g1, dim3(kWalkThreads), 0, s, succ, L, heads, H, pl.ks1, kSalt, S1, pl.per_wave1,
+    hipLaunchKernelGGL(kern, g1, dim3(kWalkThreads), 0, s, succ, L, heads, H, pl.ks1, kSalt, S1, per_wave1,
                        pl.packed, pl.rec1, pl.ctr, S1 + H, cont_max, empty_head_ok, c->d_status);
   } else {
     ET_PROF(c, s, "k_walk1<false>");
     hipLaunchKernelGGL(k_walk1<false>, g1, dim3(kWalkThreads), 0, s, succ, L, heads, H, pl.ks1, kSalt, S1,
-                       pl.per_wave1, pl.packed, pl.rec1, pl.ctr, S1 + H, cont_max, empty_head_ok, c->d_status);
+                       per_wave1, pl.packed, pl.rec1, pl.ctr, S1 + H, cont_max, empty_head_ok, c->d_status,
+                       local && local_len <= kLocalXcd);
   }
   // upper levels: level k's records are walked into level k+1's
   const auto& lv = pl.lv;
@@ -973,12 +994,12 @@ static OffWord off_word(const LrPlan& pl, int weighted) {
 
 int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const int32_t* heads,
                    int32_t nheads, bool tree_weights, const int32_t* expected_reach, LRResult* out,
-                   hipStream_t s, bool empty_head_ok, int weighted) {
+                   hipStream_t s, bool empty_head_ok, int weighted, int32_t local_len) {
   LrPlan pl;
   list_rank_plan(c, sc, len, nheads, weighted, &pl);
   if (sc.failed) return ET_ENOMEM;
   const int rc = list_rank_launch(c, pl, succ, len, heads, nheads, tree_weights, expected_reach, s, empty_head_ok,
-                                  weighted);
+                                  weighted, local_len);
   out->packed = pl.packed;
   out->off = pl.lv[0].off;
   out->word = off_word(pl, weighted);
@@ -1000,7 +1021,7 @@ static int list_rank_with(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len,
                        heads, 0, nheads, false, ks, kSalt, nullptr, nullptr, rank, nullptr, nullptr, c->d_status);
     return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
   }
-  int rc = list_rank_launch(c, pl, succ, len, heads, nheads, false, nullptr, s, false, 0);
+  int rc = list_rank_launch(c, pl, succ, len, heads, nheads, false, nullptr, s, false, 0, 0);
   if (rc) return rc;
   {
     ET_PROF(c, s, "k_rank_fix");

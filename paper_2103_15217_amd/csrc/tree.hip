@@ -628,7 +628,8 @@ int tree_build(Ctx* c, et_tree* t, const int32_t* parent, hipStream_t s) {
       hipLaunchKernelGGL(k_succ, dim3(gn), dim3(kB), 0, s, keys, vals, n, sc, t->d_succ, c->d_status,
                          t->batch != 0);
     }
-    rc = list_rank_core(c, scr, t->d_succ, L2, sc + SC_HEAD, 1, true, sc + SC_EXPECT, &lr, s);
+    rc = list_rank_core(c, scr, t->d_succ, L2, sc + SC_HEAD, 1, true, sc + SC_EXPECT, &lr, s, false, 0,
+                        t->batch ? L2 / t->batch : 0);
     if (rc) return rc;
     {
       ET_PROF(c, s, "k_node");
