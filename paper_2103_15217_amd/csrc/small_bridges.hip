@@ -1,10 +1,9 @@
 // Bridges of many small graphs in one launch (Section 4.1, Tarjan-Vishkin,
 // for a batch of instances as the tree batch of Section 3.3 does for LCA).
 //
-// A workgroup of 1024 lanes takes one graph at a time from an atomic counter
-// (in the caller's order when one is given)
-// (a persistent grid sized to what stays resident) and runs the whole method
-// on it in LDS, reading only its CSR from HBM and writing only its mask words
+// A workgroup takes one graph at a time from an atomic counter (in the caller's
+// order when one is given; a persistent grid sized to what stays resident) and
+// runs the whole method on it in LDS, reading only its CSR from HBM and writing only its mask words
 // and its bridge count:
 //   1. row pointers and columns into LDS, checked (monotone rows from 0 to
 //      the slot count, sorted rows, every slot's twin present);
@@ -32,8 +31,10 @@
 namespace et {
 namespace {
 
-constexpr int kBT = 1024;            // lanes per workgroup
-constexpr int kBW = kBT / 64;
+constexpr int kBT = 1024;            // lanes per workgroup,
+constexpr int kBTSmall = 256;        // and for many small graphs:
+constexpr int kGSmallV = 256;        // of at most this many vertices
+constexpr int kGSmallS = 2048;       // and CSR slots
 constexpr int kGMaxV = 1024;         // vertices of a graph at most
 constexpr int kGMaxS = 8192;         // CSR slots of a graph at most
 constexpr uint16_t kNil = 0xffff;    // list end, no slot
@@ -133,10 +134,11 @@ __device__ __forceinline__ uint32_t row_of_slot(const uint16_t* rp, uint32_t n, 
 }
 
 // Inclusive prefix maximum of the u16 values a[0..m) in place by the
-// workgroup; wsum: kBW slots.
+// workgroup; wsum: a slot per wavefront.
+template <int BT>
 __device__ inline void wg_prefix_max_u16(uint16_t* a, int m, int32_t* wsum) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int per = (m + kBT - 1) / kBT;
+  const int per = (m + BT - 1) / BT;
   const int lo = min(tid * per, m), hi = min(lo + per, m);
   uint32_t mx = 0;
   for (int i = lo; i < hi; ++i) mx = max(mx, (uint32_t)a[i]);
@@ -149,14 +151,14 @@ __device__ inline void wg_prefix_max_u16(uint16_t* a, int m, int32_t* wsum) {
   if (lane == 63) wsum[w] = (int32_t)incl;
   __syncthreads();
   if (tid < 64) {
-    uint32_t x = tid < kBW ? (uint32_t)wsum[tid] : 0u;
+    uint32_t x = tid < (BT / 64) ? (uint32_t)wsum[tid] : 0u;
 #pragma unroll
-    for (int d = 1; d < kBW; d <<= 1) {
+    for (int d = 1; d < (BT / 64); d <<= 1) {
       const uint32_t y = __shfl_up(x, d);
       if (lane >= d) x = max(x, y);
     }
     const uint32_t before = __shfl_up(x, 1);  // the waves before this one
-    if (tid < kBW) wsum[tid] = (int32_t)(tid == 0 ? 0u : before);
+    if (tid < (BT / 64)) wsum[tid] = (int32_t)(tid == 0 ? 0u : before);
   }
   __syncthreads();
   const uint32_t lanes_before = __shfl_up(incl, 1);
@@ -178,7 +180,8 @@ __device__ __forceinline__ uint32_t uf_find(uint32_t* uf, uint32_t x) {
   }
 }
 
-__global__ __launch_bounds__(kBT, 8) void k_small_bridges(
+template <int BT>
+__global__ __launch_bounds__(BT, 8) void k_small_bridges(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, const int64_t* __restrict__ voff,
     const int64_t* __restrict__ soff, const int64_t* __restrict__ moff, int32_t T, int64_t n_total,
     int64_t nnz_total, int64_t mask_words, uint32_t N, uint32_t M, int32_t vmax, int32_t smax,
@@ -224,8 +227,8 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
         moff[T] > mask_words)
       flag(status, ST_BAD_CSR);
   }
-  for (;;) {
-    if (tid == 0) SC[B_GRAPH] = (int32_t)atomicAdd(&counters[0], 1u);
+  for (bool first = true;; first = false) {  // the first ones are dealt out by workgroup
+    if (tid == 0) SC[B_GRAPH] = (int32_t)(first ? blockIdx.x : gridDim.x + atomicAdd(&counters[0], 1u));
     __syncthreads();
     const int32_t k = SC[B_GRAPH];
     if (k >= T) break;
@@ -246,14 +249,14 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
       SC[B_CNT] = 0;
       SC[B_NR] = 0;
     }
-    for (uint32_t i = tid; i < (m + 31) / 32 + 1; i += kBT) {
+    for (uint32_t i = tid; i < (m + 31) / 32 + 1; i += BT) {
       TF[i] = 0;
       MB[i] = 0;
     }
     __syncthreads();
 
     // 1. the CSR (nothing is read for a graph whose offsets are out of range)
-    for (uint32_t v = tid; g_ok && v <= n; v += kBT) {
+    for (uint32_t v = tid; g_ok && v <= n; v += BT) {
       const int32_t r = rpg[v];
       if (r < 0 || (uint32_t)r > m || (v == 0 && r != 0) || (v == n && (uint32_t)r != m)) {
         SC[B_BAD] = 1;
@@ -262,7 +265,7 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
         RP[v] = (uint16_t)r;
       }
     }
-    for (uint32_t k = tid; k < m; k += kBT) {
+    for (uint32_t k = tid; k < m; k += BT) {
       const int32_t w = col[sb + k];
       if (w < 0 || (uint32_t)w >= n) {
         SC[B_BAD] = 1;
@@ -272,19 +275,19 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
       }
     }
     __syncthreads();
-    for (uint32_t v = tid; v < n; v += kBT)
+    for (uint32_t v = tid; v < n; v += BT)
       if (RP[v] > RP[v + 1]) SC[B_BAD] = 1;
     __syncthreads();
     if (!SC[B_BAD] && n > 0) {
       // the row of every slot: each non-empty row's first slot marked with
       // the row, then a prefix maximum (rows are stored in vertex order)
-      for (uint32_t k = tid; k < m; k += kBT) ROW[k] = 0;
+      for (uint32_t k = tid; k < m; k += BT) ROW[k] = 0;
       __syncthreads();
-      for (uint32_t v = tid; v < n; v += kBT)
+      for (uint32_t v = tid; v < n; v += BT)
         if (RP[v] < RP[v + 1]) ROW[RP[v]] = (uint16_t)v;
       __syncthreads();
-      wg_prefix_max_u16(ROW, (int)m, SC + B_WSUM);
-      for (uint32_t k = tid; k < m; k += kBT) {
+      wg_prefix_max_u16<BT>(ROW, (int)m, SC + B_WSUM);
+      for (uint32_t k = tid; k < m; k += BT) {
         const uint32_t lo = ROW[k];
         const uint32_t w = COL[k];
         if (k > RP[lo] && COL[k - 1] > w) SC[B_BAD] = 1;  // rows sorted
@@ -301,9 +304,9 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
 
     if (!SC[B_FAIL] && m > 0) {
       // 2. spanning forest
-      for (uint32_t v = tid; v < n; v += kBT) UF[v] = v;
+      for (uint32_t v = tid; v < n; v += BT) UF[v] = v;
       __syncthreads();
-      for (uint32_t k = tid; k < m; k += kBT) {
+      for (uint32_t k = tid; k < m; k += BT) {
         const uint32_t u = ROW[k], w = COL[k];
         if (u >= w || (k > RP[u] && COL[k - 1] == w)) continue;  // one slot per u-w run, u < w
         uint32_t ru = uf_find(UF, u), rw = uf_find(UF, w);
@@ -320,23 +323,23 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
         }
       }
       __syncthreads();
-      for (uint32_t v = tid; v < n; v += kBT) UF[v] = uf_find(UF, v);  // roots (the least id of each component)
+      for (uint32_t v = tid; v < n; v += BT) UF[v] = uf_find(UF, v);  // roots (the least id of each component)
       __syncthreads();
 
       // 3. forest half-edges per vertex, in row order: rows are stored in
       // slot order, so a forest slot's half-edge is its rank among the
       // forest slots (forest bits before its word, then within the word)
       const uint32_t nwd = (m + 31) / 32;
-      for (uint32_t i = tid; i < nwd; i += kBT) DC[i] = __popc(TF[i]);
+      for (uint32_t i = tid; i < nwd; i += BT) DC[i] = __popc(TF[i]);
       __syncthreads();
       const uint32_t wlast = DC[nwd - 1];
-      wg_scan_excl<kBT>(DC, (int)nwd, SC + B_WSUM);
+      wg_scan_excl<BT>(DC, (int)nwd, SC + B_WSUM);
       const uint32_t Et = DC[nwd - 1] + wlast;
-      for (uint32_t v = tid; v <= n; v += kBT) {
+      for (uint32_t v = tid; v <= n; v += BT) {
         const uint32_t k = RP[v];
         TPTR[v] = (uint16_t)(k >= m ? Et : DC[k >> 5] + __popc(TF[k >> 5] & ((1u << (k & 31)) - 1u)));
       }
-      for (uint32_t k = tid; k < m; k += kBT) {
+      for (uint32_t k = tid; k < m; k += BT) {
         const uint32_t bits = TF[k >> 5];
         if (!((bits >> (k & 31)) & 1u)) continue;
         const uint32_t h = DC[k >> 5] + __popc(bits & ((1u << (k & 31)) - 1u));
@@ -344,11 +347,11 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
         TNB[h] = COL[k];
       }
       __syncthreads();
-      for (uint32_t v = tid; v < n; v += kBT)
+      for (uint32_t v = tid; v < n; v += BT)
         for (uint32_t h = TPTR[v]; h < TPTR[v + 1]; ++h) HS[h] = (uint16_t)v;
       __syncthreads();
       uint16_t* SUCC = DDa;  // the successors, in the upper half of the pointer-jumping region
-      for (uint32_t h = tid; h < Et; h += kBT) {
+      for (uint32_t h = tid; h < Et; h += BT) {
         const uint32_t u = HS[h], w = TNB[h];
         const uint32_t tw = lower16(TNB, TPTR[w], TPTR[w + 1], u);
         TTW[h] = (uint16_t)tw;
@@ -356,11 +359,11 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
         SUCC[h] = (uint16_t)((tw + 1 == TPTR[w + 1]) ? TPTR[w] : tw + 1);
       }
       // component roots that own forest edges, in id order
-      for (uint32_t v = tid; v < n; v += kBT) DC[v] = (UF[v] == v && TPTR[v + 1] > TPTR[v]) ? 1u : 0u;
+      for (uint32_t v = tid; v < n; v += BT) DC[v] = (UF[v] == v && TPTR[v + 1] > TPTR[v]) ? 1u : 0u;
       __syncthreads();
       const uint32_t rlast = n ? DC[n - 1] : 0;
-      wg_scan_excl<kBT>(DC, (int)n, SC + B_WSUM);
-      for (uint32_t v = tid; v < n; v += kBT)
+      wg_scan_excl<BT>(DC, (int)n, SC + B_WSUM);
+      for (uint32_t v = tid; v < n; v += BT)
         if (UF[v] == v && TPTR[v + 1] > TPTR[v]) {
           RIDX[v] = (uint16_t)DC[v];
           RL[DC[v]] = (uint16_t)v;
@@ -372,7 +375,7 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
       __syncthreads();
       const uint32_t R = (uint32_t)SC[B_NR];
       // cut each component's cycle before its root's first half-edge and chain them
-      for (uint32_t i = tid; i < R; i += kBT) {
+      for (uint32_t i = tid; i < R; i += BT) {
         const uint32_t r = RL[i];
         const uint32_t last = TTW[TPTR[r + 1] - 1];  // its successor is r's first half-edge
         SUCC[last] = (i + 1 < R) ? TPTR[RL[i + 1]] : kNil;
@@ -385,14 +388,14 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
         // sums the distances
         uint32_t* PJ0 = reinterpret_cast<uint32_t*>(NXa);
         uint32_t* PJ1 = reinterpret_cast<uint32_t*>(DDa);
-        for (uint32_t h = tid; h < Et; h += kBT) {
+        for (uint32_t h = tid; h < Et; h += BT) {
           const uint32_t x = SUCC[h];
           PJ0[h] = (x << 16) | (x == kNil ? 0u : 1u);
         }
         __syncthreads();
         const int jumps = (32 - __clz((int)Et)) + 1;
         for (int it = 0; it < jumps; ++it) {
-          for (uint32_t h = tid; h < Et; h += kBT) {
+          for (uint32_t h = tid; h < Et; h += BT) {
             const uint32_t p = PJ0[h], x = p >> 16;
             if (x != kNil && x < Et) {
               const uint32_t q = PJ0[x];
@@ -414,24 +417,24 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
         __syncthreads();
         if (!SC[B_FAIL]) {
           uint16_t* RK = reinterpret_cast<uint16_t*>(PJ1);  // rank = Et - 1 - distance to the end
-          for (uint32_t h = tid; h < Et; h += kBT) {
+          for (uint32_t h = tid; h < Et; h += BT) {
             const uint32_t r = Et - 1 - (PJ0[h] & 0xffffu);
             RK[h] = (uint16_t)r;
             TOUR[r] = (uint16_t)h;
           }
           __syncthreads();
-          for (uint32_t r = tid; r < Et; r += kBT) {
+          for (uint32_t r = tid; r < Et; r += BT) {
             const uint32_t h = TOUR[r];
             DC[r] = RK[h] < RK[TTW[h]] ? 1u : 0u;
           }
           __syncthreads();
-          wg_scan_excl<kBT>(DC, (int)Et, SC + B_WSUM);  // down half-edges before each tour position
+          wg_scan_excl<BT>(DC, (int)Et, SC + B_WSUM);  // down half-edges before each tour position
           // preorder and subtree size: a down half-edge (u -> w) enters w;
           // the bridge test also takes u and the slot of (w -> u), kept in
           // the tour order's place (dead now)
           uint16_t* PU = TOUR;
           uint16_t* PTW = TOUR + N;
-          for (uint32_t h = tid; h < Et; h += kBT) {
+          for (uint32_t h = tid; h < Et; h += BT) {
             const uint32_t t = TTW[h];
             const uint32_t r = RK[h], rt = RK[t];
             if (r < rt) {
@@ -443,7 +446,7 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
               PTW[w] = TSL[t];
             }
           }
-          for (uint32_t i = tid; i < R; i += kBT) {
+          for (uint32_t i = tid; i < R; i += BT) {
             const uint32_t r = RL[i];
             const uint32_t start = RK[TPTR[r]];
             const uint32_t end = (i + 1 < R) ? RK[TPTR[RL[i + 1]]] : Et;  // one past its last half-edge
@@ -455,13 +458,13 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
 
           // 5. non-forest extremes per preorder position
           const uint32_t P = Et / 2 + R;  // vertices in components with forest edges
-          for (uint32_t v = tid; v < n; v += kBT)
+          for (uint32_t v = tid; v < n; v += BT)
             if (TPTR[v + 1] > TPTR[v]) {
               AMN[PRE[v]] = PRE[v];
               AMX[PRE[v]] = PRE[v];
             }
           __syncthreads();
-          for (uint32_t k = tid; k < m; k += kBT) {
+          for (uint32_t k = tid; k < m; k += BT) {
             if ((TF[k >> 5] >> (k & 31)) & 1u) continue;
             const uint32_t u = row_of_slot(RP, n, k), w = COL[k];
             if (TPTR[u + 1] == TPTR[u]) continue;  // a loop on a vertex without forest edges
@@ -473,7 +476,7 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
           // segments (one lane per position, a segment per block), then the
           // sparse table over the at most 32 blocks by one wavefront
           const uint32_t nb = (P + kRB - 1) / kRB;
-          for (uint32_t i = tid; i < nb * kRB; i += kBT) {
+          for (uint32_t i = tid; i < nb * kRB; i += BT) {
             const uint32_t j = i & (kRB - 1);
             const uint32_t a = i < P ? AMN[i] : 0xffffu, x = i < P ? AMX[i] : 0u;
             uint32_t pmn = a, pmx = x, smn = a, smx = x;
@@ -517,7 +520,7 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
           }
           __syncthreads();
           // the bridge test for the forest edge above every non-root vertex
-          for (uint32_t w = tid; w < n; w += kBT) {
+          for (uint32_t w = tid; w < n; w += BT) {
             const uint32_t k = PSLOT[w];
             if (TPTR[w + 1] == TPTR[w] || k == kNil) continue;
             const uint32_t l = PRE[w], r = l + SIZE[w] - 1;
@@ -556,7 +559,7 @@ __global__ __launch_bounds__(kBT, 8) void k_small_bridges(
     // 6. the graph's mask words and count
     if (out_ok) {
       const bool fail = SC[B_FAIL] != 0;
-      for (int64_t i = tid; i < nw; i += kBT) mask[mw + i] = fail ? 0u : MB[i];
+      for (int64_t i = tid; i < nw; i += BT) mask[mw + i] = fail ? 0u : MB[i];
       if (tid == 0 && counts) counts[t] = fail ? 0 : SC[B_CNT];
     }
     __syncthreads();  // the tables and SC[B_GRAPH] are rewritten by the next graph
@@ -583,13 +586,25 @@ int small_bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, const 
   if (max_vertices > kGMaxV || max_slots > kGMaxS) return ET_ESIZE;
   const uint32_t N = a64((uint32_t)std::max(max_vertices, 1)), M = a64((uint32_t)std::max(max_slots, 1));
   const uint32_t lds = blayout(N, M).total;
-  int grid = 0;
-  const int rc = persistent_grid(reinterpret_cast<const void*>(k_small_bridges), kBT, lds, T, &grid);
+  int grid = 0, lanes = kBT;
+  auto kern = k_small_bridges<kBT>;
+  int rc = persistent_grid(reinterpret_cast<const void*>(kern), lanes, lds, T, &grid);
   if (rc) return rc;
+  // More small graphs than there is room for at 1024 lanes: a small graph
+  // leaves most of them idle at every step, and its step lasts as long on a
+  // quarter, four times as many at a time. 1024 / 256 lanes, us: 1300 graphs of
+  // 2^3 to 2^8 vertices 68 / 57, 5000 of 2^8 286 / 180, 20000 of 2^3 to 2^6 716 /
+  // 278; but 500 of 2^8 43 / 57, and 5000 of 2^3 to 2^10 254 / 324.
+  if (grid < T && max_vertices <= kGSmallV && max_slots <= kGSmallS) {
+    kern = k_small_bridges<kBTSmall>;
+    lanes = kBTSmall;
+    rc = persistent_grid(reinterpret_cast<const void*>(kern), lanes, lds, T, &grid);
+    if (rc) return rc;
+  }
   ET_PROF(c, s, "k_small_bridges");
-  hipLaunchKernelGGL(k_small_bridges, dim3(grid), dim3(kBT), lds, s, row_ptr, col, voff, soff, moff, T,
-                     (int64_t)n_total, (int64_t)nnz_total, mask_words, N, M, max_vertices, max_slots, mask, counts,
-                     order, c->d_fused, c->d_status);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(lanes), lds, s, row_ptr, col, voff, soff, moff, T, (int64_t)n_total,
+                     (int64_t)nnz_total, mask_words, N, M, max_vertices, max_slots, mask, counts, order, c->d_fused,
+                     c->d_status);
   return hipGetLastError() == hipSuccess ? ET_OK : ET_EHIP;
 }
 
