@@ -788,15 +788,36 @@ __global__ __launch_bounds__(256) void k_rank_fix(const int32_t* __restrict__ su
 }
 
 // {successor, weight} pairs for the weighted walk, and the number of used
-// elements (successor other than -2)
-__global__ void k_pair_count(const int32_t* __restrict__ succ, const int32_t* __restrict__ w, int32_t L,
-                             int2* __restrict__ sw, int32_t* __restrict__ count) {
+// elements (successor other than -2). The workgroups' updates of the one
+// counter come at about 10 ns each, which bounded this kernel with one per 512
+// elements (10^6 elements 30 us): at least 4096 elements a workgroup, on short
+// lists 1024, where the lanes are too few otherwise (4 / 16 elements a lane:
+// 10^5 elements 7 / 8 us, 10^6 18 / 11).
+inline int pair_blocks(int32_t len) {
+  const int32_t per = len < (1 << 18) ? 1024 : 4096;
+  const int64_t b = ((int64_t)len + per - 1) / per;
+  return (int)(b < 1024 ? b : 1024);
+}
+
+__global__ __launch_bounds__(256) void k_pair_count(const int32_t* __restrict__ succ, const int32_t* __restrict__ w,
+                                                    int32_t L, int2* __restrict__ sw, int32_t* __restrict__ count) {
+  constexpr int kTogether = kFixTogether;
   __shared__ int32_t part[4];
   int32_t c = 0;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < L; e += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t x = succ[e];
-    sw[e] = make_int2(x, w[e]);
-    c += (x != -2);
+  for (int64_t b = (int64_t)blockIdx.x * (256 * kTogether); b < L; b += (int64_t)gridDim.x * (256 * kTogether)) {
+    int32_t x[kTogether], y[kTogether];
+#pragma unroll
+    for (int r = 0; r < kTogether; ++r) {
+      const int64_t e = b + r * 256 + threadIdx.x;
+      x[r] = e < L ? succ[e] : -2;
+      y[r] = e < L ? w[e] : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < kTogether; ++r) {
+      const int64_t e = b + r * 256 + threadIdx.x;
+      if (e < L) sw[e] = make_int2(x[r], y[r]);
+      c += (x[r] != -2);
+    }
   }
   for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
   if (__lane_id() == 0) part[threadIdx.x >> 6] = c;
@@ -1076,8 +1097,8 @@ int list_scan_generic(Ctx* c, const int32_t* succ, const int32_t* weights, int32
   hipLaunchKernelGGL(k_set_scalar, dim3(1), dim3(1), 0, s, expected, 0);
   {
     ET_PROF(c, s, "k_pair_count");
-    hipLaunchKernelGGL(k_pair_count, dim3(std::min(ceil_div(len, 256), 2048)), dim3(256), 0, s, succ, weights,
-                       len, sw, expected);
+    hipLaunchKernelGGL(k_pair_count, dim3(pair_blocks(len)), dim3(256), 0, s, succ, weights, len, sw,
+                       expected);
   }
   LRResult r;
   int rc = list_rank_core(c, sc, reinterpret_cast<const int32_t*>(sw), len, heads, nheads, false, expected, &r, s,
