@@ -1107,7 +1107,7 @@ size_t bridges_scratch_bytes(const Ctx* c, int32_t n, int32_t nnz) {
 }
 
 int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, uint32_t* mask,
-                hipStream_t s, int algo) {
+                hipStream_t s, int algo, int32_t graphs) {
   if (algo == kAlgoCK) return bridges_ck_bfs(c, row_ptr, col, n, nnz, mask, s);
   const int32_t words = (int32_t)(((int64_t)nnz + 31) >> 5);
   if (n <= 1 || nnz == 0) {  // no bridge
@@ -1172,7 +1172,7 @@ int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, i
   // 3. one list ranking, directions, preorder
   LRResult lr;
   rc = list_rank_core(c, sc, reinterpret_cast<int32_t*>(succ), L2, scal + FS_HEAD, 1, false, scal + FS_LEN, &lr, s,
-                      true);
+                      true, 0, graphs > 1 ? L2 / graphs : 0);
   if (rc) return rc;
   int2* ds = next;  // the list pointers are dead
   {

@@ -197,7 +197,7 @@ int bridges_batch_run(Ctx* c, const int32_t* rows, const int32_t* col, const int
     hipLaunchKernelGGL(k_gb_cols, dim3(ceil_div(nnz, (int64_t)kB * kPerLane)), dim3(kB), 0, s, col, voff, soff, T, V,
                        nnz, col_g, c->d_status);
   }
-  rc = bridges_run(c, row_g, col_g, V, nnz, umask, s, kAlgoTV);
+  rc = bridges_run(c, row_g, col_g, V, nnz, umask, s, kAlgoTV, T);
   if (rc) return rc;
   if (counts) hipLaunchKernelGGL(k_gb_zero, dim3(ceil_div(T, kB)), dim3(kB), 0, s, counts, T);
   if (mask_words > 0) {

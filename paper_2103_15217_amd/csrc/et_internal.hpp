@@ -354,8 +354,9 @@ int tree_build_edges(Ctx* c, et_tree* t, const int32_t* eu, const int32_t* ev, i
 // high), kAlgoCK = Chaitanya-Kothapalli marking on a BFS forest, kAlgoHybrid
 // = marking on the connectivity forest rooted by the Euler tour.
 enum { kAlgoTV = 0, kAlgoCK = 1, kAlgoHybrid = 2 };
+// graphs: of how many graphs, one after the other, this one is the union
 int bridges_run(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, uint32_t* mask,
-                hipStream_t s, int algo);
+                hipStream_t s, int algo, int32_t graphs = 1);
 int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t n, int32_t nnz, int32_t* cc,
                     int32_t* scalars, int4* erec, int32_t* first, int32_t* next, uint32_t* mask, int64_t* count,
                     int32_t* work, hipStream_t s);
