@@ -41,17 +41,18 @@ ALG_BYTES = {
     "k_lca": (76, "query", lambda w: w["q"]),
     # first hooking round: row pointers (8 B) and up to two columns (8 B) per vertex
     "k_hook_sample": (16, "vertex", lambda w: w["graph_n"]),
-    # path tops: 16-B record, parent and the parent's gathered inlabel read; about half the
-    # nodes are tops and write an 8-B head entry and a 4-B parent-path label
-    "k_head": (30, "node", lambda w: w["n"]),
+    # path tops: inlabel, parent and the parent's gathered inlabel read; about half the nodes
+    # are tops, read their depth and write an 8-B head entry and a 4-B parent-path label
+    "k_head": (20, "node", lambda w: w["n"]),
     # successor: parent and child read per grouped position, succ(2c+1) and (at the first
     # child) succ(2p) written
     "k_succ": (14, "node", lambda w: w["n"]),
-    # ascendant into the node record: inlabel read, label ascendant gathered, 4 B written
-    "k_asc": (12, "node", lambda w: w["n"]),
+    # node records: inlabel, preorder and the rank of the entering half-edge (or the depth)
+    # read, label ascendant gathered, 16 B written
+    "k_record": (32, "node", lambda w: w["n"]),
     # node statistics: the 8-B records of 2c and 2c+1 and their two 8-B sublist offsets
-    # read; rank pair (8 B), pre, size, inlabel (4 B each) and the 16-B node record written
-    "k_node": (68, "node", lambda w: w["n"]),
+    # read; rank pair (8 B), pre, size, inlabel and depth (4 B each) written
+    "k_node": (56, "node", lambda w: w["n"]),
     # non-forest min/max: column (4 B) + gathered preorder (4 B) per slot
     "k_minmax": (8, "CSR slot", lambda w: w["graph_nnz"]),
     # radix passes: key + value read and written
@@ -269,7 +270,7 @@ def main():
     # list ranking and LCA queries, and the largest kernels of the build and
     # of the bridges, from the profiled steps
     kernel_rooflines = {}
-    for k in ("k_walk1<true>", "k_lca", "k_node", "k_head", "k_succ", "k_asc", "k_minmax"):
+    for k in ("k_walk1<true>", "k_lca", "k_node", "k_head", "k_succ", "k_record", "k_minmax"):
         if k in kernels and kernels[k][0] > 0:
             kernel_rooflines[k] = kernel_roofline(k, kernels[k][1] / kernels[k][0], kernels[k][0] / prof_steps,
                                                   work, launch["single"])
