@@ -1102,7 +1102,7 @@ size_t bridges_scratch_bytes(const Ctx* c, int32_t n, int32_t nnz) {
   size_t b = 6 * scratch_block<int32_t>(N) + 4 * scratch_block<int2>(N) + 2 * scratch_block<int4>(N) +
              2 * scratch_block<uint32_t>(N << (rlog - 5)) + 2 * scratch_block<int32_t>(levels * nb) +
              scratch_block<int32_t>(8);
-  b += list_rank_plan_bytes(c, (int32_t)(2 * N), 1, 0);
+  b += list_rank_plan_bytes(c, (int32_t)(2 * N), 1, 0, true);  // (a union's, the larger one)
   return b + scan_scratch_bytes((int64_t)(2 * N));
 }
 

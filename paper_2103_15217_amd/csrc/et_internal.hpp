@@ -388,7 +388,7 @@ int list_rank_generic(Ctx* c, const int32_t* succ, int32_t len, const int32_t* h
 // the size asked for.)
 size_t scan_scratch_bytes(int64_t n);
 size_t group_by_parent_scratch_bytes(int32_t n);
-size_t list_rank_plan_bytes(const Ctx* c, int32_t len, int32_t nheads, int weighted);
+size_t list_rank_plan_bytes(const Ctx* c, int32_t len, int32_t nheads, int weighted, bool local);
 size_t tree_build_scratch_bytes(const Ctx* c, int32_t n, int32_t batch);
 size_t bridges_scratch_bytes(const Ctx* c, int32_t n, int32_t nnz);
 size_t bridges_batch_scratch_bytes(const Ctx* c, int32_t n_graphs, int32_t n_total, int32_t nnz_total);

@@ -856,7 +856,9 @@ struct LrPlan {
   std::vector<LrLevel> lv;
 };
 
-static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weighted, LrPlan* pl) {
+constexpr int32_t kLongList = 24000000;
+
+static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weighted, bool local, LrPlan* pl) {
   const int32_t lds_max = H <= kLdsHeads ? kLdsMax : kLdsMaxHeads;
   // One workgroup ranks a short list by itself, one launch in place of three.
   // Tree builds by this / by level 1 and a final level: 60 / 68 us at 2000
@@ -874,7 +876,11 @@ static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weight
   // walk is bound by its dependent steps rather than by line fetches, so the
   // spacing drops by half per factor 4 of length (2^24 -> 16, 2^22 -> 8,
   // 2^20 -> 4), down to 4; the context's value is the largest spacing used.
-  pl->ks1 = std::min(c->lr.k1_log2, std::max(2, (floor_log2(L) - 15) / 2));
+  // From 24M elements on it is twice that: the sublists' offsets, which every
+  // element gathers, are then half as many (list of 2^25 elements, spacing 16 /
+  // 32: 1687 / 1614 us; tree of 2^24 nodes 3130 / 3077, of 2^25 7379 / 7143; but
+  // 2^23 1537 / 1576, and a batch of 2^25 local elements 3899 / 4070).
+  pl->ks1 = std::min(c->lr.k1_log2, std::max(2, (floor_log2(L) - 15) / 2)) + (!local && L >= kLongList ? 1 : 0);
   pl->S1 = (int32_t)(((int64_t)L + (1 << pl->ks1) - 1) >> pl->ks1);
   pl->cont_max = L / kCap + H + 64;
   pl->T1 = pl->S1 + H + pl->cont_max;
@@ -1017,7 +1023,7 @@ int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const 
                    int32_t nheads, bool tree_weights, const int32_t* expected_reach, LRResult* out,
                    hipStream_t s, bool empty_head_ok, int weighted, int32_t local_len) {
   LrPlan pl;
-  list_rank_plan(c, sc, len, nheads, weighted, &pl);
+  list_rank_plan(c, sc, len, nheads, weighted, local_len > 0, &pl);
   if (sc.failed) return ET_ENOMEM;
   const int rc = list_rank_launch(c, pl, succ, len, heads, nheads, tree_weights, expected_reach, s, empty_head_ok,
                                   weighted, local_len);
@@ -1033,7 +1039,7 @@ int list_rank_core(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const 
 static int list_rank_with(Ctx* c, Scratch& sc, const int32_t* succ, int32_t len, const int32_t* heads,
                           int32_t nheads, int32_t* rank, hipStream_t s) {
   LrPlan pl;
-  list_rank_plan(c, sc, len, nheads, 0, &pl);
+  list_rank_plan(c, sc, len, nheads, 0, false, &pl);
   if (sc.failed || sc.counting) return sc.failed ? ET_ENOMEM : ET_OK;
   if (pl.direct) {  // sees every element itself: nothing to count, no records to add up
     const int ks = rank_lds_ks(len);
@@ -1062,13 +1068,13 @@ int list_rank_generic(Ctx* c, const int32_t* succ, int32_t len, const int32_t* h
   return list_rank_with(c, sc, succ, len, heads, nheads, rank, s);
 }
 
-size_t list_rank_plan_bytes(const Ctx* c, int32_t len, int32_t nheads, int weighted) {
+size_t list_rank_plan_bytes(const Ctx* c, int32_t len, int32_t nheads, int weighted, bool local) {
   if (len == 0) return 0;
   Ctx shape;  // the plan reads only the launch shape
   shape.lr = c ? c->lr : LrShape{};
   Scratch count(&shape, nullptr, nullptr, 0);
   LrPlan pl;
-  list_rank_plan(&shape, count, len, nheads, weighted, &pl);
+  list_rank_plan(&shape, count, len, nheads, weighted, local, &pl);
   // as pool blocks: every block, the last one too, takes whole 256-byte units
   return (count.used + 255) & ~(size_t)255;
 }

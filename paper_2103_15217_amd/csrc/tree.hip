@@ -601,7 +601,7 @@ size_t tree_build_scratch_bytes(const Ctx* c, int32_t n, int32_t batch) {
   if (n <= 1) return b;
   b += scratch_block<uint32_t>(2 * (size_t)n + 2) + scratch_block<uint32_t>((size_t)n) +
        scratch_block<int32_t>(kPartRanges);
-  return b + group_by_parent_scratch_bytes(n) + list_rank_plan_bytes(c, 2 * n, 1, 0);
+  return b + group_by_parent_scratch_bytes(n) + list_rank_plan_bytes(c, 2 * n, 1, 0, batch != 0);
 }
 
 // Nodes from which the successors of one tree are stored in two passes. Up to
