@@ -97,7 +97,8 @@ int et_ctx_status_bits(et_ctx* ctx, hipStream_t s, uint32_t* h_bits);
  *   "lr_per_wave1"  level 1: sublists owned by one wavefront at most
  *                   (64..65536, default 256); fewer when that would leave
  *                   under 4096 wavefronts, never under 64
- *   "lr_kn_log2"    upper levels: one splitter per 2^v elements (1..10, default 3)
+ *   "lr_kn_log2"    upper levels: one splitter per 2^v elements at most (1..10,
+ *                   default 3)
  *   "lr_per_waven"  upper levels: sublists per wavefront at most (64..65536,
  *                   default 128), reduced like lr_per_wave1
  *   "rmq_block_log2"  range-minimum blocks of 2^v positions for the bridge
