@@ -857,6 +857,7 @@ struct LrPlan {
 };
 
 constexpr int32_t kLongList = 24000000;
+constexpr int kLongSpacing = 5;
 constexpr int32_t kShortLevel = 1 << 21;
 
 static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weighted, bool local, LrPlan* pl) {
@@ -877,11 +878,13 @@ static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weight
   // walk is bound by its dependent steps rather than by line fetches, so the
   // spacing drops by half per factor 4 of length (2^24 -> 16, 2^22 -> 8,
   // 2^20 -> 4), down to 4; the context's value is the largest spacing used.
-  // From 24M elements on it is twice that: the sublists' offsets, which every
-  // element gathers, are then half as many (list of 2^25 elements, spacing 16 /
-  // 32: 1687 / 1614 us; tree of 2^24 nodes 3130 / 3077, of 2^25 7379 / 7143; but
+  // From 24M elements on a spacing below 32 is doubled: the sublists' offsets,
+  // which every element gathers, are then half as many (list of 2^25 elements,
+  // spacing 16 / 32 / 64: 1687 / 1614 / 1808 us; trees of 2^24 nodes of three
+  // shapes 3136 / 3061 / 3130, 3155 / 3102 / 3217 and 3045 / 2958 / 3113; but
   // 2^23 1537 / 1576, and a batch of 2^25 local elements 3899 / 4070).
-  pl->ks1 = std::min(c->lr.k1_log2, std::max(2, (floor_log2(L) - 15) / 2)) + (!local && L >= kLongList ? 1 : 0);
+  pl->ks1 = std::min(c->lr.k1_log2, std::max(2, (floor_log2(L) - 15) / 2));
+  if (!local && L >= kLongList && pl->ks1 < kLongSpacing) ++pl->ks1;
   pl->S1 = (int32_t)(((int64_t)L + (1 << pl->ks1) - 1) >> pl->ks1);
   pl->cont_max = L / kCap + H + 64;
   pl->T1 = pl->S1 + H + pl->cont_max;
