@@ -462,7 +462,9 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
         ad = wadd(ad, d);
         if (nx >= kEnd) {
           if (nx & kSplit) {
-            to[k] = (int32_t)(nx & (kSplit - 1u)) >> ks;
+            const uint32_t x = nx & (kSplit - 1u);
+            if (NXT[x] == kUnused) bad = true;  // (the code of an unused slot never changes)
+            to[k] = (int32_t)x >> ks;
             PRED[to[k]] = (uint16_t)s;
           }
           break;
@@ -597,7 +599,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_final_lds(const int4* __restr
     top[e] = e;
     if (used[k] && r.x >= 0) {
       if (r.x < T) pred[r.x] = e;
-      else bad = true;
+      if (r.x >= T || rec[r.x].x == -3) bad = true;
     }
   }
   if (bad) flag(status, ST_BAD_SUCC);
