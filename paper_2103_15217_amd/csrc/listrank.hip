@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
     PRED[s] = (uint16_t)kNone;
     TOP[s] = (uint16_t)s;
   }
-  for (int i = t; i <= hw; i += kFinalThreads) HB[i] = 0u;
+  for (int i = t; i <= hw + 2; i += kFinalThreads) HB[i] = 0u;
 #pragma unroll 4
   for (int32_t e = t; e < T; e += kFinalThreads) {
     int32_t nx, l = 1, d = 0;
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
     if (kDn) DN[e] = d;
   }
   __syncthreads();
-  int32_t wl[kFinalSub], wd[kFinalSub], to[kFinalSub];
+  int32_t wl[kFinalSub], wd[kFinalSub], to[kFinalSub], passed = 0;
 #pragma unroll
   for (int k = 0; k < kFinalSub; ++k) {
     wl[k] = wd[k] = 0;
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
       }
     }
     if (e >= 0) {
-      int32_t al = 0, ad = 0;
+      int32_t al = 0, ad = 0, after = -1;
       for (int32_t step = 0;; ++step) {
         const uint32_t nx = NXT[e];
         if ((nx & kWalked) || nx == kUnused || step >= T) {  // a second way into an element, or into no element
@@ -454,6 +454,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
           break;
         }
         NXT[e] = (uint16_t)(kWalked | (uint32_t)s);
+        ++passed;
         const int32_t l = kLen ? LEN[e] : 1;
         const int32_t d = kDn ? DN[e] : (IN == IN_TREE ? (int32_t)((e & 1) == 0) : 0);
         LEN[e] = al;
@@ -461,15 +462,15 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
         al += l;
         ad = wadd(ad, d);
         if (nx >= kEnd) {
-          if (nx & kSplit) {
-            const uint32_t x = nx & (kSplit - 1u);
-            if (NXT[x] == kUnused) bad = true;  // (the code of an unused slot never changes)
-            to[k] = (int32_t)x >> ks;
-            PRED[to[k]] = (uint16_t)s;
-          }
+          if (nx & kSplit) after = (int32_t)(nx & (kSplit - 1u));
           break;
         }
         e = (int32_t)nx;
+      }
+      if (after >= 0) {  // (out of the loop, whose lanes end one by one)
+        if (NXT[after] == kUnused) bad = true;  // (the code of an unused slot never changes)
+        to[k] = after >> ks;
+        PRED[to[k]] = (uint16_t)s;
       }
       wl[k] = al;
       wd[k] = ad;
@@ -533,11 +534,18 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
     const int32_t s = t + k * kFinalThreads;
     if (s < SM) PRED[s] = reached[k];
   }
-  for (int dd = 32; dd >= 1; dd >>= 1) mine += __shfl_xor(mine, dd, 64);
-  if (__lane_id() == 0 && mine) atomicAdd(&HB[hw], (uint32_t)mine);  // (the slot after the bits)
+  for (int dd = 32; dd >= 1; dd >>= 1) {
+    mine += __shfl_xor(mine, dd, 64);
+    passed += __shfl_xor(passed, dd, 64);
+  }
+  if (__lane_id() == 0) {  // (the slots after the bits)
+    if (mine) atomicAdd(&HB[hw], (uint32_t)mine);
+    if (passed) atomicAdd(&HB[hw + 1], (uint32_t)passed);
+  }
   __syncthreads();
   if (t == 0 && reached_out) *reached_out = (int32_t)HB[hw];
   bool unreached = t == 0 && expected && (int32_t)HB[hw] != *expected;
+  int32_t walked = 0;
 #pragma unroll 4
   for (int32_t e = t; e < T; e += kFinalThreads) {
     const uint32_t c = NXT[e];  // kWalked | sublist, or never walked
@@ -547,6 +555,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
     }
     int2 o = make_int2(0, 0);
     if (c & kWalked) {
+      ++walked;
       const uint32_t s = c & (kWalked - 1u);
       o = make_int2(ACL[s] + LEN[e], IN != IN_SUCC ? wadd(ACD[s], DN[e]) : 0);
       if (!PRED[s]) unreached = true;
@@ -566,6 +575,12 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
           make_ulonglong2((uint64_t)(uint32_t)e, (uint64_t)(uint32_t)in[2 * e + 1]);
   }
   if (unreached) flag(status, ST_UNREACHED);
+  // Two lanes may enter a shared element before either has marked it; then
+  // they passed more elements than are marked.
+  for (int dd = 32; dd >= 1; dd >>= 1) walked += __shfl_xor(walked, dd, 64);
+  if (__lane_id() == 0 && walked) atomicAdd(&HB[hw + 2], (uint32_t)walked);
+  __syncthreads();
+  if (t == 0 && HB[hw + 1] != HB[hw + 2]) flag(status, ST_BAD_SUCC);
 }
 
 // The final level of lists with many heads (more sublists than the kernel
@@ -601,6 +616,14 @@ __global__ __launch_bounds__(kFinalThreads) void k_final_lds(const int4* __restr
       if (r.x < T) pred[r.x] = e;
       if (r.x >= T || rec[r.x].x == -3) bad = true;
     }
+  }
+  __syncthreads();
+  // two elements that lead into one: the other one's link is gone
+  for (int k = 0; k < kFinalPer; ++k) {
+    const int e = t + k * kFinalThreads;
+    if (!used[k]) continue;
+    const int32_t x = rec[e].x;
+    if (x >= 0 && x < T && pred[x] != e) bad = true;
   }
   if (bad) flag(status, ST_BAD_SUCC);
   __syncthreads();

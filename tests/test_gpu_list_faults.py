@@ -48,3 +48,46 @@ def test_last_element_names_an_unused_slot(L, nlists):
         bad = succ.copy()
         bad[parts[rng.integers(len(parts))][-1]] = slot
         assert _flagged(bad, heads), (L, nlists, int(slot))
+
+
+@pytest.mark.parametrize("L", [40, 1025, 3000, 8000, 8193, 30000])
+def test_one_element_list_named_twice(L):
+    rng = np.random.default_rng(L)
+    for gap in (1, 64, 65, 300):  # lanes of one wavefront, of two, of two workgroup rounds
+        for _ in range(6):
+            order = rng.permutation(L)
+            succ = np.full(L, -2, dtype=np.int32)
+            n = min(L // 2, 900)
+            succ[order[:n]] = -1
+            heads = order[:n].astype(np.int32)
+            at = int(rng.integers(0, n))
+            assert _flagged(succ, np.insert(heads, min(n, at + gap), heads[at])), (L, gap, at)
+
+
+@pytest.mark.parametrize("L", [40, 1025, 3000, 8000, 8193, 30000])
+@pytest.mark.parametrize("depth", [1, 2, 5])
+def test_two_heads_share_a_tail(L, depth):
+    rng = np.random.default_rng(L + depth)
+    n = min(L // (3 * depth + 1), 400)  # pairs of lists that meet in one element
+    for wrong in range(0, n, max(1, n // 24)):
+        order = rng.permutation(L)
+        succ = np.full(L, -2, dtype=np.int32)
+        heads, at = [], 0
+        for i in range(n):
+            a, b = order[at:at + depth], order[at + depth:at + 2 * depth]
+            tail = order[at + 2 * depth:at + 2 * depth + 1]
+            at += 2 * depth + 1
+            for part, meets in ((a, True), (b, i == wrong)):
+                succ[part[:-1]] = part[1:]
+                succ[part[-1]] = tail[0] if meets else -1
+                heads.append(part[0])
+            succ[tail] = -1
+        assert _flagged(succ, np.array(heads, dtype=np.int32)), (L, depth, wrong)
+
+
+@pytest.mark.parametrize("L,nlists", [(9000, 2000), (30000, 1500), (30000, 12000)])
+def test_many_heads_name_a_list_twice(L, nlists):
+    rng = np.random.default_rng(nlists)
+    succ, heads, _ = _chain(rng.permutation(L), nlists, L)
+    for at in range(0, nlists, nlists // 16):
+        assert _flagged(succ, np.append(heads, heads[at])), (L, nlists, at)
