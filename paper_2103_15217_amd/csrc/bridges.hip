@@ -6,12 +6,11 @@
 //     different trees, so its edge is a forest edge. A root is hooked at most
 //     once, so the hooked root's id numbers the edge: half-edges 2e and 2e+1
 //     are its two directions, twins by numbering. Parallel copies of an edge
-//     are never forest edges and self-loops are skipped. Every vertex first
-//     hangs below its first neighbour, if that has a smaller id, and hooks
-//     its second; then the most frequent root of a sample names the big
-//     component, and only rows of vertices outside it hook all their edges
-//     (an edge inside the big component joins nothing new). Small sparse
-//     graphs skip the sampling.
+//     are never forest edges and self-loops are skipped. Every vertex is
+//     linked along its first edge and hooks its second; then the most
+//     frequent root of a sample names the big component, and only rows of
+//     vertices outside it hook all their edges (an edge inside the big
+//     component joins nothing new).
 //  2. Euler tour of the forest as the paper's DCEL (Section 2.1): succ(h) =
 //     next(twin(h)), next() cyclic over the half-edges that leave a vertex.
 //     Any cyclic order gives a tour and the bridges do not depend on it, so
@@ -40,6 +39,7 @@ namespace {
 
 constexpr int kB = 256;
 constexpr int kRowsPerBlock = 256;
+constexpr int32_t kTinySlots = 1 << 13;         // slots up to which a sparse graph hooks all its edges at once
 constexpr int32_t kLabelNodes = (1 << 20) + 1;  // vertices from which k_hook_rest gathers labels
 constexpr int kMaxGrid = 1 << 20;  // workgroups of a grid-stride launch (a dispatch holds < 2^32 work-items)
 
@@ -144,14 +144,18 @@ __device__ int32_t twin_slot(const int32_t* __restrict__ row_ptr, const int32_t*
 
 __device__ __forceinline__ int32_t clampi(int32_t x, int32_t lo, int32_t hi) { return min(max(x, lo), hi); }
 
-// Start of a forest, and its first round of links: a vertex whose first
-// neighbour has a smaller id hangs below it. Every vertex decides for itself
-// and ids strictly decrease upwards, so all these links are edges of one
-// forest and need no compare-and-swap (a device-scope one per vertex, at 24
-// G/s, and its dependent climb made this round 316 us at 2^22 vertices and
-// 2^25 edges; with plain stores it takes 81 us). Only local minima (smaller than every
-// neighbour) stay roots. row_ptr must be monotone from 0 to nnz, anything
-// else is flagged.
+// Start of a forest, and its first round of links, one for the first neighbour
+// of every vertex. A vertex whose first neighbour w has a smaller id hangs
+// below it. A local minimum v hangs below the first neighbour x of its first
+// neighbour w, if x < v: w hangs below x by its own link, so the edge {v, w}
+// joins v's tree to that one (and if x is v, w hangs below v). Every vertex
+// decides for itself and ids strictly decrease upwards, so all these links are
+// edges of one forest and need no compare-and-swap (a device-scope one per
+// vertex, at 24 G/s, and its dependent climb made this round 316 us at 2^22
+// vertices and 2^25 edges; with plain stores it takes 81 us). The trees are
+// chains as long as the graph where ids follow its shape, which a later link
+// would climb step by step: a full compression comes before any. row_ptr must
+// be monotone from 0 to nnz, anything else is flagged.
 // EDGES: keep the forest: a linked edge's record {u, w, slot (u, w), -} and
 // its half-edge out of u as u's list so far. Also clears the forest's scalars
 // and, where given, the mask and the bridge count.
@@ -178,20 +182,26 @@ __global__ void k_forest_init(const int32_t* __restrict__ row_ptr, const int32_t
   if (v == 0 && a0 != 0) bad = true;
   if (v == n - 1 && b0 != nnz) bad = true;
   const int32_t a = clampi(a0, 0, nnz), b = clampi(b0, a, nnz);
-  int32_t w = (int32_t)v;
-  if (a < b) {  // rows are sorted: no later slot has a smaller neighbour
-    w = col[a];
+  int32_t k = a, w = (int32_t)v, up = (int32_t)v;
+  while (k < b && (w = col[k]) == (int32_t)v) ++k;  // self-loops
+  // rows are sorted: no later slot has a smaller neighbour
+  if (k < b) {
     if ((uint32_t)w >= (uint32_t)n) {
       bad = true;
-      w = (int32_t)v;
+    } else if (w < (int32_t)v) {
+      up = w;
+    } else {
+      const int32_t wa = clampi(row_ptr[w], 0, nnz), wb = clampi(row_ptr[w + 1], wa, nnz);
+      const int32_t x = wa < wb ? col[wa] : (int32_t)v;
+      if (x >= 0 && x < (int32_t)v) up = x;
     }
   }
-  const bool link = w < (int32_t)v;
-  cc[v] = link ? w : (int32_t)v;
+  const bool link = up != (int32_t)v;
+  cc[v] = up;
   if (EDGES) {
     first[v] = link ? (int32_t)(2 * v) : -1;
     if (link) {
-      erec[v] = make_int4((int32_t)v, w, a, -1);
+      erec[v] = make_int4((int32_t)v, w, k, -1);
       next[2 * v] = -1;
     }
   }
@@ -209,14 +219,11 @@ __device__ __forceinline__ int row_of(const int32_t* rp_lds, int cnt, int32_t k)
   return lo;
 }
 
-// Second round: every vertex hooks its second distinct neighbour, and one
-// whose first is larger than itself (no link in the first round) that one
-// too. Both rounds end with a full path compression.
+// Second round: every vertex hooks its second distinct neighbour. Both rounds
+// end with a full path compression.
 // EDGES: only the lane of u touches u's list here, so the insertion of the
 // half-edge out of u needs no atomics; those out of the other ends follow in
 // k_link_in.
-constexpr int kSample = 2;
-
 template <bool EDGES>
 __global__ void k_hook_sample(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int32_t n,
                               int32_t nnz, int32_t* cc, int4* __restrict__ erec, int32_t* __restrict__ first,
@@ -226,14 +233,14 @@ __global__ void k_hook_sample(const int32_t* __restrict__ row_ptr, const int32_t
   const int32_t a = clampi(row_ptr[u], 0, nnz), b = clampi(row_ptr[u + 1], a, nnz);
   bool bad = false, over = false;
   int taken = 0;
-  for (int32_t k = a; k < b && taken < kSample; ++k) {
+  for (int32_t k = a; k < b && taken < 2; ++k) {
     const int32_t w = col[k];
     if ((uint32_t)w >= (uint32_t)n) {
       bad = true;
       continue;
     }
     if (w == u || (k > a && col[k - 1] == w)) continue;  // self-loop or a parallel copy
-    if (taken++ == 0 && w < u && k == a) continue;       // linked in the first round
+    if (taken++ == 0) continue;                          // the first round's
     const int32_t e = cc_hook(cc, (int32_t)u, w, -1, &over);
     if (EDGES && e >= 0) {
       erec[e] = make_int4((int32_t)u, w, k, -1);
@@ -358,7 +365,7 @@ __global__ __launch_bounds__(kB) void k_cc_compress(int32_t* cc, int32_t n, cons
 // already inside one tree; any other edge is seen from an endpoint outside.
 // The lanes of one row run side by side here, so the list insertion is an
 // exchange.
-// Sampled (ALL false): a workgroup closes up its rows that are left and deals
+// A workgroup closes up its rows that are left and deals
 // their slots to the lanes, PER neighbouring ones at a time. Nearly all slots
 // are inside one tree; bound by the gathers that find this out: of the label
 // where there are labels (a byte a vertex, so that the table of a graph of
@@ -366,7 +373,7 @@ __global__ __launch_bounds__(kB) void k_cc_compress(int32_t* cc, int32_t n, cons
 // 2^26 slots in 513 components 433 us with labels, 675 without; a connected
 // graph of 2^21 vertices and 2^25 slots 16 us (67 when the slots of all rows
 // were dealt out and dropped one by one).
-// ALL: no sampling came before; every row and slot goes to the hook.
+// ALL: no second round and no big component came before; every row is left.
 template <bool EDGES, bool ALL, int PER>
 __global__ __launch_bounds__(kB) void k_hook_rest(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                                                  int32_t n, int32_t nnz, int32_t* cc, const int32_t* __restrict__ sc,
@@ -389,13 +396,10 @@ __global__ __launch_bounds__(kB) void k_hook_rest(const int32_t* __restrict__ ro
     a = row_ptr[r0 + t];
     b = row_ptr[r0 + t + 1];
     bad = a < 0 || a > b || b > nnz;
-    keep = a < b;
-    if (!ALL) {
-      const int32_t root = cc_find(cc, r0 + t);
-      mine = named ? (int32_t)label[r0 + t] : kLabelMax;
-      if (mine == kLabelMax) mine = -1 - root;
-      keep = keep && root != big;
-    }
+    const int32_t root = cc_find(cc, r0 + t);
+    mine = named ? (int32_t)label[r0 + t] : kLabelMax;
+    if (mine == kLabelMax) mine = -1 - root;
+    keep = a < b && root != big;
   }
   if (__syncthreads_or(bad)) return;  // flagged at the start of the forest
   const uint64_t kept = __ballot(keep);
@@ -446,18 +450,16 @@ __global__ __launch_bounds__(kB) void k_hook_rest(const int32_t* __restrict__ ro
         w[i] = 0;
       }
     }
-    if (!ALL) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i) other[i] = named ? (int32_t)label[w[i]] : -1 - ldc(cc + w[i]);
-      if (named) {
+    for (int i = 0; i < PER; ++i) other[i] = named ? (int32_t)label[w[i]] : -1 - ldc(cc + w[i]);
+    if (named) {
 #pragma unroll
-        for (int i = 0; i < PER; ++i)
-          if (other[i] == kLabelMax) other[i] = -1 - ldc(cc + w[i]);
-      }
+      for (int i = 0; i < PER; ++i)
+        if (other[i] == kLabelMax) other[i] = -1 - ldc(cc + w[i]);
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      if (k[i] < 0 || (!ALL && other[i] == tree[row[i]])) continue;
+      if (k[i] < 0 || other[i] == tree[row[i]]) continue;
       const int32_t u = vert[row[i]];
       if (w[i] == u || (k[i] > slot[row[i]] && col[k[i] - 1] == w[i])) continue;
       const int32_t e = cc_hook(cc, u, w[i], big, &over);
@@ -1042,22 +1044,13 @@ int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t 
     hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, erec, first, next, sc, mask,
                        words, count, c->d_status);
   }
-  // Sparse graphs that are tiny (bound by launches, and the sampling and the
-  // pick are four) or of middling size hook all their edges at once; between
-  // them and above, or with longer rows, the hooks of all rows meet at too few
-  // roots. Whole call without / with sampling, in us, at 8 slots a vertex: 59 /
-  // 74 (500 vertices), 80 / 88 (2000), 126 / 112 (5000), 160 / 150 (20000), 192
-  // / 184 (50000), 233 / 233 (10^5), 288 / 301 (2 * 10^5), 391 / 395 (4 * 10^5);
-  // at 16 slots: 84 / 78 (1000), 139 / 111 (5000), 313 / 318 (2 * 10^5), 434 /
-  // 423 (4 * 10^5).
-  const bool sample = nnz > 8 * (int64_t)n || (nnz > (1 << 14) && n < (1 << 16)) || n >= (1 << 19);
   // Labels where the parents (4 bytes a vertex) are more than an XCD's 4 MiB
   // L2 holds. Whole call without / with them, us: 2^20 vertices 870 / 885 (4
   // slots a vertex, connected), 949 / 939 (16), 951 / 952 (16, many
   // components); 2^21 1332 / 1330, 1431 / 1448, 1609 / 1575; 2^22 2287 / 2281,
   // 3088 / 2872, 3362 / 3134; 2^23 4210 / 4208, 5737 / 5674, 6842 / 6860 (there
   // too many components to name). They cost one kernel's climb and count, 10 us.
-  const bool labels = sample && n >= kLabelNodes;
+  const bool labels = nnz > kTinySlots && n >= kLabelNodes;
   int32_t* table = labels ? work : nullptr;
   uint8_t* label = reinterpret_cast<uint8_t*>(work + kLabelMax + 1);
   const auto compress = [&](bool named) {
@@ -1065,8 +1058,15 @@ int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t 
     const auto kern = named ? k_cc_compress<true> : k_cc_compress<false>;
     hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, cc, n, sc, table, label);
   };
+  compress(false);
+  // A tiny sparse graph is bound by its launches, and the second round, its
+  // compression and the pick are three. Whole call without / with them, us: at 8
+  // slots a vertex 78 / 86 (200 vertices), 94 / 95 (500), 101 / 102 (1000), 122 /
+  // 111 (2000); vertices joined to the next ones by id 90 / 102 (1000) and 154 /
+  // 123 (2000); cycles 85 / 98 (1000), 119 / 130 (4000). Beyond, and with longer
+  // rows, the hooks of all rows meet at too few roots.
+  const bool sample = nnz > kTinySlots || nnz > 8 * (int64_t)n;
   if (sample) {
-    compress(false);
     {
       ET_PROF(c, s, "k_hook_sample");
       const auto kern = edges ? k_hook_sample<true> : k_hook_sample<false>;
@@ -1081,9 +1081,9 @@ int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t 
   }
   {
     ET_PROF(c, s, "k_hook_rest");
-    const auto kern = !sample                  ? (edges ? k_hook_rest<true, true, 1> : k_hook_rest<false, true, 1>)
+    const auto kern = !sample                 ? (edges ? k_hook_rest<true, true, 1> : k_hook_rest<false, true, 1>)
                       : rows == kRowsPerBlock ? (edges ? k_hook_rest<true, false, 4> : k_hook_rest<false, false, 4>)
-                                               : (edges ? k_hook_rest<true, false, 1> : k_hook_rest<false, false, 1>);
+                                              : (edges ? k_hook_rest<true, false, 1> : k_hook_rest<false, false, 1>);
     hipLaunchKernelGGL(kern, dim3(grows), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, sc, label, rows, erec, first,
                        next, c->d_status);
   }
