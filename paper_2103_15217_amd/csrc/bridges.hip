@@ -260,13 +260,13 @@ constexpr int kBigSample = 1024;
 constexpr int kLabelMax = 255;                             // labels; also "none of them"
 constexpr int kLabelRuns = kBigSample / (kLabelMax + 1);  // so many samples and they fit, but for one
 
-__global__ __launch_bounds__(kBigSample) void k_big_component(int32_t* cc, int32_t n, int32_t* __restrict__ sc,
+__global__ __launch_bounds__(kBigSample) void k_big_component(const int32_t* __restrict__ cc, int32_t n, int32_t* __restrict__ sc,
                                                              int32_t* __restrict__ table) {
   __shared__ int32_t r[kBigSample];
   __shared__ int32_t best, best_count, in, all[kLabelRuns], wsum[kLabelRuns][kBigSample / 64];
   const int t = threadIdx.x;
   const uint32_t v = mix32(0x2545f491u + (uint32_t)t) % (uint32_t)n;
-  r[t] = cc_find(cc, (int32_t)v);
+  r[t] = cc[v];
   if (t == 0) {
     best = INT32_MAX;
     best_count = 0;
@@ -1049,7 +1049,7 @@ int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t 
   // slots a vertex, connected), 949 / 939 (16), 951 / 952 (16, many
   // components); 2^21 1332 / 1330, 1431 / 1448, 1609 / 1575; 2^22 2287 / 2281,
   // 3088 / 2872, 3362 / 3134; 2^23 4210 / 4208, 5737 / 5674, 6842 / 6860 (there
-  // too many components to name). They cost one kernel's climb and count, 10 us.
+  // too many components to name). They cost one more pass over the parents.
   const bool labels = nnz > kTinySlots && n >= kLabelNodes;
   int32_t* table = labels ? work : nullptr;
   uint8_t* label = reinterpret_cast<uint8_t*>(work + kLabelMax + 1);
@@ -1072,7 +1072,7 @@ int spanning_forest(Ctx* c, const int32_t* row_ptr, const int32_t* col, int32_t 
       const auto kern = edges ? k_hook_sample<true> : k_hook_sample<false>;
       hipLaunchKernelGGL(kern, dim3(gn), dim3(kB), 0, s, row_ptr, col, n, nnz, cc, erec, first, next, c->d_status);
     }
-    if (!labels) compress(false);
+    compress(false);  // (the pick climbs for its samples one by one)
     {
       ET_PROF(c, s, "k_big_component");
       hipLaunchKernelGGL(k_big_component, dim3(1), dim3(kBigSample), 0, s, cc, n, sc, table);

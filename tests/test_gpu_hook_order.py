@@ -65,3 +65,30 @@ def test_ids_that_follow_the_shape(kind, n):
     if n >= 100000:
         p = np.random.default_rng(n).permutation(n)
         assert t < 12 * _run(*_csr(p[u], p[v], n))[2]
+
+
+@pytest.mark.parametrize("kind", ["halves", "near", "shaken"])
+def test_pick_samples_compressed_trees(kind):
+    """Above 2^20 vertices, where labels follow the pick: its 1024 samples are
+    one gather each (20 us), not a climb of the second round's chains."""
+    n = (1 << 21) + 5
+    if kind == "shaken":  # a strip with its ids exchanged within short distances
+        u, v = _pairs("strip", n)
+        at = np.empty(n, dtype=np.int64)
+        at[np.argsort(np.arange(n) + 64 * np.random.default_rng(7).random(n))] = np.arange(n)
+        u, v = at[u], at[v]
+    else:
+        u, v = _pairs(kind, n)
+    rp, col = _csr(u, v, n)
+    ctx = et.Context()
+    d = [torch.from_numpy(a).cuda() for a in (rp, col)]
+    et.et_bridges(*d, ctx=ctx)
+    ctx.profile(True, only="k_big_component")
+    for _ in range(3):
+        mask, count = et.et_bridges(*d, ctx=ctx)
+    launches, total, _ = ctx.profile_read()["k_big_component"]
+    ctx.check()
+    ctx.close()
+    want, want_count = oracle.bridges(rp, col)
+    assert count == want_count and np.array_equal(mask.cpu().numpy().view(np.uint32)[: len(want)], want)
+    assert total / launches < 0.08
