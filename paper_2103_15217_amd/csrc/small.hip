@@ -17,7 +17,7 @@
 //   3. successors over the grouped order (next sibling, else back up to the
 //      parent; the first child under its parent's down half-edge), the same
 //      rule as the multi-kernel build;
-//   4. list ranking of the tour: both half-edges of every 2^k-th node (and
+//   4. list ranking of the tour: both half-edges of a node in every 2^k (and
 //      the head) start a sublist that one lane walks, recording its length
 //      and down count, and per half-edge its rank and inclusive down count
 //      within the sublist and (in place of its successor, which no other
@@ -45,6 +45,7 @@ constexpr int kRoundsMax = 4;
 constexpr int kWavesMax = 16;       // wavefronts per workgroup at most
 constexpr uint16_t kEnd = 0xffff;   // list end, no node, unused label
 constexpr uint16_t kNoSucc = 0xfffe;  // a half-edge id of the root (not on the tour)
+constexpr uint32_t kSplit = 0x4000;   // of a successor: it starts a sublist
 constexpr int kDigitBits = 7;
 constexpr int kDigits = 1 << kDigitBits;
 constexpr int kCP = kDigits + 1;    // a wavefront's digit counters: one row, padded so rows start in other banks
@@ -188,6 +189,20 @@ struct SmallTree {
     __syncthreads();
   }
 
+  // Sublists: both half-edges of one node in every 2^m ids start one (so the
+  // runs down into and up out of a subtree both meet splitters), at a place that
+  // moves on by the golden ratio: with every 2^m-th id a tree of regular ids,
+  // for instance legs of every 8th id, had sublists of thousands (4000 nodes on
+  // 8 legs 1142 us, 36 now).
+  static __device__ __forceinline__ int shift(uint32_t n) { return max(0, clog2(n) - 9); }
+  static __device__ __forceinline__ uint32_t split_node(uint32_t chunk, int m) {
+    return (chunk << m) + ((__umul24(chunk, 0x9e37u) >> (16 - m)) & ((1u << m) - 1u));
+  }
+  // half-edge e as a successor
+  static __device__ __forceinline__ uint16_t code(uint32_t e, int m) {
+    return (uint16_t)(split_node((e >> 1) >> m, m) == (e >> 1) ? e | kSplit : e);
+  }
+
   // 2. and 3. children grouped by parent, successors
   __device__ __forceinline__ void tour(uint32_t n, uint32_t root, uint32_t* __restrict__ status) {
     const uint32_t E = 2 * n;
@@ -235,21 +250,22 @@ struct SmallTree {
       dst = tmp;
     }
     const uint16_t* ord = src;
+    const int m = shift(n);
 
     // 3. successors; the root sorts last (position n-1)
     for (uint32_t e = tid; e < E; e += kFT)
-      SUCC[e] = ((e >> 1) == root) ? kNoSucc : ((e & 1u) ? kEnd : (uint16_t)(e + 1));
+      SUCC[e] = ((e >> 1) == root) ? kNoSucc : ((e & 1u) ? kEnd : code(e + 1, m));
     __syncthreads();
     for (uint32_t k = tid; k + 1 < n; k += kFT) {
       const uint32_t c = ord[k];
       const uint16_t p = P[c];
       uint16_t nxt;
-      if (k + 2 < n && P[ord[k + 1]] == p) nxt = (uint16_t)(2 * ord[k + 1]);
-      else nxt = (p == root) ? kEnd : (uint16_t)(2 * p + 1);
+      if (k + 2 < n && P[ord[k + 1]] == p) nxt = code(2u * ord[k + 1], m);
+      else nxt = (p == root) ? kEnd : code(2u * p + 1, m);
       SUCC[2 * c + 1] = nxt;
       if (k == 0 || P[ord[k - 1]] != p) {
         if (p == root) SC[S_HEAD] = (int32_t)(2 * c);
-        else SUCC[2 * p] = (uint16_t)(2 * c);
+        else SUCC[2 * p] = code(2 * c, m);
       }
     }
     __syncthreads();
@@ -265,23 +281,21 @@ struct SmallTree {
   // 4. ranks and inclusive down counts of the half-edges
   __device__ __forceinline__ void ranks(uint32_t n, uint32_t root, uint32_t* __restrict__ status) {
     const uint32_t E = 2 * n;
-    // 4. sublists: both half-edges of every 2^m-th node id start one (so
-    // the runs down into and up out of a subtree both meet splitters),
-    // and so does the head; at most 1024 regular ones
-    const int m = max(0, clog2(n) - 9);
-    const uint32_t M = (1u << m) - 1u;
-    const uint32_t Sreg = 2 * ((n + M) >> m);
+    // 4. the sublists of the splitters, at most 1024, and the head's
+    const int m = shift(n);
+    const uint32_t Sreg = 2 * ((n + (1u << m) - 1u) >> m);
     const uint32_t S = Sreg + 1;
     const uint32_t head = (uint32_t)SC[S_HEAD];
-    const uint32_t hsub = ((head >> 1) & M) ? Sreg : (((head >> 1) >> m) << 1);
+    const bool hown = split_node((head >> 1) >> m, m) != head >> 1;  // the head is no splitter
+    const uint32_t hsub = hown ? Sreg : (((head >> 1) >> m) << 1);
     for (uint32_t s = tid; s < S; s += kFT) {
-      const uint32_t e0 = (s == Sreg) ? head : ((((s >> 1) << m) << 1) | (s & 1u));
-      const bool valid = (s == Sreg) ? ((head >> 1) & M) != 0 : (e0 < E && SUCC[e0] != kNoSucc);
+      const uint32_t e0 = (s == Sreg) ? head : (split_node(s >> 1, m) << 1) | (s & 1u);
+      const bool valid = (s == Sreg) ? hown : (e0 < E && SUCC[e0] != kNoSucc);
       uint32_t len = 0, dn = 0, nxs = kEnd;
       if (valid) {
-        uint32_t e = e0;
+        uint32_t e = e0, nx;
         for (;;) {
-          const uint32_t nx = SUCC[e];
+          nx = SUCC[e];
           SUCC[e] = (uint16_t)s;  // only this lane reads e's successor
           if (e & 1u) {
             R1[e >> 1] = (uint16_t)len;
@@ -291,17 +305,12 @@ struct SmallTree {
           }
           ++len;
           dn += !(e & 1u);
-          if (nx == kEnd) break;
-          if (nx >= E || len >= E) {
-            SC[S_BAD] = 1;
-            break;
-          }
-          if (!((nx >> 1) & M)) {
-            nxs = (((nx >> 1) >> m) << 1) | (nx & 1u);
-            break;
-          }
+          if ((nx & kSplit) || nx >= E || len >= E) break;  // (kEnd has that bit too)
           e = nx;
         }
+        const uint32_t to = nx & ~kSplit;
+        if (nx != kEnd && (!(nx & kSplit) || to >= E)) SC[S_BAD] = 1;
+        else if (nx != kEnd) nxs = (((to >> 1) >> m) << 1) | (to & 1u);
       }
       NX(0)[s] = (uint16_t)nxs;
       LD(0)[s] = (len << 16) | dn;
@@ -565,7 +574,7 @@ __global__ __launch_bounds__(kTreeLanes) void k_small_tree(
     tr.tour(n, root, status);
     for (uint32_t e = tid; e < 2 * n; e += kTreeLanes) {
       const uint16_t x = tr.SUCC[e];
-      succ[e] = x == kEnd ? -1 : x == kNoSucc ? -2 : (int32_t)x;
+      succ[e] = x == kEnd ? -1 : x == kNoSucc ? -2 : (int32_t)(x & ~kSplit);
     }
     __syncthreads();  // the ranking writes over the successors
   }
