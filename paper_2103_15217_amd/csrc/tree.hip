@@ -91,7 +91,11 @@ __global__ void k_succ(const uint32_t* __restrict__ keys, const int32_t* __restr
 // and appends each range's pairs to that range's place in `pairs` (a child
 // occurs once, so range b owns [b << shift, (b + 1) << shift)), and the second
 // pass stores them, all of one range close together in time and on one XCD, so
-// that its stores fill lines in the L2: 329 us.
+// that its stores fill lines in the L2: 329 us. Where the ids follow the shape
+// the stores of neighbours fill lines as they are, and pairs would only be
+// more bytes: 64 neighbours of the grouped order whose children lie in one
+// range are stored at once (a path in id order, 2^24 nodes: 265 -> 176 us, the
+// call 2044 -> 1960; 110 and 1995 when there was one pass only).
 constexpr int kPartThreads = 512;
 constexpr int kPartPer = 8;
 constexpr int kPartRanges = 512;  // at most; one lane each
@@ -120,7 +124,17 @@ __global__ __launch_bounds__(kPartThreads) void k_succ_part(const uint32_t* __re
     at[r] = -1;
     if (k >= n) continue;
     succ_scalars(k, n, sc, status);
-    if (succ_at(keys, vals, n, k, root, sc, succ, &pr[r].x, &pr[r].y)) at[r] = atomicAdd(&cnt[pr[r].x >> shift], 1);
+    const bool has = succ_at(keys, vals, n, k, root, sc, succ, &pr[r].x, &pr[r].y);
+    const int32_t range = has ? pr[r].x >> shift : -1;
+    // (the lanes beyond n are the last ones: the others are here)
+    const uint64_t mask = __ballot(has);
+    if (mask == 0) continue;
+    const int32_t lead = __shfl(range, __ffsll((unsigned long long)mask) - 1, 64);
+    if (__ballot(range == lead) == mask) {
+      if (has) succ[2 * pr[r].x + 1] = pr[r].y;
+    } else if (has) {
+      at[r] = atomicAdd(&cnt[range], 1);
+    }
   }
   __syncthreads();
   // a lane per range: its start in the tile, its place in `pairs`
