@@ -90,13 +90,15 @@ int et_ctx_status(et_ctx* ctx, hipStream_t s);
 int et_ctx_status_bits(et_ctx* ctx, hipStream_t s, uint32_t* h_bits);
 
 /* Tunable launch parameters of this context (used by later calls):
- *   "lr_k1_log2"    list ranking, level 1: one splitter per 2^v ids at most
- *                   (1..10, default 4); a list of L elements uses
+ *   "lr_k1_log2"    list ranking, level 1: one splitter per 2^v ids (1..10,
+ *                   default 4); a list of L elements uses
  *                   min(v, max(2, (floor(log2 L) - 15) / 2)), below 5 one
- *                   more if it is alone and has at least 24 000 000
+ *                   more (so up to v + 1) if it is alone and L >= 2^25
  *   "lr_per_wave1"  level 1: sublists owned by one wavefront at most
  *                   (64..65536, default 256); fewer when that would leave
- *                   under 4096 wavefronts, never under 64
+ *                   under 4096 wavefronts, at most 64 in one list of 2^25
+ *                   elements and more (128 in a tree's tour), and never under
+ *                   64. Batches of trees and graphs always use 64
  *   "lr_kn_log2"    upper levels: one splitter per 2^v elements at most (1..10,
  *                   default 3)
  *   "lr_per_waven"  upper levels: sublists per wavefront at most (64..65536,

@@ -881,7 +881,7 @@ struct LrPlan {
   std::vector<LrLevel> lv;
 };
 
-constexpr int32_t kLongList = 24000000;
+constexpr int32_t kLongList = 1 << 25;
 constexpr int kLongSpacing = 5;
 constexpr int32_t kShortLevel = 1 << 21;
 
@@ -903,11 +903,12 @@ static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weight
   // walk is bound by its dependent steps rather than by line fetches, so the
   // spacing drops by half per factor 4 of length (2^24 -> 16, 2^22 -> 8,
   // 2^20 -> 4), down to 4; the context's value is the largest spacing used.
-  // From 24M elements on a spacing below 32 is doubled: the sublists' offsets,
-  // which every element gathers, are then half as many (list of 2^25 elements,
-  // spacing 16 / 32 / 64: 1687 / 1614 / 1808 us; trees of 2^24 nodes of three
-  // shapes 3136 / 3061 / 3130, 3155 / 3102 / 3217 and 3045 / 2958 / 3113; but
-  // 2^23 1537 / 1576, and a batch of 2^25 local elements 3899 / 4070).
+  // From 2^25 elements on a spacing below 32 is doubled: the sublists' offsets,
+  // which every element gathers, are then half as many. Spacing 16 / 32, us:
+  // random lists of 24.5M elements 1220 / 1242, of 2^25 1719 / 1687, of 2^26 4878 /
+  // 4635; random trees of 12.5M nodes 2348 / 2368, of 2^24 3131 / 3075, a path
+  // 2172 / 2222 and 3056 / 2964, 30M 6377 / 6183; a batch of 2^25 local elements
+  // 3899 / 4070.
   pl->ks1 = std::min(c->lr.k1_log2, std::max(2, (floor_log2(L) - 15) / 2));
   if (!local && L >= kLongList && pl->ks1 < kLongSpacing) ++pl->ks1;
   pl->S1 = (int32_t)(((int64_t)L + (1 << pl->ks1) - 1) >> pl->ks1);
@@ -981,7 +982,19 @@ static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32
   // 735, 16 of 2^20 976 / 858 / 902, 4 of 2^22 1015 / 923 / 1096; one tree of
   // 2^24 866 / 901 / 900.
   const bool local = local_len > 0;
-  const int32_t per_wave1 = local ? 64 : pl.per_wave1;
+  // With the doubled spacing a wavefront covers twice as much of the array, and
+  // with 256 sublists there are only half as many of them. Where ids follow the
+  // order of the list its lines then leave the cache half used; fewer sublists
+  // keep them and cost a random list nothing, a random tour little. 256 / 128 / 64
+  // a wavefront (spacing 16 and 256), us: list of 2^25 elements in order 1159 /
+  // 1067 / 996 (992), random 1688 / 1656 / 1687, 2^26 in order 2231 / 2079 / 1907
+  // (1927), random 4543 / 4595 / 4635; tree of 2^24 nodes on 64 legs 2282 / 2266 /
+  // 2111 (2160), random 3055 / 3075 / 3142, 30M on 64 legs 4428 / 3752 / 3472 (3594),
+  // random 6236 / 6183 / 6081.
+  const int32_t long_wave = tree_weights ? 128 : 64;
+  const int32_t per_wave1 = local                ? 64
+                            : L >= kLongList ? std::min(pl.per_wave1, long_wave)
+                                             : pl.per_wave1;
   const dim3 g1(walk_grid(S1 + H, per_wave1));
   if (tree_weights) {
     ET_PROF(c, s, "k_walk1<true>");
