@@ -164,7 +164,7 @@ int et_list_rank(et_ctx* ctx, const int32_t* d_succ, int32_t len, const int32_t*
  */
 #define ET_NOALLOC_MAX_LEN (1 << 20)
 #define ET_NOALLOC_MAX_HEADS (1 << 16)
-#define ET_NOALLOC_SCRATCH_BYTES (40u << 20)
+#define ET_NOALLOC_SCRATCH_BYTES (44u << 20)
 int et_list_rank_noalloc(et_ctx* ctx, const int32_t* d_succ, int32_t len, const int32_t* d_heads,
                          int32_t n_heads, int32_t* d_rank, hipStream_t s);
 
