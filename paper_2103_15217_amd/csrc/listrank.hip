@@ -310,15 +310,15 @@ __global__ __launch_bounds__(kWalkThreads) void k_walkN(
 // end. 20 us for 2000 elements, 34 for 8000.
 //   IN_REC   level records {next, len, down} (next == -3 unused); the heads
 //            are the H records from hb on
-//   IN_SUCC, IN_TREE, IN_PAIR   a whole list, as k_walk1's W = 0 (plain), W = 0
-//            (tree half-edges) and W > 0 inputs; the level-1 records are then
-//            one sublist per element (PAIR2: with the 16-byte records), or,
-//            where `rank` is given, the ranks are written themselves
+//   IN_SUCC, IN_PAIR   a whole list, as k_walk1's W = 0 (plain) and W > 0
+//            inputs; the level-1 records are then one sublist per element
+//            (PAIR2: with the 16-byte records), or, where `rank` is given, the
+//            ranks are written themselves
 // Elements whose predecessor chain does not start at a head are unreachable
 // (malformed input), as are elements that no walk passes.
 constexpr int kFinalThreads = 1024;
 constexpr int kFinalSub = 2;  // sublists per lane: 1024 by chunks, kLdsHeads by heads
-enum { IN_REC, IN_SUCC, IN_TREE, IN_PAIR, IN_PAIR2 };
+enum { IN_REC, IN_SUCC, IN_PAIR, IN_PAIR2 };
 
 struct RankLds {  // bytes of the dynamic LDS of k_rank_lds
   uint32_t dn, acl, acd, nxt, pred, top, hb, total;
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
   static_assert(kLdsMax <= 0x3ffe && 1024 + kLdsHeads <= 0x7fff, "the codes of NXT");
   constexpr uint32_t kNone = 0xffffu;
   constexpr bool kLen = IN == IN_REC;                    // element lengths other than 1
-  constexpr bool kDn = IN != IN_SUCC && IN != IN_TREE;   // element weights from the input
+  constexpr bool kDn = IN != IN_SUCC;                    // element weights
   extern __shared__ __align__(16) unsigned char lds[];
   const int32_t S = (T + (1 << ks) - 1) >> ks, SM = S + H;
   const RankLds lay = rank_lds_layout((uint32_t)T, (uint32_t)SM);
@@ -401,7 +401,6 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
     } else {
       nx = in[e];
       used = nx != -2;
-      if (IN == IN_TREE) d = (e & 1) == 0;
     }
     uint32_t code = kUnused;
     if (used) {
@@ -456,9 +455,9 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
         NXT[e] = (uint16_t)(kWalked | (uint32_t)s);
         ++passed;
         const int32_t l = kLen ? LEN[e] : 1;
-        const int32_t d = kDn ? DN[e] : (IN == IN_TREE ? (int32_t)((e & 1) == 0) : 0);
+        const int32_t d = kDn ? DN[e] : 0;
         LEN[e] = al;
-        if (IN != IN_SUCC) DN[e] = ad;
+        if (kDn) DN[e] = ad;
         al += l;
         ad = wadd(ad, d);
         if (nx >= kEnd) {
@@ -557,7 +556,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
     if (c & kWalked) {
       ++walked;
       const uint32_t s = c & (kWalked - 1u);
-      o = make_int2(ACL[s] + LEN[e], IN != IN_SUCC ? wadd(ACD[s], DN[e]) : 0);
+      o = make_int2(ACL[s] + LEN[e], kDn ? wadd(ACD[s], DN[e]) : 0);
       if (!PRED[s]) unreached = true;
     } else {
       unreached = true;
@@ -568,7 +567,6 @@ __global__ __launch_bounds__(kFinalThreads) void k_rank_lds(
     }
     off[e] = o;
     if (IN == IN_SUCC) packed[e] = (uint64_t)(uint32_t)e;
-    if (IN == IN_TREE) packed[e] = (uint64_t)(uint32_t)e | ((uint64_t)((e & 1) == 0) << 48);
     if (IN == IN_PAIR) packed[e] = (uint64_t)(uint32_t)e | ((uint64_t)(uint32_t)in[2 * e + 1] << 32);
     if (IN == IN_PAIR2)
       reinterpret_cast<ulonglong2*>(packed)[e] =
@@ -888,9 +886,9 @@ constexpr int32_t kShortLevel = 1 << 21;
 static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weighted, bool local, LrPlan* pl) {
   const int32_t lds_max = H <= kLdsHeads ? kLdsMax : kLdsMaxHeads;
   // One workgroup ranks a short list by itself, one launch in place of three.
-  // Tree builds by this / by level 1 and a final level: 60 / 68 us at 2000
-  // half-edges, 74 / 80 at 8000, 91 / 87 at 12000; plain lists (whose ranks
-  // it writes itself) 16 / 29, 29 / 38 and 39 / 39 us
+  // By this / by level 1 and a final level, us: plain lists (whose ranks it
+  // writes itself) 16 / 29 at 2000 elements, 29 / 38 at 8000, 39 / 39 at 12000;
+  // weighted lists 29 / 41 and 43 / 47, in id order 26 / 31 and 35 / 32.
   pl->direct = L <= kLdsDirect && H <= kLdsHeads;
   if (pl->direct) {
     pl->T1 = L;
@@ -961,10 +959,9 @@ static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32
   const int32_t S1 = pl.S1, T1 = pl.T1, cont_max = pl.cont_max;
   if (pl.direct) {
     const int ks = rank_lds_ks(L);
-    const auto kern = tree_weights    ? k_rank_lds<IN_TREE>
-                      : weighted == 2 ? k_rank_lds<IN_PAIR2>
-                      : weighted      ? k_rank_lds<IN_PAIR>
-                                      : k_rank_lds<IN_SUCC>;
+    if (tree_weights) return ET_EINVAL;  // (never: small.hip builds trees of so few half-edges)
+    static_assert(2 * (kSmallTreeMax + 1) > kLdsDirect, "a tour that comes here is longer");
+    const auto kern = weighted == 2 ? k_rank_lds<IN_PAIR2> : weighted ? k_rank_lds<IN_PAIR> : k_rank_lds<IN_SUCC>;
     ET_PROF(c, s, "k_rank_lds");
     hipLaunchKernelGGL(kern, dim3(1), dim3(kFinalThreads), rank_lds_bytes(L, H), s, succ, L, heads, 0, H,
                        empty_head_ok, ks, kSalt,
@@ -1056,8 +1053,7 @@ static int list_rank_launch(Ctx* c, const LrPlan& pl, const int32_t* succ, int32
 int list_rank_prepare() {
   for (const void* kern :
        {reinterpret_cast<const void*>(k_rank_lds<IN_REC>), reinterpret_cast<const void*>(k_rank_lds<IN_SUCC>),
-        reinterpret_cast<const void*>(k_rank_lds<IN_TREE>), reinterpret_cast<const void*>(k_rank_lds<IN_PAIR>),
-        reinterpret_cast<const void*>(k_rank_lds<IN_PAIR2>)})
+        reinterpret_cast<const void*>(k_rank_lds<IN_PAIR>), reinterpret_cast<const void*>(k_rank_lds<IN_PAIR2>)})
     if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)rank_lds_bytes(kLdsMax, kLdsHeads)) != hipSuccess)
       return ET_EHIP;
