@@ -923,19 +923,17 @@ static void list_rank_plan(Ctx* c, Scratch& sc, int32_t L, int32_t H, int weight
   for (;;) {
     LrLevel& cur = pl->lv.back();
     if (cur.T <= lds_max) break;
-    // The walk of a level lasts as long as its longest sublist, about 2^ks
-    // ln(sublists) dependent steps of 0.5 us, so three levels of spacing 4 are
-    // quicker than two of 8, unless a level moves enough bytes, or there are so
-    // many heads that the lists are short and a level shrinks little; but not
-    // if one of 8 and one of 4 come to a last level of half its size, whose
-    // workgroup takes 3.3 us per 1000 elements. Calls with spacing 8 / by this
-    // rule, us: 10^6 nodes with tables 335 / 328, 10^6 weighted elements 149 /
-    // 142, 2^21 nodes 510 / 496, 3 * 10^5 elements 112 / 97, 2^23 482 / 462 (and
-    // 2^22 292 / 296: how long the longest sublist is varies by some us from list
-    // to list); with 1747 heads in 2^20 elements spacing 4 would cost 127 / 136.
+    // The walk of a short level lasts as long as its longest sublist, about 2^ks
+    // ln(sublists) dependent steps of 0.5 us (that of a long one as long as its
+    // total work), so there three levels of spacing 4 are quicker than two of 8,
+    // unless there are so many heads that the lists are short and a level shrinks
+    // little. Calls with spacing 8 / by this rule, us: 10^6 nodes with tables 335
+    // / 328, 10^6 weighted elements 149 / 142, 2^21 nodes 510 / 496, 3 * 10^5
+    // elements 112 / 97, 2^23 482 / 462 (and 2^22 292 / 296: how long the longest
+    // sublist is varies by some us from list to list); with 1747 heads in 2^20
+    // elements spacing 4 would cost 127 / 136.
     const int kn = c->lr.kn_log2;
-    const bool small_last = ((int64_t)cur.T >> 4) + H > lds_max * 3 / 4 && ((int64_t)cur.T >> 5) + H <= lds_max / 2;
-    const int widest = cur.T <= kShortLevel && H <= kLdsHeads && !small_last ? std::min(2, kn) : kn;
+    const int widest = cur.T <= kShortLevel && H <= kLdsHeads ? std::min(2, kn) : kn;
     int ks = std::min(2, c->lr.kn_log2);
     while (ks < widest && (((int64_t)cur.T + (1 << ks) - 1) >> ks) + H > lds_max) ++ks;
     const int32_t S = (int32_t)(((int64_t)cur.T + (1 << ks) - 1) >> ks);
