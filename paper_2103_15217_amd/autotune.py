@@ -251,7 +251,9 @@ def tune(workload="single", log2n=24, graph_log2n=22, reps=3, rounds=2, log=prin
             ctx.set_param(k, v)
         return sum(_best_ms(f, reps) for f in parts)
 
-    best, final, default, table = coordinate_search(cost, rounds=rounds, log=log)
+    # a batch takes 64 sublists a wavefront whatever lr_per_wave1 says
+    grid = {k: v for k, v in GRID.items() if not (workload == "batch" and k == "lr_per_wave1")}
+    best, final, default, table = coordinate_search(cost, grid, rounds=rounds, log=log)
     ctx.check()
     log(f"best {best} -> {final:.3f} ms (default {default:.3f} ms)")
     return best, final, default, table
