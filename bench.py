@@ -7,7 +7,9 @@ One step = the whole path over one batch of synthetic input:
   2^22-vertex, ~2^25-edge sparse graph with 4096 planted bridge chains.
 Inputs are generated on the host, copied to HBM before timing, and stay
 resident. W untimed warmup steps, then K timed steps between two device
-synchronisations. Prints one JSON line.
+synchronisations. Prints one JSON line of at most 8000 characters (a log's end
+holds it whole); what does not fit goes to stderr before it, with everything
+else, as one line after "[bench] all figures:".
 
 value = (sum over the three trees of (nodes + queries) + graph edges) per
 second of step time. Per-component rates, per-kernel times (HIP events on
@@ -39,7 +41,7 @@ ALG_BYTES = {
     "k_walk1<false>": (8, "half-edge", lambda w: 2 * (w["graph_n"] - 1)),
     # LCA: 12 B streamed (x, y, out) + 4 gathers of 16-B records per query
     "k_lca": (76, "query", lambda w: w["q"]),
-    # first hooking round: row pointers (8 B) and up to two columns (8 B) per vertex
+    # second hooking round: row pointers (8 B) and up to two columns (8 B) per vertex
     "k_hook_sample": (16, "vertex", lambda w: w["graph_n"]),
     # path tops: inlabel, parent and the parent's gathered inlabel read; about half the nodes
     # are tops, read their depth and write an 8-B head entry and a 4-B parent-path label
@@ -124,6 +126,42 @@ def copy_calibration(mib):
 
 def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
+
+
+LINE_LIMIT = 8000
+# what leaves the printed line first when it is too long
+DETAILS = ("kernel_rooflines", "components.small_batches", "components.small_graph_batches", "components.protocol",
+           "components.naive_lca", "components.query_engines", "components.serving", "components.list_ranking",
+           "components.bridges_methods", "components.edge_list_build", "kernels_ms_per_step",
+           "components.bridges_batched", "components.batched", "components.concurrent_step")
+
+
+def _rounded(x):
+    if isinstance(x, float):
+        return float(f"{x:.6g}")
+    if isinstance(x, dict):
+        return {k: _rounded(v) for k, v in x.items()}
+    if isinstance(x, (list, tuple)):
+        return [_rounded(v) for v in x]
+    return x
+
+
+def result_line(result, limit=LINE_LIMIT):
+    """The printed line: the top level as it is, figures below it to six
+    digits, and details left out (named in "on_stderr") until it fits."""
+    out = {k: v if isinstance(v, float) else _rounded(v) for k, v in result.items()}
+    line = json.dumps(out)
+    for name in DETAILS:
+        if len(line) <= limit:
+            break
+        at = out
+        *path, last = name.split(".")
+        for k in path:
+            at = at.get(k) or {}
+        if at.pop(last, None) is not None:
+            out.setdefault("on_stderr", []).append(name)
+            line = json.dumps(out)
+    return line
 
 
 def main():
@@ -346,7 +384,8 @@ def main():
         log("timing the CPU oracle on the sample")
         result["cpu_baseline"], result["parity"] = cpu_baseline(trees[0], qx, qy, rp, col, ginfo, et, d, ctx,
                                                                 d_parent[0], d_qx, d_qy, d_rp, d_col)
-    print(json.dumps(result), flush=True)
+    log("all figures: " + json.dumps(result))
+    print(result_line(result), flush=True)
 
 
 def _gpu_ms(fn, reps=3):
