@@ -149,7 +149,7 @@ __device__ __forceinline__ int32_t clampi(int32_t x, int32_t lo, int32_t hi) { r
 // decides for itself and ids strictly decrease upwards, so all these links are
 // edges of one forest and need no compare-and-swap (a device-scope one per
 // vertex, at 24 G/s, and its dependent climb made this round 316 us at 2^22
-// vertices and 2^25 edges; with plain stores it takes 81 us). The trees are
+// vertices and 2^25 edges; with plain stores it takes 86 us). The trees are
 // chains as long as the graph where ids follow its shape, which a later link
 // would climb step by step: a full compression comes before any. row_ptr must
 // be monotone from 0 to nnz, anything else is flagged.

@@ -197,8 +197,8 @@ __device__ __forceinline__ void walk1_body(
   }
 }
 
-// Bound by random accesses, a load and a store per element (2^25 elements 1.1
-// ms, 30 G/s; a random tree's 2^25 half-edges 865 us). Fewer wavefronts at a
+// Bound by random accesses, a load and a store per element (2^25 elements 1.2
+// ms, 28 G/s; a random tree's 2^25 half-edges 930 us). Fewer wavefronts at a
 // time are slower, and so are shorter runs of sublists per wavefront, unless
 // the lists are local (see list_rank_launch): then xcd hands each XCD a
 // contiguous range of the sublists.
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(kWalkThreads) void k_walkN(
 // Against jumping over every element, limited to 4096, a list of sublists
 // needs one k_walkN and k_push_down level less: 10^6-node build 355 -> 345 us.
 // Bound by LDS bandwidth: the wavefronts' steps until their longest sublists
-// end. 20 us for 2000 elements, 34 for 8000.
+// end. 20 us for 2000 elements, 30 for 8000.
 //   IN_REC   level records {next, len, down} (next == -3 unused); the heads
 //            are the H records from hb on
 //   IN_SUCC, IN_PAIR   a whole list, as k_walk1's W = 0 (plain) and W > 0

@@ -554,7 +554,7 @@ __global__ __launch_bounds__(kFT, kFT == 1024 ? 8 : 1) void k_small_batch(
 // same steps, with everything a multi-kernel build keeps written out. There a
 // build of that size is bound by its launches (about 17, each waiting for the
 // one before): build and 1000 queries took 43 us at 256 nodes, 54 at 1000, 73
-// at 3000 and 76 at 4096; here 20, 21, 45 and 55 (20 is what the host needs
+// at 3000 and 76 at 4096; here 23, 22, 39 and 50 (20 is what the host needs
 // for the two calls). 256 lanes instead of 1024 are no faster at 256 nodes and
 // 39 us at 1000.
 // On malformed input the tables hold values that no later call trips over.
